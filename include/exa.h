@@ -259,14 +259,19 @@ exa_status exa_jprod(exa_model* m, const double* x, const double* v, double* Jv,
  * patterns declared over the same data arrays add their contributions
  * (Jacobian entry times w of its row, members in declaration order) to one
  * variable reference in the lane; the reduction then sums these per
- * variable in a fixed order (Sec. 7.2.3).  An augmentation term that is
+ * variable in a fixed order (Sec. 7.2.3), or the evaluation kernel finishes
+ * a variable itself, in the same order, where all its contributions come
+ * through strictly increasing index columns.  Contributions to a variable
+ * that every point of a data set shares are first added over runs of
+ * consecutive points.  An augmentation term that is
  * plus or minus one variable, and its data set's only contribution to that
  * reference, contributes plus or minus w of its row: the reduction reads
  * that weight from w itself, at the same place in the order. */
 exa_status exa_jtprod(exa_model* m, const double* x, const double* w, double* Jtw,
                       exa_stream_t stream);
 /* (sigma grad^2 f + sum y_j grad^2 g_j) v into Hv [nvar] (Sec. 2.1.3 hprod).
- * Contributions are summed as exa_jtprod sums them.  A variable reference
+ * Contributions are summed as exa_jtprod sums them (the models' work space
+ * for exa_hprod_noalloc counts every one of them).  A variable reference
  * of a data set whose every entry is the only H v contribution to its
  * variable (ACOPF's branch flows, for instance) is written into Hv by the
  * evaluation kernel; the reduction sums the other variables. */
@@ -415,7 +420,9 @@ exa_status exa_eval_set_schedule(exa_model* m, uint32_t mask, int32_t block, int
  * counted as exa_kernel_bytes counts one callback (x, v entries once over
  * the launch); out4[2], out4[3] = bytes read and written by the reduction
  * launch (segment maps, each buffer entry once, each output once, and the
- * objective partials when there are several).  Works on host-only models. */
+ * objective partials when there are several).  On a device model, variables
+ * whose sums the evaluation launch finishes itself count there and not in
+ * the reduction; host-only models report every sum as reduced. */
 exa_status exa_eval_bytes(const exa_model* m, uint32_t mask, int64_t* out4);
 /* Launch timing of exa_eval, for measurement.  With enable != 0, the next
  * 1024 exa_eval calls of this model record HIP events on their stream
@@ -498,7 +505,9 @@ exa_status exa_counters(const exa_model* m, int64_t* out9);
  * callback of every instance in ONE evaluation launch over a tile list of
  * (instance, unit, data range) tiles, one workgroup per tile, with the
  * instances binned over the 8 XCDs by cost (or, with EXA_UNITS_SEPARATE,
- * one such launch per callback, one after another); then ONE launch of every
+ * one such launch per callback, one after another; or one launch per kind of
+ * instance where index columns of different shape, such as a permuted one,
+ * make instances finish their sums differently); then ONE launch of every
  * instance's deterministic reductions (gradient, J^T w, H v, parameter
  * adjoint segment sums, objective partials), plus one small launch when a
  * segment is longer than 1024 entries.  The launches are recorded once into

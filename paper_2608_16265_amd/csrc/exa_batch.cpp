@@ -51,12 +51,19 @@ int64_t aligned(int64_t n) { return (n + kAlign - 1) / kAlign * kAlign; }
 struct exa_batch {
     std::vector<exa_model*> models;
     int B = 0;
-    std::shared_ptr<Module> module;
-    // code of the batch's own when the instances disagree on which index
-    // columns are 0, 1, ..., n-1 (then only the columns that are so in every
-    // instance use the data point itself), with its liveness records
-    bool own_code = false;
-    std::map<std::pair<int, int>, UnitLive> live;
+    // Instances whose sums are finished by the same units (Model::own_sig) run
+    // the same code, one evaluation launch per such class (nearly always one
+    // class).  A class has code of its own when its instances disagree on which
+    // index columns count up by one (then only the columns that do in every
+    // instance use the data point itself), with its liveness records.
+    struct Class {
+        std::shared_ptr<Module> module;
+        bool own_code = false;
+        std::map<std::pair<int, int>, UnitLive> live;
+        std::vector<int> inst;
+    };
+    std::vector<Class> classes;
+    std::vector<int> cls;              // class of each instance
     DeviceState mem;                   // owns every device array below
     ExaInstDev* inst = nullptr;        // per-instance tables (device)
     std::vector<int64_t> offsets;      // kNoff * (B + 1)
@@ -83,17 +90,21 @@ struct exa_batch {
         bool fused = true, tuned = false;
         bool unstaged = false;               // each lane's own output stores (EXA_UNSTAGED)
         std::vector<std::vector<int>> bins;  // instances per XCD
-        ExaTile* tiles = nullptr;
-        int64_t ntiles = 0;
-        ExaTile* atiles = nullptr;           // parameter adjoint launch
-        int64_t antiles = 0;
         // EXA_UNITS_SEPARATE: one launch per callback (mode, tiles, count)
         struct Part {
             int mode;
             ExaTile* tiles;
             int64_t ntiles;
         };
-        std::vector<Part> parts;
+        struct Launch {                      // per class
+            int units = EXA_UNITS_PER_CALLBACK;
+            ExaTile* tiles = nullptr;
+            int64_t ntiles = 0;
+            ExaTile* atiles = nullptr;       // parameter adjoint launch
+            int64_t antiles = 0;
+            std::vector<Part> parts;
+        };
+        std::vector<Launch> launch;
         int64_t tuned_ns = 0;
         ExaBatchJob* jobs = nullptr;
         int32_t* blocks = nullptr;
@@ -147,32 +158,36 @@ struct exa_batch {
 namespace {
 
 // The exa_eval mask whose tiles a batch mask launches (the Lagrangian
-// gradient is the gradient and J^T y tiles; the adjoint has a launch of its
-// own).
-uint32_t eval_mask(uint32_t mask) {
+// gradient is the gradient and J^T y tiles, with EXA_EV_LAG where units finish
+// it; the adjoint has a launch of its own).
+uint32_t eval_mask(const Model& M, uint32_t mask) {
     uint32_t e = mask & EXA_EV_ALL;
-    if (mask & EXA_EV_LAG) e |= EXA_EV_GRAD | EXA_EV_JTPROD;
+    if (mask & EXA_EV_LAG) e |= EXA_EV_GRAD | EXA_EV_JTPROD | (M.lag_units ? EXA_EV_LAG : 0u);
     return e;
 }
 
 // The units a batch mask can run as asked: EXA_UNITS_SEPARATE needs two
-// callbacks or more; the others as exa_eval allows them.
+// callbacks or more (and no Lagrangian gradient units, which run in the
+// several-callback kernels); the others as exa_eval allows them.
 int batch_units(uint32_t em, int units) {
     if (!em) return EXA_UNITS_PER_CALLBACK;
-    if (units == EXA_UNITS_SEPARATE) return eval_modes(em, false).size() > 1 ? units : EXA_UNITS_PER_CALLBACK;
+    if (units == EXA_UNITS_SEPARATE)
+        return eval_modes(em, false).size() > 1 && !(em & EXA_EV_LAG) ? units : EXA_UNITS_PER_CALLBACK;
     return valid_units(em, units);
 }
 
 // Modes of the evaluation launch(es) of a mask under units.
-std::vector<int> modes_of(uint32_t em, int units) {
+std::vector<int> modes_of(const Model& M, uint32_t em, int units) {
     if (!em) return {};
     if (units == EXA_UNITS_SEPARATE) return eval_modes(em, false);
-    return launch_modes(em, units);
+    return launch_modes(M, em, units);
 }
 
-const std::vector<int>& main_modes(const exa_batch::Sched& S, uint32_t mask, std::vector<int>& tmp) {
-    tmp = modes_of(eval_mask(mask), S.units);
-    return tmp;
+const Model& lead_of(const exa_batch& b, int c) { return b.models[b.classes[c].inst[0]]->impl; }
+
+const std::map<std::pair<int, int>, UnitLive>* live_of(const exa_batch& b, int i) {
+    const exa_batch::Class& C = b.classes[b.cls[i]];
+    return C.own_code ? &C.live : nullptr;
 }
 
 // A launch of one plain mode runs that mode's own kernel (exa_k_<mode>);
@@ -183,16 +198,16 @@ bool single_kernel(const std::vector<int>& modes) { return modes.size() == 1 && 
 // instances are binned over the XCDs.
 std::vector<int64_t> instance_cost(const exa_batch& b, uint32_t mask, int units, bool fused) {
     std::vector<int64_t> cost(b.B, 0);
-    const uint32_t em = eval_mask(mask);
     for (int i = 0; i < b.B; ++i) {
         const Model& M = b.models[i]->impl;
+        const uint32_t em = eval_mask(M, mask);
         int64_t rd = 0, wr = 0;
         if (em) {
-            kernel_bytes(M, modes_of(em, batch_units(em, units)), fused, rd, wr, b.own_code ? &b.live : nullptr);
+            kernel_bytes(M, modes_of(M, em, batch_units(em, units)), fused, rd, wr, live_of(b, i));
             cost[i] += rd + wr;
         }
         if (mask & EXA_EV_ADJ) {
-            kernel_bytes(M, {M_ADJ}, fused, rd, wr, b.own_code ? &b.live : nullptr);
+            kernel_bytes(M, {M_ADJ}, fused, rd, wr, live_of(b, i));
             cost[i] += rd + wr;
         }
     }
@@ -245,7 +260,8 @@ void instance_tiles(const exa_batch& b, int i, const std::vector<int>& modes, bo
         }
         for (ExaTile& x : t) {
             x.inst = i;
-            if (tagged && x.pat != ((M_GRAD << EXA_MODE_SHIFT) | EXA_ZERO_TILE)) x.pat |= mode << EXA_MODE_SHIFT;
+            if (tagged && x.pat != ((M_GRAD << EXA_MODE_SHIFT) | EXA_ZERO_TILE))
+                x.pat |= tile_mode(mode) << EXA_MODE_SHIFT;
         }
         out.insert(out.end(), t.begin(), t.end());
     }
@@ -276,37 +292,41 @@ ExaTile* upload_binned(exa_batch& b, const exa_batch::Sched& S, const std::vecto
 
 void set_batch_schedule(exa_batch& b, uint32_t mask, int block, int epl, bool fused, int units) {
     exa_batch::Sched& S = b.sched[mask];
-    const uint32_t em = eval_mask(mask);
-    S.units = batch_units(em, units);
+    S.units = batch_units(eval_mask(lead_of(b, 0), mask), units);
     S.block = block;
     S.epl = epl;
     S.fused = fused;
     if (S.bins.empty()) make_bins(b, S, mask);
     const int64_t tp = (int64_t)block * epl;
-    std::vector<int> tmp;
-    const std::vector<int>& modes = main_modes(S, mask, tmp);
-    b.mem.release(S.tiles);
-    b.mem.release(S.atiles);
-    for (auto& p : S.parts) b.mem.release(p.tiles);
-    S.tiles = nullptr;
-    S.ntiles = 0;
-    S.parts.clear();
-    std::vector<std::vector<ExaTile>> per(b.B), adj(b.B);
-    if (S.units == EXA_UNITS_SEPARATE) {
-        for (int mode : modes) {
-            for (auto& v : per) v.clear();
-            for (int i = 0; i < b.B; ++i) instance_tiles(b, i, {mode}, false, em, tp, fused, per[i]);
-            exa_batch::Sched::Part part{mode, nullptr, 0};
-            part.tiles = upload_binned(b, S, per, part.ntiles);
-            S.parts.push_back(part);
+    S.launch.resize(b.classes.size());
+    for (size_t c = 0; c < b.classes.size(); ++c) {
+        exa_batch::Sched::Launch& Lc = S.launch[c];
+        const std::vector<int>& inst = b.classes[c].inst;
+        const Model& M = lead_of(b, (int)c);
+        const uint32_t em = eval_mask(M, mask);
+        b.mem.release(Lc.tiles);
+        b.mem.release(Lc.atiles);
+        for (auto& p : Lc.parts) b.mem.release(p.tiles);
+        Lc = exa_batch::Sched::Launch();
+        Lc.units = batch_units(em, units);
+        const std::vector<int> modes = modes_of(M, em, Lc.units);
+        std::vector<std::vector<ExaTile>> per(b.B), adj(b.B);
+        if (Lc.units == EXA_UNITS_SEPARATE) {
+            for (int mode : modes) {
+                for (auto& v : per) v.clear();
+                for (int i : inst) instance_tiles(b, i, {mode}, false, em, tp, fused, per[i]);
+                exa_batch::Sched::Part part{mode, nullptr, 0};
+                part.tiles = upload_binned(b, S, per, part.ntiles);
+                Lc.parts.push_back(part);
+            }
+        } else if (!modes.empty()) {
+            for (int i : inst) instance_tiles(b, i, modes, !single_kernel(modes), em, tp, fused, per[i]);
+            Lc.tiles = upload_binned(b, S, per, Lc.ntiles);
         }
-    } else if (!modes.empty()) {
-        for (int i = 0; i < b.B; ++i) instance_tiles(b, i, modes, !single_kernel(modes), em, tp, fused, per[i]);
-        S.tiles = upload_binned(b, S, per, S.ntiles);
-    }
-    if (mask & EXA_EV_ADJ) {
-        for (int i = 0; i < b.B; ++i) instance_tiles(b, i, {M_ADJ}, false, 0, tp, fused, adj[i]);
-        S.atiles = upload_binned(b, S, adj, S.antiles);
+        if (mask & EXA_EV_ADJ) {
+            for (int i : inst) instance_tiles(b, i, {M_ADJ}, false, 0, tp, fused, adj[i]);
+            Lc.atiles = upload_binned(b, S, adj, Lc.antiles);
+        }
     }
 }
 
@@ -326,6 +346,7 @@ ExaBatchJob seg_batch_job(const DevMap& m, int bufk, int64_t buf_off, int out, i
     J.longs = m.longs;
     J.lpart = m.lpart;
     J.lsum = m.lsum;
+    J.long_len = m.long_len;
     J.nseg = m.nseg;
     J.nlanes = m.nlanes;
     J.nparts = m.nparts;
@@ -398,7 +419,7 @@ void build_reductions(exa_batch& b, exa_batch::Sched& S, uint32_t mask) {
                 jobs.push_back(J);
                 const int64_t nb = batch_job_blocks(J);
                 for (int64_t k = 0; k < nb; ++k) per_bin[j].insert(per_bin[j].end(), {id, (int32_t)k});
-                if (J.kind == 0 && J.nparts > 0)
+                if (J.kind == 0 && J.nparts > 0 && J.nlong > 0)
                     for (int64_t l = 0; l < J.nlong; ++l) lbl.insert(lbl.end(), {id, (int32_t)l});
             }
         }
@@ -437,6 +458,7 @@ ExaMulti call_records(exa_batch& b, uint32_t mask, const exa_batch_io& io) {
             case M_GRAD:
                 c.direct = b.grad_direct_all ? 1 : 0;
                 c.out0 = b.grad_direct_all ? (lag ? io.lag : io.g) : b.buf[kBufFo];
+                c.out1 = lag ? io.lag : io.g;
                 break;
             case M_CONS: c.out0 = io.c; break;
             case M_JAC: c.out0 = io.jac; break;
@@ -457,7 +479,9 @@ ExaMulti call_records(exa_batch& b, uint32_t mask, const exa_batch_io& io) {
                 break;
             case M_JTPROD:
                 c.y = lag ? io.y : io.w;
+                c.sigma = io.obj_weight;
                 c.out0 = b.buf[kBufFo];
+                c.out1 = !lag ? io.jtw : b.grad_direct_all ? io.lag : b.lag_tmp;
                 break;
             case M_HPROD:
                 c.y = io.y;
@@ -481,52 +505,39 @@ ExaMulti call_records(exa_batch& b, uint32_t mask, const exa_batch_io& io) {
 // The evaluation launch(es) of a mask under its current schedule.
 void launch_eval(exa_batch& b, uint32_t mask, const ExaMulti& rec, hipStream_t s) {
     const exa_batch::Sched& S = b.sched.at(mask);
-    const Module& K = *b.module;
-    std::vector<int> tmp;
-    const std::vector<int>& modes = main_modes(S, mask, tmp);
-    auto launch_single = [&](int mode, ExaTile* tiles, int64_t n) {
-        if (n == 0) return;
-        ExaCall c = rec.c[mode];
-        c.tiles = tiles;
-        c.ntiles = n;
-        c.per_xcd = n / 8;
-        void* args[] = {&c};
-        hip_check(hipModuleLaunchKernel(K.fn[mode], (unsigned)n, 1, 1, (unsigned)S.block, 1, 1, 0, s, args, nullptr),
-                  "hipModuleLaunchKernel");
-    };
-    for (const auto& p : S.parts) launch_single(p.mode, p.tiles, p.ntiles);
-    if (S.ntiles > 0) {
-        if (single_kernel(modes)) {
-            ExaCall c = rec.c[modes[0]];
-            c.tiles = S.tiles;
-            c.ntiles = S.ntiles;
-            c.per_xcd = S.ntiles / 8;
-            void* args[] = {&c};
-            hip_check(hipModuleLaunchKernel(K.fn[modes[0]], (unsigned)S.ntiles, 1, 1, (unsigned)S.block, 1, 1, 0, s,
-                                            args, nullptr),
+    for (size_t c = 0; c < b.classes.size(); ++c) {
+        const exa_batch::Sched::Launch& Lc = S.launch[c];
+        const Module& K = *b.classes[c].module;
+        const Model& M = lead_of(b, (int)c);
+        auto launch_single = [&](int mode, ExaTile* tiles, int64_t n) {
+            if (n == 0) return;
+            ExaCall call = rec.c[mode];
+            call.tiles = tiles;
+            call.ntiles = n;
+            call.per_xcd = n / 8;
+            void* args[] = {&call};
+            hip_check(hipModuleLaunchKernel(K.fn[mode], (unsigned)n, 1, 1, (unsigned)S.block, 1, 1, 0, s, args, nullptr),
                       "hipModuleLaunchKernel");
-        } else {
-            ExaMulti mc = rec;
-            mc.tiles = S.tiles;
-            mc.ntiles = S.ntiles;
-            mc.per_xcd = S.ntiles / 8;
-            hipFunction_t fn = S.units == EXA_UNITS_ONE_PASS   ? K.fn_onepass
-                               : S.units == EXA_UNITS_JAC_HESS ? K.fn_multijh
-                                                               : K.fn_multi;
-            void* args[] = {&mc};
-            hip_check(hipModuleLaunchKernel(fn, (unsigned)S.ntiles, 1, 1, (unsigned)S.block, 1, 1, 0, s, args, nullptr),
-                      "hipModuleLaunchKernel");
+        };
+        for (const auto& p : Lc.parts) launch_single(p.mode, p.tiles, p.ntiles);
+        if (Lc.ntiles > 0) {
+            const std::vector<int> modes = modes_of(M, eval_mask(M, mask), Lc.units);
+            if (single_kernel(modes)) {
+                launch_single(modes[0], Lc.tiles, Lc.ntiles);
+            } else {
+                ExaMulti mc = rec;
+                mc.tiles = Lc.tiles;
+                mc.ntiles = Lc.ntiles;
+                mc.per_xcd = Lc.ntiles / 8;
+                hipFunction_t fn = Lc.units == EXA_UNITS_ONE_PASS   ? K.fn_onepass
+                                   : Lc.units == EXA_UNITS_JAC_HESS ? K.fn_multijh
+                                                                    : K.fn_multi;
+                void* args[] = {&mc};
+                hip_check(hipModuleLaunchKernel(fn, (unsigned)Lc.ntiles, 1, 1, (unsigned)S.block, 1, 1, 0, s, args, nullptr),
+                          "hipModuleLaunchKernel");
+            }
         }
-    }
-    if (S.antiles > 0) {
-        ExaCall c = rec.c[M_ADJ];
-        c.tiles = S.atiles;
-        c.ntiles = S.antiles;
-        c.per_xcd = S.antiles / 8;
-        void* args[] = {&c};
-        hip_check(hipModuleLaunchKernel(K.fn[M_ADJ], (unsigned)S.antiles, 1, 1, (unsigned)S.block, 1, 1, 0, s, args,
-                                        nullptr),
-                  "hipModuleLaunchKernel");
+        if (Lc.antiles > 0) launch_single(M_ADJ, Lc.atiles, Lc.antiles);
     }
 }
 
@@ -588,7 +599,7 @@ void run(exa_batch& b, uint32_t mask, const exa_batch_io& io, hipStream_t s) {
 // First call with a mask under autotune: time every candidate schedule's
 // evaluation launch(es) on the caller's arguments and keep the fastest.
 void tune_batch(exa_batch& b, uint32_t mask, const exa_batch_io& io, hipStream_t s) {
-    const uint32_t em = eval_mask(mask);
+    const uint32_t em = eval_mask(b.models[0]->impl, mask);
     const int blocks[] = {64, 128, 256};
     const int epls[] = {1, 2, 4, 8};
     std::vector<int> fuses = {0};
@@ -600,7 +611,7 @@ void tune_batch(exa_batch& b, uint32_t mask, const exa_batch_io& io, hipStream_t
     std::vector<int> combos = {EXA_UNITS_PER_CALLBACK};
     if (em && has_jh(em)) combos.push_back(EXA_UNITS_JAC_HESS);
     if (em && combined_mode_of(em) >= 0) combos.push_back(EXA_UNITS_ONE_PASS);
-    if (em && eval_modes(em, false).size() > 1) combos.push_back(EXA_UNITS_SEPARATE);
+    if (em && batch_units(em, EXA_UNITS_SEPARATE) == EXA_UNITS_SEPARATE) combos.push_back(EXA_UNITS_SEPARATE);
     hipEvent_t e0, e1;
     hip_check(hipEventCreate(&e0), "hipEventCreate");
     hip_check(hipEventCreate(&e1), "hipEventCreate");
@@ -732,29 +743,46 @@ exa_status exa_batch_create(exa_model* const* models, int32_t B, const exa_batch
         if (b->epl < 1 || b->epl > 16) fail(EXA_EINVAL, "epl must be in 1..16");
         if ((b->units & ~EXA_UNSTAGED) < EXA_UNITS_PER_CALLBACK || (b->units & ~EXA_UNSTAGED) > EXA_UNITS_SEPARATE)
             fail(EXA_EINVAL, "units must be one of the EXA_UNITS_* values");
-        // every instance runs the same generated code
-        const Model& M0 = models[0]->impl;
-        std::vector<std::vector<char>> ident;
-        for (const Pattern& P : M0.pats) ident.push_back(P.ident);
-        for (int i = 1; i < B; ++i)
-            for (size_t p = 0; p < ident.size(); ++p)
-                for (size_t c = 0; c < ident[p].size(); ++c) ident[p][c] &= models[i]->impl.pats[p].ident[c];
-        // H v references stored into the output: code for any instance that
-        // may (the others take the buffer path by their own bits)
-        std::vector<std::vector<char>> hvd;
-        for (const Group& G : M0.groups) hvd.push_back(G.hv_direct);
-        for (int i = 1; i < B; ++i)
-            for (size_t g = 0; g < hvd.size(); ++g)
-                for (size_t r = 0; r < hvd[g].size(); ++r) hvd[g][r] |= models[i]->impl.groups[g].hv_direct[r];
-        bool same = true;
-        for (size_t p = 0; p < ident.size(); ++p) same = same && ident[p] == M0.pats[p].ident;
-        for (size_t g = 0; g < hvd.size(); ++g) same = same && hvd[g] == M0.groups[g].hv_direct;
-        if (same) {
-            b->module = M0.dev->module;
-        } else {
-            bool hit = false;
-            b->module = compile_module(generate_source(M0, &b->live, &ident, &hvd), M0.cache_dir, &hit);
-            b->own_code = true;
+        // instances whose sums are finished by the same units share code
+        b->cls.assign(B, 0);
+        for (int i = 0; i < B; ++i) {
+            size_t c = 0;
+            while (c < b->classes.size() &&
+                   models[b->classes[c].inst[0]]->impl.own_sig != models[i]->impl.own_sig)
+                ++c;
+            if (c == b->classes.size()) b->classes.emplace_back();
+            b->classes[c].inst.push_back(i);
+            b->cls[i] = (int)c;
+        }
+        std::vector<std::vector<std::vector<char>>> class_ident;
+        for (exa_batch::Class& C : b->classes) {
+            const Model& M0 = models[C.inst[0]]->impl;
+            std::vector<std::vector<char>> ident;
+            for (const Pattern& P : M0.pats) ident.push_back(P.ident);
+            // H v references stored into the output: code for any instance that
+            // may (the others take the buffer path by their own bits)
+            std::vector<std::vector<char>> hvd;
+            for (const Group& G : M0.groups) hvd.push_back(G.hv_direct);
+            bool same = true;
+            for (int i : C.inst) {
+                const Model& M = models[i]->impl;
+                for (size_t p = 0; p < ident.size(); ++p) {
+                    same = same && M.pats[p].ident == M0.pats[p].ident;
+                    for (size_t c = 0; c < ident[p].size(); ++c) ident[p][c] &= M.pats[p].ident[c];
+                }
+                for (size_t g = 0; g < hvd.size(); ++g) {
+                    same = same && M.groups[g].hv_direct == M0.groups[g].hv_direct;
+                    for (size_t r = 0; r < hvd[g].size(); ++r) hvd[g][r] |= M.groups[g].hv_direct[r];
+                }
+            }
+            if (same) {
+                C.module = M0.dev->module;
+            } else {
+                bool hit = false;
+                C.module = compile_module(generate_source(M0, &C.live, &ident, &hvd), M0.cache_dir, &hit);
+                C.own_code = true;
+            }
+            class_ident.push_back(ident);
         }
 
         // offsets in the concatenated arrays and bases in the work buffers
@@ -806,6 +834,17 @@ exa_status exa_batch_create(exa_model* const* models, int32_t B, const exa_batch
             inst[i].off[EXA_OFF_PAR] = b->base[kBufPar][i];
             inst[i].off[EXA_OFF_TILE] = b->base[kBufTile][i];
             inst[i].theta = b->theta + b->offsets[kNoff * i + kOffTheta];
+            // columns this instance counts from the data point but the class's
+            // code loads: their first value leaves the offsets again
+            const std::vector<std::vector<char>>& ident = class_ident[b->cls[i]];
+            for (size_t p = 0; p < M.pats.size(); ++p) {
+                const Pattern& P = M.pats[p];
+                auto extra = [&](int c) { return c >= 0 && P.ident[c] && !ident[p][c] ? (int64_t)P.icols[c][0] : 0; };
+                ExaPatDev& d = inst[i].pat[p];
+                for (int r = 0; r < P.o1step(); ++r) d.roff[r] -= extra(P.vslots[r].col);
+                for (int r = 0; r < P.pstep(); ++r) d.roff[P.o1step() + r] -= extra(P.pslots[r].col);
+                if (P.kind == EXA_AUG) d.row_off -= extra(P.row_icol);
+            }
         }
         b->inst = (ExaInstDev*)b->mem.upload(inst.data(), inst.size() * sizeof(ExaInstDev));
         // the models' maps, each with part sums of the batch's own
@@ -818,7 +857,7 @@ exa_status exa_batch_create(exa_model* const* models, int32_t B, const exa_batch
             mp.h = D.h_map;
             mp.par = D.par_map;
             for (DevMap* m : {&mp.grad, &mp.jt, &mp.h, &mp.par})
-                if (m->nparts > 0) m->lsum = (double*)b->mem.alloc(m->nparts * sizeof(double));
+                if (m->nparts > 0 && m->nlong > 0) m->lsum = (double*)b->mem.alloc(m->nparts * sizeof(double));
         }
         hip_check(hipStreamCreate(&b->cap), "hipStreamCreate");
         *out = b.release();
@@ -858,8 +897,11 @@ exa_status exa_batch_schedule(const exa_batch* b, uint32_t mask, int64_t* out6) 
         out6[1] = S.epl;
         out6[2] = S.fused ? 1 : 0;
         out6[3] = S.units | (S.unstaged ? EXA_UNSTAGED : 0);
-        int64_t nt = S.ntiles + S.antiles;
-        for (const auto& p : S.parts) nt += p.ntiles;
+        int64_t nt = 0;
+        for (const auto& Lc : S.launch) {
+            nt += Lc.ntiles + Lc.antiles;
+            for (const auto& p : Lc.parts) nt += p.ntiles;
+        }
         out6[4] = nt;
         out6[5] = S.tuned_ns;
     });
@@ -895,18 +937,18 @@ exa_status exa_batch_bytes(const exa_batch* b, uint32_t mask, int64_t* out4) {
             units = it->second.units;
             fused = it->second.fused;
         }
-        const uint32_t em = eval_mask(mask);
         int64_t er = 0, ew = 0, rr = 0, rw = 0;
         for (int i = 0; i < b->B; ++i) {
             const Model& M = b->models[i]->impl;
+            const uint32_t em = eval_mask(M, mask);
             int64_t r = 0, w = 0;
             if (em) {
-                kernel_bytes(M, modes_of(em, batch_units(em, units)), fused, r, w, b->own_code ? &b->live : nullptr);
+                kernel_bytes(M, modes_of(M, em, batch_units(em, units)), fused, r, w, live_of(*b, i));
                 er += r;
                 ew += w;
             }
             if (mask & EXA_EV_ADJ) {
-                kernel_bytes(M, {M_ADJ}, fused, r, w, b->own_code ? &b->live : nullptr);
+                kernel_bytes(M, {M_ADJ}, fused, r, w, live_of(*b, i));
                 er += r;
                 ew += w;
             }

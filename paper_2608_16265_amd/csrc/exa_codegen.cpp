@@ -220,8 +220,10 @@ class PatternCg {
     }
 
     // Records the statements of this pattern; outputs go to `out`[s] (array
-    // modes) or to `out` itself (scalar modes).
-    void body(const std::string& out) {
+    // modes) or to `out` itself (scalar modes).  With `only`, just the output
+    // slots flagged in it.
+    void body(const std::string& out, const std::vector<char>* only = nullptr) {
+        auto want = [&](int s) { return !only || (*only)[s]; };
         const bool second = mode_ == M_HESS || mode_ == M_HPROD || mode_ == M_ADJ;
         const bool first = mode_ != M_OBJ && mode_ != M_CONS;
         forward(first, second);
@@ -242,7 +244,7 @@ class PatternCg {
                 std::vector<std::string> J(P_.o1step(), Z), Pacc, adj;
                 reverse(ONE, adj, J, Pacc, false);
                 for (int s = 0; s < P_.o1step(); ++s)
-                    e_.out(slot(s), mode_ == M_JTPROD ? e_.mul(J[s], nm_.wgt) : J[s]);
+                    if (want(s)) e_.out(slot(s), mode_ == M_JTPROD ? e_.mul(J[s], nm_.wgt) : J[s]);
                 break;
             }
             case M_JPROD: {
@@ -261,7 +263,8 @@ class PatternCg {
                 tangent(SEED_VEC, -1, tg);
                 std::vector<std::string> Hc(P_.o1step(), Z), Pt;
                 reverse_tangent(adj, tg, Hc, Pt, false);
-                for (size_t i = 0; i < P_.hvs.size(); ++i) e_.out(slot((int)i), Hc[P_.hvs[i]]);
+                for (size_t i = 0; i < P_.hvs.size(); ++i)
+                    if (want((int)i)) e_.out(slot((int)i), Hc[P_.hvs[i]]);
                 break;
             }
             case M_ADJ: {
@@ -616,7 +619,7 @@ bool scalar_mode(int mode) { return mode == M_OBJ || mode == M_CONS || mode == M
 
 const char* mode_name(int m) {
     static const char* n[] = {"obj", "cons", "grad", "jac", "hess", "jprod", "jtprod", "hprod", "adj", "jh",
-                              "sfull", "sipm"};
+                              "sfull", "sipm", "lag"};
     return n[m];
 }
 
@@ -667,7 +670,7 @@ std::vector<Job> jobs_of(const Model& M, int mode, const Unit& U) {
             j.push_back({p, mode, "C.out0"});
             continue;
         }
-        for (int m : job_modes(mode))
+        for (int m : job_modes(M, mode))
             if (pattern_in_mode(M.pats[p], m))
                 j.push_back({p, m, mode == M_JH ? (m == M_JAC ? "C.out0" : "C.out1") : call_of(mode, m) + ".out0"});
     }
@@ -746,6 +749,96 @@ std::string aug_fn(const Model& M, int mode, int a, int& ntmp, UnitLive& live) {
     return os.str();
 }
 
+// The inputs of a data set's patterns as named statements: index columns,
+// float columns, references and parameters.  `cv`: the index column whose
+// value the caller passes (a pulled contribution through an inverse table).
+struct Loads {
+    std::set<int> icols, fcols, vrefs, prefs;
+};
+Loads record_loads(const Model& M, const Group& G, const std::vector<int>& members, bool weighs, bool seeds, Em& e,
+                   int cv = -1) {
+    Loads L;
+    for (int p : members) {
+        const Pattern& P = M.pats[p];
+        for (auto& r : P.vslots) if (r.col >= 0) L.icols.insert(r.col);
+        for (auto& r : P.pslots) if (r.col >= 0) L.icols.insert(r.col);
+        for (auto& q : P.nodes) if (q.op == EXA_OP_DATA) L.fcols.insert(q.col);
+        if (weighs && P.kind == EXA_AUG) L.icols.insert(P.row_icol);
+    }
+    const int p0 = members[0];  // the unit's data arrays
+    for (int c : L.icols)
+        e.named("long long", "ic" + std::to_string(c),
+                c == cv ? "cv" : ident(M, p0, c) ? "k" : "P0.ic[" + std::to_string(c) + "][k]");
+    for (int c : L.fcols) e.named("double", "fc" + std::to_string(c), "P0.fc[" + std::to_string(c) + "][k]");
+    for (int p : members) {
+        for (int r : M.pats[p].vg) L.vrefs.insert(r);
+        for (int r : M.pats[p].pg) L.prefs.insert(r);
+    }
+    for (int r : L.vrefs) {
+        const RefKey& k = G.vrefs[r];
+        const std::pair<int, int> src = G.vsrc[r];
+        const std::string off = "I.pat[" + std::to_string(G.members[src.first]) + "].roff[" +
+                                std::to_string(src.second) + "]";
+        const std::string idx = k.col < 0 ? off : "ic" + std::to_string(k.col) + " + " + off;
+        e.named("long long", "ix" + std::to_string(r), idx);
+        e.named("double", "x" + std::to_string(r), "X[ix" + std::to_string(r) + "]");
+        if (seeds) e.named("double", "v" + std::to_string(r), "V[ix" + std::to_string(r) + "]");
+    }
+    for (int r : L.prefs) {
+        const RefKey& k = G.prefs[r];
+        const std::pair<int, int> src = G.psrc[r];
+        const int member = G.members[src.first];
+        // a parameter slot's offset sits after the member's variable slots
+        const std::string off = "I.pat[" + std::to_string(member) + "].roff[" +
+                                std::to_string(M.pats[member].o1step() + src.second) + "]";
+        const std::string idx = k.col < 0 ? off : "ic" + std::to_string(k.col) + " + " + off;
+        e.named("double", "p" + std::to_string(r), "TH[" + idx + "]");
+    }
+    return L;
+}
+
+// Names of pattern P's inputs among record_loads' statements.
+Names input_names(const Pattern& P) {
+    Names nm;
+    for (int s = 0; s < P.o1step(); ++s) {
+        nm.x.push_back("x" + std::to_string(P.vg[s]));
+        nm.v.push_back("v" + std::to_string(P.vg[s]));
+        nm.ix.push_back("ix" + std::to_string(P.vg[s]));
+    }
+    for (int s = 0; s < P.pstep(); ++s) nm.p.push_back("p" + std::to_string(P.pg[s]));
+    return nm;
+}
+
+// Row weight of pattern p's job: w for J^T w, y (sigma for objectives) otherwise.
+std::string record_weight(Em& e, const Pattern& P, int p, bool byw, const std::string& sigma) {
+    const std::string src = byw ? "W" : "Y", pd = "P" + std::to_string(p) + "_";
+    std::string w;
+    if (P.kind == EXA_OBJ)
+        w = sigma;
+    else if (P.kind == EXA_CON)
+        w = src + "[" + pd + ".o0 + k]";
+    else
+        w = src + "[" + pd + ".tgt0 + ic" + std::to_string(P.row_icol) + " + " + pd + ".row_off]";
+    return e.named_once("double", (byw ? "ww" : "wy") + std::to_string(p), w);
+}
+
+void record_live(const Model& M, const std::vector<int>& members, const Loads& L, const std::set<std::string>& names,
+                 UnitLive& live, int cv = -1) {
+    for (int c : L.icols)
+        if (names.count("ic" + std::to_string(c)) && c != cv && !ident(M, members[0], c)) live.icols.push_back(c);
+    for (int c : L.fcols) if (names.count("fc" + std::to_string(c))) live.fcols.push_back(c);
+    for (int r : L.vrefs) {
+        if (names.count("x" + std::to_string(r))) live.vrefs.push_back(r);
+        if (names.count("v" + std::to_string(r))) live.vseeds.push_back(r);
+    }
+    for (int r : L.prefs) if (names.count("p" + std::to_string(r))) live.prefs.push_back(r);
+    for (int p : members)
+        // an objective's weight is the scalar sigma, not a per-point load
+        if (M.pats[p].kind != EXA_OBJ)
+            for (const char* w : {"wy", "ww"})
+                if (names.count(w + std::to_string(p))) live.weights++;
+}
+
 // Generates the tile function of one unit; fills `live`.  A plain unit runs
 // one callback's job per member (two for JH); a multi unit (M_SFULL,
 // M_SIPM) runs every job of its modes per member from one set of loads and
@@ -754,8 +847,7 @@ std::string unit_tile(const Model& M, int mode, const Unit& U, int& ntmp, UnitLi
     const Group& G = M.groups[U.group];
     const int m0 = G.members[0];  // owner of the shared column pointers
     const bool multi = multi_unit(mode);
-    const std::vector<int>& jm = job_modes(mode);
-    auto has = [&](int m) { return std::find(jm.begin(), jm.end(), m) != jm.end(); };
+    const std::vector<int>& jm = job_modes(M, mode);
     auto call = [&](int m) { return call_of(mode, m); };
     std::ostringstream os;
     const std::string fn = std::string("unit_") + mode_name(mode) + "_" + std::to_string(U.code);
@@ -838,67 +930,13 @@ std::string unit_tile(const Model& M, int mode, const Unit& U, int& ntmp, UnitLi
         seeds |= m == M_JPROD || m == M_HPROD || m == M_ADJ;
     }
     Em e(ntmp);
-    std::set<int> icols, fcols;
-    for (int p : U.members) {
-        const Pattern& P = M.pats[p];
-        for (auto& r : P.vslots) if (r.col >= 0) icols.insert(r.col);
-        for (auto& r : P.pslots) if (r.col >= 0) icols.insert(r.col);
-        for (auto& q : P.nodes) if (q.op == EXA_OP_DATA) fcols.insert(q.col);
-        if (weighs && P.kind == EXA_AUG) icols.insert(P.row_icol);
-    }
-    const int p0 = U.members[0];  // the unit's data arrays
-    for (int c : icols)
-        e.named("long long", "ic" + std::to_string(c), ident(M, p0, c) ? "k" : "P0.ic[" + std::to_string(c) + "][k]");
-    for (int c : fcols) e.named("double", "fc" + std::to_string(c), "P0.fc[" + std::to_string(c) + "][k]");
-    std::set<int> vrefs, prefs;
-    for (int p : U.members) {
-        for (int r : M.pats[p].vg) vrefs.insert(r);
-        for (int r : M.pats[p].pg) prefs.insert(r);
-    }
-    for (int r : vrefs) {
-        const RefKey& k = G.vrefs[r];
-        const std::pair<int, int> src = G.vsrc[r];
-        const std::string off = "I.pat[" + std::to_string(G.members[src.first]) + "].roff[" +
-                                std::to_string(src.second) + "]";
-        const std::string idx = k.col < 0 ? off : "ic" + std::to_string(k.col) + " + " + off;
-        e.named("long long", "ix" + std::to_string(r), idx);
-        e.named("double", "x" + std::to_string(r), "X[ix" + std::to_string(r) + "]");
-        if (seeds) e.named("double", "v" + std::to_string(r), "V[ix" + std::to_string(r) + "]");
-    }
-    for (int r : prefs) {
-        const RefKey& k = G.prefs[r];
-        const std::pair<int, int> src = G.psrc[r];
-        const int member = G.members[src.first];
-        // a parameter slot's offset sits after the member's variable slots
-        const std::string off = "I.pat[" + std::to_string(member) + "].roff[" +
-                                std::to_string(M.pats[member].o1step() + src.second) + "]";
-        const std::string idx = k.col < 0 ? off : "ic" + std::to_string(k.col) + " + " + off;
-        e.named("double", "p" + std::to_string(r), "TH[" + idx + "]");
-    }
+    const Loads L = record_loads(M, G, U.members, weighs, seeds, e);
     for (const Job& j : jobs) {
         const int p = j.p;
         const Pattern& P = M.pats[p];
         const std::string pd = "P" + std::to_string(p) + "_";
-        Names nm;
-        for (int s = 0; s < P.o1step(); ++s) {
-            nm.x.push_back("x" + std::to_string(P.vg[s]));
-            nm.v.push_back("v" + std::to_string(P.vg[s]));
-            nm.ix.push_back("ix" + std::to_string(P.vg[s]));
-        }
-        for (int s = 0; s < P.pstep(); ++s) nm.p.push_back("p" + std::to_string(P.pg[s]));
-        if (needs_weight(j.mode)) {
-            // row weight: w for J^T w, y (sigma for objectives) otherwise
-            const bool byw = j.mode == M_JTPROD;
-            const std::string src = byw ? "W" : "Y";
-            std::string w;
-            if (P.kind == EXA_OBJ)
-                w = cy + ".sigma";
-            else if (P.kind == EXA_CON)
-                w = src + "[" + pd + ".o0 + k]";
-            else
-                w = src + "[" + pd + ".tgt0 + ic" + std::to_string(P.row_icol) + " + " + pd + ".row_off]";
-            nm.wgt = e.named_once("double", (byw ? "ww" : "wy") + std::to_string(p), w);
-        }
+        Names nm = input_names(P);
+        if (needs_weight(j.mode)) nm.wgt = record_weight(e, P, p, j.mode == M_JTPROD, cy + ".sigma");
         PatternCg cg(P, j.mode, e, nm);
         cg.body(oname(j));
         if (j.mode == M_GRAD)
@@ -1040,18 +1078,7 @@ std::string unit_tile(const Model& M, int mode, const Unit& U, int& ntmp, UnitLi
     os << "        }\n";
 
     // ---- liveness record
-    for (int c : icols) if (names.count("ic" + std::to_string(c)) && !ident(M, p0, c)) live.icols.push_back(c);
-    for (int c : fcols) if (names.count("fc" + std::to_string(c))) live.fcols.push_back(c);
-    for (int r : vrefs) {
-        if (names.count("x" + std::to_string(r))) live.vrefs.push_back(r);
-        if (names.count("v" + std::to_string(r))) live.vseeds.push_back(r);
-    }
-    for (int r : prefs) if (names.count("p" + std::to_string(r))) live.prefs.push_back(r);
-    for (int p : U.members)
-        // an objective's weight is the scalar sigma, not a per-point load
-        if (M.pats[p].kind != EXA_OBJ)
-            for (const char* w : {"wy", "ww"})
-                if (names.count(w + std::to_string(p))) live.weights++;
+    record_live(M, U.members, L, names, live);
     for (const Job& j : jobs)
         if (j.mode != M_JTPROD && j.mode != M_HPROD) live.outputs += out_step(M.pats[j.p], j.mode);
     for (auto& kv : gout) live.outputs += (int64_t)grefs(kv.first).size();
@@ -1076,6 +1103,365 @@ std::string unit_tile(const Model& M, int mode, const Unit& U, int& ntmp, UnitLi
     return os.str();
 }
 
+// ---- units that finish sums themselves (OwnPlan) ----------------------------
+
+SumKind sum_of(int mode) { return mode == M_HPROD ? SUM_HV : mode == M_GRAD ? SUM_GRAD : SUM_JT; }
+
+bool adds_to(const Pattern& P, int mode) {
+    return P.ndata > 0 && (mode == M_HPROD  ? !P.hvs.empty()
+                           : mode == M_GRAD ? P.kind == EXA_OBJ && P.o1step() > 0
+                                            : P.kind != EXA_OBJ && P.o1step() > 0 && !P.wread);
+}
+
+// Output slots of pattern P's job for `mode` that go to group references in `refs`.
+std::vector<char> slots_to(const Pattern& P, int mode, const std::set<int>& refs) {
+    std::vector<char> f(out_step(P, mode), 0);
+    for (size_t i = 0; i < f.size(); ++i) f[i] = refs.count(P.vg[mode == M_HPROD ? P.hvs[i] : i]) ? 1 : 0;
+    return f;
+}
+
+std::string own_prologue(const Model& M, const std::vector<int>& members, int m0) {
+    std::ostringstream os;
+    os << "    const ExaPatDev& P0 = I.pat[" << m0 << "];\n";
+    for (int p : members) os << "    const ExaPatDev& P" << p << "_ = I.pat[" << p << "];\n";
+    os << "    const double* __restrict__ X = C.x + I.off[" << EXA_OFF_X << "];\n";
+    os << "    const double* __restrict__ V = C.v + I.off[" << EXA_OFF_X << "];\n";
+    os << "    const double* __restrict__ Y = C.y + I.off[" << EXA_OFF_Y << "];\n";
+    os << "    const double* __restrict__ W = C.y + I.off[" << EXA_OFF_Y << "];\n";
+    os << "    const double* __restrict__ TH = I.theta;\n";
+    os << "    (void)X; (void)V; (void)Y; (void)W; (void)TH; (void)P0;\n";
+    return os.str();
+}
+
+std::string pull_name(const OwnSrc& s, int mode) {
+    return std::string("pull_") + mode_name(s.pat >= 0 ? M_GRAD : mode) + "_" + std::to_string(s.group) + "_" +
+           std::to_string(s.ref) + (s.pat >= 0 ? "_" + std::to_string(s.pat) : "");
+}
+
+// The contribution of one (data set, reference) at one of its points, for the
+// unit that pulls it: the group's members' sum in declaration order, as the
+// data set's own unit adds it; +-w[row] for a weight entry; the pattern's
+// entry for an objective gradient.
+std::string pull_fn(const Model& M, int mode, const OwnSrc& s, int& ntmp, UnitLive& live) {
+    const Group& G = M.groups[s.group];
+    const int jm = s.pat >= 0 ? M_GRAD : mode;
+    std::ostringstream os;
+    os << "__device__ __forceinline__ double " << pull_name(s, mode)
+       << "(const ExaCall& C, const ExaInstDev& I, long long k, long long cv) {\n    (void)cv;\n";
+    std::vector<int> members;
+    if (s.wread >= 0)
+        members = {s.wread};
+    else if (s.pat >= 0)
+        members = {s.pat};
+    else
+        for (int p : G.members)
+            if (adds_to(M.pats[p], mode) &&
+                std::find(M.pats[p].vg.begin(), M.pats[p].vg.end(), s.ref) != M.pats[p].vg.end())
+                members.push_back(p);
+    os << own_prologue(M, members, G.members[0]);
+    const int cv = s.how == OWN_INVERSE ? G.vrefs[s.ref].col : -1;
+    if (s.wread >= 0) {
+        const Pattern& P = M.pats[s.wread];
+        const std::string pd = "P" + std::to_string(s.wread) + "_";
+        const int c = P.row_icol;
+        const bool loaded = c != cv && !ident(M, s.wread, c);
+        os << "    const double t = W[" << pd << ".tgt0 + "
+           << (c == cv ? std::string("cv") : loaded ? pd + ".ic[" + std::to_string(c) + "][k]" : std::string("k"))
+           << " + " << pd << ".row_off];\n    return " << (P.wread < 0 ? "-t" : "t") << ";\n}\n";
+        live.extra += 8 + (loaded ? 4 : 0);
+        return os.str();
+    }
+    Em e(ntmp);
+    const bool weighs = jm != M_GRAD;
+    const Loads L = record_loads(M, G, members, weighs, jm == M_HPROD, e, cv);
+    os << "    double r = 0.0;\n";
+    for (int p : members) os << "    double o" << p << "[" << std::max(1, out_step(M.pats[p], jm)) << "] = {};\n";
+    for (int p : members) {
+        const Pattern& P = M.pats[p];
+        Names nm = input_names(P);
+        if (weighs) nm.wgt = record_weight(e, P, p, jm == M_JTPROD, "C.sigma");
+        const std::vector<char> want = slots_to(P, jm, {s.ref});
+        PatternCg cg(P, jm, e, nm);
+        cg.body("o" + std::to_string(p), &want);
+        for (size_t i = 0; i < want.size(); ++i)
+            if (want[i])
+                e.out("r", (jm == M_GRAD ? std::string() : "r + ") + "o" + std::to_string(p) + "[" + std::to_string(i) + "]");
+    }
+    const std::set<std::string> names = e.emit(os, "    ");
+    os << "    return r;\n}\n";
+    UnitLive own;
+    record_live(M, members, L, names, own, cv);
+    live.extra += 4 * (int64_t)own.icols.size() + 8 * (int64_t)own.fcols.size() + 8 * own.weights;
+    // entries of x and v count once per pulled contribution (their reuse
+    // between neighbouring variables stays in the caches)
+    return os.str();
+}
+
+// Statements of the pulled contributions of variable `v`, named <pre><i> with
+// condition <pre><i>ok (evaluated before any is added, so that their chains of
+// loads overlap).
+void emit_pulls(const Model& M, int mode, const std::vector<OwnSrc>& srcs, const std::string& v, const std::string& pre,
+                const std::string& ind, std::ostringstream& os) {
+    for (size_t i = 0; i < srcs.size(); ++i) {
+        const OwnSrc& s = srcs[i];
+        const Group& G = M.groups[s.group];
+        const std::string u = pre + std::to_string(i), pd = "I.pat[" + std::to_string(G.members[0]) + "]",
+                          vd = pd + ".vd[" + std::to_string(s.ref) + "]", fn = pull_name(s, mode) + "(C, I, ";
+        const int col = G.vrefs[s.ref].col;
+        if (s.how == OWN_INVERSE) {
+            const std::string c = std::to_string(col);
+            os << ind << "const long long " << u << "c = " << v << " - " << vd << ";\n";
+            os << ind << "const bool " << u << "in = " << u << "c >= " << pd << ".icmin[" << c << "] && " << u << "c <= "
+               << pd << ".icmax[" << c << "];\n";
+            os << ind << "const int " << u << "k = " << pd << ".inv[" << c << "][" << u << "in ? " << u << "c - " << pd
+               << ".icmin[" << c << "] : 0];\n";
+            os << ind << "const bool " << u << "ok = " << u << "in && " << u << "k >= 0;\n";
+            if (s.sparse)
+                os << ind << "double " << u << " = 0.0;\n" << ind << "if (" << u << "ok) " << u << " = " << fn << u << "k, "
+                   << u << "c);\n";
+            else
+                os << ind << "const double " << u << " = " << fn << u << "ok ? " << u << "k : 0, " << u << "ok ? " << u
+                   << "c : (long long)" << pd << ".icmin[" << c << "]);\n";
+        } else {
+            os << ind << "const long long " << u << "k = " << v << " - " << vd << ";\n";
+            os << ind << "const bool " << u << "ok = " << u << "k >= 0 && " << u << "k < " << pd << ".ndata;\n";
+            if (s.sparse || col < 0) {  // few lanes take it
+                os << ind << "double " << u << " = 0.0;\n";
+                os << ind << "if (" << u << "ok) " << u << " = " << fn << u << "k, 0);\n";
+            } else {
+                os << ind << "const double " << u << " = " << fn << u << "ok ? " << u << "k : 0, 0);\n";
+            }
+        }
+    }
+}
+
+// acc += the pulled contributions, in order.
+void emit_adds(size_t n, const std::string& acc, const std::string& pre, const std::string& ind, std::ostringstream& os) {
+    for (size_t i = 0; i < n; ++i)
+        os << ind << "if (" << pre << i << "ok) " << acc << " += " << pre << i << ";\n";
+}
+
+// The value stored for a variable: the sum, or sigma * gradient + sum (the
+// product rounded first) in the Lagrangian gradient's units.
+void emit_result(int mode, size_t ngrad, const std::string& acc, const std::string& pre, const std::string& ind,
+                 const std::string& lhs, const std::string& cond, std::ostringstream& os) {
+    std::string val = acc;
+    if (mode == M_LAG) {
+        os << ind << "double " << pre << "q = 0.0;\n";
+        for (size_t i = 0; i < ngrad; ++i) os << ind << "if (" << pre << i << "ok) " << pre << "q = " << pre << i << ";\n";
+        os << ind << "const double " << pre << "p = C.sigma * " << pre << "q;\n";
+        val = pre + "p + " + acc;
+    }
+    os << ind << (cond.empty() ? "" : "if (" + cond + ") ") << lhs << " = " << val << ";\n";
+}
+
+// A unit over variables: lane i of the range owns variable vlo + i and pulls
+// every contribution.
+std::string own_vunit(const Model& M, int mode, const OwnUnit& U, int sum, UnitLive& live) {
+    std::ostringstream os;
+    const int jm = mode == M_LAG ? M_JTPROD : mode;
+    os << "__device__ __forceinline__ void own_" << mode_name(mode) << "_" << U.code
+       << "(const ExaCall& C, const ExaInstDev& I, const ExaTile& T, double*) {\n";
+    os << "    double* __restrict__ OUT = C.out1 + I.off[" << EXA_OFF_X << "];\n";
+    os << "    for (long long i = T.start + threadIdx.x; i < T.start + T.count; i += blockDim.x) {\n";
+    os << "        const long long v = I.vlo[" << sum << "][" << U.vunit << "] + i;\n";
+    emit_pulls(M, jm, U.srcs, "v", "u", "        ", os);
+    if (mode == M_LAG) emit_pulls(M, jm, U.grad, "v", "g", "        ", os);
+    os << "        double a = 0.0;\n";
+    emit_adds(U.srcs.size(), "a", "u", "        ", os);
+    emit_result(mode, U.grad.size(), "a", "g", "        ", "OUT[v]", "", os);
+    os << "    }\n}\n";
+    live.outputs += 1;
+    for (const OwnSrc& s : U.srcs) live.extra += s.how == OWN_INVERSE ? 4 : 0;
+    return os.str();
+}
+
+// A host unit: one data set's members in the lane of a point, in chunks of 64
+// lanes whose first W = 64 - S own a point each (the last S repeat the next
+// chunk's first points), a wave per run of chunks.  Contributions of
+// references a chain owns are shifted down the wave and added in ascending
+// point order; shared references are added up over the run and by the wave;
+// the others go to the work buffer or straight to the output.
+std::string own_hunit(const Model& M, int mode, const OwnUnit& U, int sum, int& ntmp, UnitLive& live) {
+    const Group& G = M.groups[U.group];
+    const int m0 = G.members[0], jm = mode == M_LAG ? M_JTPROD : mode;
+    std::vector<int> members;
+    for (int p : G.members)
+        if (adds_to(M.pats[p], jm)) members.push_back(p);
+    std::ostringstream os;
+    os << "__device__ __forceinline__ void own_" << mode_name(mode) << "_" << U.code
+       << "(const ExaCall& C, const ExaInstDev& I, const ExaTile& T, double*) {\n";
+    os << own_prologue(M, members, m0);
+    os << "    double* __restrict__ OUT = C.out1 + I.off[" << EXA_OFF_X << "];\n    (void)OUT;\n";
+    const std::string W = std::to_string(64 - U.S), S = std::to_string(U.S);
+    // (in both loops, table fields are read again in every round: held over
+    // the loop they take 40 to 50 registers on the branch units, which cost
+    // more waves than the scalar cache's answers cost time)
+    if (U.plain()) {
+        // no lane needs another's values: points straight over the workgroup.
+        // Lanes past the end repeat the last point and store its values once
+        // more, without a branch: a branch per store would end the block over
+        // which the compiler can move later loads ahead
+        os << "    const long long n = P0.ndata, kend = T.start + T.count;\n    (void)n;\n    {\n";
+        os << "        for (long long kb = T.start; kb < kend; kb += (int)blockDim.x) {\n";
+        os << "            const long long kr = kb + threadIdx.x;\n";
+        os << "            const long long k = kr < kend ? kr : kend - 1;\n";
+        os << "            asm volatile(\"\" ::: \"memory\");\n";
+    } else {
+    os << "    const int lane = (int)(threadIdx.x & 63), nwav = (int)(blockDim.x >> 6);\n";
+    os << "    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));\n";
+    os << "    const long long n = P0.ndata;\n";
+    os << "    const int R = P0.runl[" << sum << "];\n";
+    os << "    for (long long run = T.start + wave; run < T.start + T.count; run += nwav) {\n";
+    for (auto& x : U.shared) os << "        double s" << x.first << " = 0.0;\n";
+    os << "        for (int ch = 0; ch < R; ++ch) {\n";
+    os << "            const long long k0 = (run * R + ch) * " << W << " - " << S << ";\n";
+    os << "            if (k0 >= n) break;\n";
+    os << "            const long long kr = k0 + lane;\n";
+    os << "            const long long k = kr < 0 ? 0 : kr < n ? kr : n - 1;\n";
+    os << "            asm volatile(\"\" ::: \"memory\");\n";
+    os << "            const bool pt = " << (U.S ? "lane < " + W + " && kr >= 0 && " : std::string()) << "kr < n;\n";
+    }
+    // references this unit needs, and where they go
+    std::set<int> need;
+    for (const OwnChain& c : U.chains)
+        for (auto& r : c.refs) need.insert(r.second);
+    for (int r : U.bufrefs) need.insert(r);
+    for (auto& x : U.shared) need.insert(x.first);
+    for (int r : U.direct) need.insert(r);
+    for (int r : need) os << "            double g" << r << " = 0.0;\n";
+    for (int p : members) os << "            double o" << p << "[" << std::max(1, out_step(M.pats[p], jm)) << "] = {};\n";
+    Em e(ntmp);
+    const bool weighs = jm != M_GRAD;
+    const Loads L = record_loads(M, G, members, weighs, jm == M_HPROD, e);
+    std::map<int, int> last;  // reference -> the last member that adds to it
+    for (int p : members)
+        for (int i = 0; i < out_step(M.pats[p], jm); ++i) {
+            const int r = M.pats[p].vg[jm == M_HPROD ? M.pats[p].hvs[i] : i];
+            if (need.count(r)) last[r] = p;
+        }
+    const std::vector<int>& list = jm == M_HPROD ? G.hv_refs : G.jt_refs;
+    auto tag = [](size_t i, const char* what) { return std::string(what) + std::to_string(i) + "_"; };
+    const std::string guard = U.plain() ? "" : "if (pt) ", at_k = U.plain() ? "k" : "kr";
+    for (int p : members) {
+        const Pattern& P = M.pats[p];
+        const std::string pd = "P" + std::to_string(p) + "_";
+        Names nm = input_names(P);
+        if (weighs) nm.wgt = record_weight(e, P, p, jm == M_JTPROD, "C.sigma");
+        const std::vector<char> want = slots_to(P, jm, need);
+        PatternCg cg(P, jm, e, nm);
+        cg.body("o" + std::to_string(p), &want);
+        for (size_t i = 0; i < want.size(); ++i) {
+            if (!want[i]) continue;
+            const int r = P.vg[jm == M_HPROD ? P.hvs[i] : i];
+            const std::string g = "g" + std::to_string(r);
+            e.out(g, g + " + o" + std::to_string(p) + "[" + std::to_string(i) + "]");
+            if (last[r] != p) continue;
+            // the reference's sum is complete: out of registers where it can go
+            const int at = (int)(std::find(list.begin(), list.end(), r) - list.begin());
+            if (std::find(U.bufrefs.begin(), U.bufrefs.end(), r) != U.bufrefs.end())
+                e.raw(guard + "(" + dest(P, jm, pd, "C.out0", false) + ")[" + std::to_string(at) + " * ((" + pd +
+                      ".ndata + 15) & ~15LL) + " + at_k + "] = " + g + ";");
+            else if (std::find(U.direct.begin(), U.direct.end(), r) != U.direct.end())
+                e.raw(guard + "OUT[ix" + std::to_string(r) + "] = " + g + ";");
+            else
+                for (auto& x : U.shared)
+                    if (x.first == r) e.raw("if (pt) s" + std::to_string(r) + " += " + g + ";");
+        }
+    }
+    // pulled contributions before the sweep, so that their loads are in
+    // flight with the unit's own
+    for (size_t i = 0; i < U.chains.size(); ++i) {
+        const OwnChain& c = U.chains[i];
+        os << "            const long long v" << i << "_ = " << at_k << " + P0.vd[" << c.top << "];\n";
+        const std::string v = "v" + std::to_string(i) + "_";
+        emit_pulls(M, jm, c.before, v, tag(i, "b"), "            ", os);
+        emit_pulls(M, jm, c.after, v, tag(i, "c"), "            ", os);
+        if (mode == M_LAG) emit_pulls(M, jm, c.grad, v, tag(i, "q"), "            ", os);
+    }
+    const std::set<std::string> names = e.emit(os, "            ");
+    for (size_t i = 0; i < U.chains.size(); ++i) {
+        const OwnChain& c = U.chains[i];
+        int span = 0;
+        for (auto& r : c.refs) span = std::max(span, r.first);
+        const std::string a = "a" + std::to_string(i) + "_", ind = "            ";
+        os << ind << "double " << a << " = 0.0;\n";
+        emit_adds(c.before.size(), a, tag(i, "b"), ind, os);
+        for (auto& r : c.refs) {
+            const std::string g = "g" + std::to_string(r.second), sh = std::to_string(r.first);
+            if (r.first == 0) {
+                os << ind << (U.S ? "if (kr >= 0) " : "") << a << " += " << g << ";\n";
+            } else {
+                const std::string h = "h" + std::to_string(r.second);
+                os << ind << "const double " << h << " = __shfl_down(" << g << ", " << sh << ");\n";
+                os << ind << "if (kr >= -" << sh << " && kr < n - " << sh << ") " << a << " += " << h << ";\n";
+            }
+        }
+        emit_adds(c.after.size(), a, tag(i, "c"), ind, os);
+        const std::string own = U.S ? "lane < " + W + " && kr >= -" + std::to_string(span) + " && kr < n" : U.plain() ? "" : "pt";
+        emit_result(mode, c.grad.size(), a, tag(i, "q"), ind, "OUT[v" + std::to_string(i) + "_]", own, os);
+    }
+    os << "        }\n";
+    for (auto& x : U.shared) {
+        const std::string sv = "s" + std::to_string(x.first);
+        for (int st = 32; st >= x.second; st >>= 1) os << "        " << sv << " += __shfl_xor(" << sv << ", " << st << ");\n";
+        const int at = (int)(std::find(list.begin(), list.end(), x.first) - list.begin());
+        const std::string pd = "P" + std::to_string(members[0]) + "_";
+        os << "        if (lane < " << x.second << ") (" << dest(M.pats[members[0]], jm, pd, "C.out0", false) << ")[" << at
+           << " * ((n + 15) & ~15LL) + (long long)lane * P0.nrun[" << sum << "] + run] = " << sv << ";\n";
+    }
+    os << "    }\n}\n";
+    record_live(M, members, L, names, live);
+    live.outputs += (int64_t)(U.bufrefs.size() + U.direct.size() + U.chains.size());
+    return os.str();
+}
+
+// The plan's code for one mode (the pulled contributions' functions first).
+std::string own_units(const Model& M, int mode, int& ntmp, std::map<std::pair<int, int>, UnitLive>* live) {
+    const int jm = mode == M_LAG ? M_JTPROD : mode;
+    const SumKind sum = sum_of(jm);
+    const OwnPlan& plan = M.own[sum];
+    std::ostringstream os;
+    std::map<std::string, UnitLive> pulled;
+    auto need = [&](const std::vector<OwnSrc>& v, UnitLive& into) {
+        for (const OwnSrc& s : v) {
+            const std::string nm = pull_name(s, jm);
+            if (!pulled.count(nm)) {
+                UnitLive L;
+                const std::string fn = pull_fn(M, jm, s, ntmp, L);
+                // the Lagrangian gradient's units pull J^T w contributions
+                // through the functions of the J^T w units
+                if (!(mode == M_LAG && s.pat < 0)) os << fn;
+                pulled[nm] = L;
+            }
+            into.extra += pulled[nm].extra;
+        }
+    };
+    for (const OwnUnit& U : plan.units) {
+        UnitLive L;
+        need(U.srcs, L);
+        if (mode == M_LAG) need(U.grad, L);
+        for (const OwnChain& c : U.chains) {
+            need(c.before, L);
+            need(c.after, L);
+            if (mode == M_LAG) need(c.grad, L);
+        }
+        os << (U.vunit >= 0 ? own_vunit(M, mode, U, sum, L) : own_hunit(M, mode, U, sum, ntmp, L));
+        if (live) (*live)[{mode, U.code}] = L;
+    }
+    return os.str();
+}
+
+// Fill of variables nothing contributes to (case of a mode's kernel).
+std::string own_fill(int mode, const std::string& C, const std::string& inst) {
+    const std::string at = C + ".out1 + " + inst + ".off[" + std::to_string(EXA_OFF_X) + "] + T.start";
+    return mode == M_LAG ? "exa_fill(" + at + ", T.count, " + C + ".sigma * 0.0 + 0.0)" : "exa_fill(" + at + ", T.count, 0.0)";
+}
+
+// A model's source holds a sum's own units, or its general ones; a host-only
+// model's both, so that either can be compiled and accounted.
+bool emits_general(const Model& M, int mode) { return !M.use_own || !own_plan(M, mode, true); }
+
 }  // namespace
 
 const std::vector<int>& job_modes(int mode) {
@@ -1084,7 +1470,19 @@ const std::vector<int>& job_modes(int mode) {
     // units hold too many registers)
     static const std::vector<int> full = {M_GRAD, M_CONS, M_JAC, M_HESS, M_JPROD, M_HPROD};
     static const std::vector<int> ipm = {M_GRAD, M_CONS, M_JAC, M_HESS};
-    return mode == M_SFULL ? full : mode == M_SIPM ? ipm : one[mode];
+    static const std::vector<int> lag = {M_JTPROD}, gradl = {M_GRAD};
+    return mode == M_SFULL ? full : mode == M_SIPM ? ipm : mode == M_LAG ? lag : mode == M_GRADL ? gradl : one[mode];
+}
+
+const std::vector<int>& job_modes(const Model& M, int mode) {
+    if (!multi_unit_mode(mode)) return job_modes(mode);
+    const bool g = own_plan(M, M_GRAD, M.use_own) != nullptr, h = own_plan(M, M_HPROD, M.use_own) != nullptr;
+    static const std::vector<int> full[4] = {{M_GRAD, M_CONS, M_JAC, M_HESS, M_JPROD, M_HPROD},
+                                             {M_CONS, M_JAC, M_HESS, M_JPROD, M_HPROD},
+                                             {M_GRAD, M_CONS, M_JAC, M_HESS, M_JPROD},
+                                             {M_CONS, M_JAC, M_HESS, M_JPROD}};
+    static const std::vector<int> ipm[2] = {{M_GRAD, M_CONS, M_JAC, M_HESS}, {M_CONS, M_JAC, M_HESS}};
+    return mode == M_SFULL ? full[(g ? 1 : 0) + (h ? 2 : 0)] : ipm[g ? 1 : 0];
 }
 
 bool pattern_in_mode(const Pattern& P, int mode) {
@@ -1114,15 +1512,21 @@ std::vector<Unit> units_for(const Model& M, int mode, bool fused) {
     // lane: their units always hold the whole group
     if (mode == M_JTPROD || mode == M_HPROD) fused = true;
     if (multi_unit(mode))
-        for (int m : job_modes(mode)) fused = fused || m == M_JTPROD || m == M_HPROD;
+        for (int m : job_modes(M, mode)) fused = fused || m == M_JTPROD || m == M_HPROD;
     std::vector<Unit> out;
     for (size_t g = 0; g < M.groups.size(); ++g) {
         const Group& G = M.groups[g];
         std::vector<int> in;
-        for (int p : G.members)
-            if (pattern_in_mode(M.pats[p], mode)) in.push_back(p);
+        bool whole = true;  // a fused unit's code holds every member of the mode
+        for (int p : G.members) {
+            if (mode == M_GRADL && M.own[SUM_JT].drop[p])
+                whole = whole && !pattern_in_mode(M.pats[p], M_GRAD);
+            else if (std::any_of(job_modes(M, mode).begin(), job_modes(M, mode).end(),
+                                 [&](int m) { return pattern_in_mode(M.pats[p], m); }))
+                in.push_back(p);
+        }
         if (in.empty()) continue;
-        if (fused && in.size() > 1) {
+        if (fused && whole && in.size() > 1) {
             Unit u;
             u.code = EXA_MAX_PATTERNS + (int)g;
             u.group = (int)g;
@@ -1149,7 +1553,7 @@ std::vector<Unit> units_for(const Model& M, int mode, bool fused) {
 int mode_lds_doubles(const Model& M, int mode) {
     if (mode == M_JH || multi_unit(mode)) {
         int d = EXA_BLOCK_MAX;
-        for (int m : job_modes(mode)) d = std::max(d, mode_lds_doubles(M, m));
+        for (int m : job_modes(M, mode)) d = std::max(d, mode_lds_doubles(M, m));
         return d;
     }
     int st = 1;
@@ -1184,6 +1588,7 @@ std::string generate_source(const Model& M, std::map<std::pair<int, int>, UnitLi
     os << "static_assert(sizeof(ExaInstDev) == " << sizeof(ExaInstDev) << ", \"layout\");\n";
     os << "static_assert(sizeof(ExaTile) == " << sizeof(ExaTile) << ", \"layout\");\n";
     os << "static_assert(sizeof(ExaCall) == " << sizeof(ExaCall) << ", \"layout\");\n";
+    os << "// sums finished by units: " << M.own_sig << "\n";
     std::string pre = R"(
 __device__ __forceinline__ double exa_powi(double u, int n) {
     double r = 1.0, b = u;
@@ -1238,19 +1643,19 @@ __device__ __forceinline__ void exa_store(double* __restrict__ dst, const double
     }
     __syncthreads();
 }
-// Zeros to dst[0 .. n) by the whole workgroup: 16-byte stores from dst's
+// One value to dst[0 .. n) by the whole workgroup: 16-byte stores from dst's
 // first 16-byte boundary on, the element before it and an odd last element
 // on their own (ordinary stores: a reduction may read the entries back).
-__device__ __forceinline__ void exa_zero_fill(double* __restrict__ dst, long long n) {
+__device__ __forceinline__ void exa_fill(double* __restrict__ dst, long long n, double val) {
     const long long h = ((((unsigned long long)dst >> 3) & 1ull) && n > 0) ? 1 : 0;
     const long long n2 = (n - h) >> 1;
     exa_d2 z;
-    z.x = 0.0;
-    z.y = 0.0;
+    z.x = val;
+    z.y = val;
     for (long long i = threadIdx.x; i < n2; i += blockDim.x) *(exa_d2*)(dst + h + 2 * i) = z;
     if (threadIdx.x == 0) {
-        if (h) dst[0] = 0.0;
-        if (h + 2 * n2 < n) dst[n - 1] = 0.0;
+        if (h) dst[0] = val;
+        if (h + 2 * n2 < n) dst[n - 1] = val;
     }
 }
 // Slot-major store to a work buffer: slot s of data point k at
@@ -1328,8 +1733,9 @@ __device__ __forceinline__ int exa_term(int j, int je) { return j < je ? j : (je
     for (int mode = 0; mode < M_COUNT; ++mode) {
         // units of both schedules (separate patterns, fused groups)
         std::map<int, Unit> all;
-        for (int fused = 0; fused < 2; ++fused)
-            for (auto& u : units_for(M, mode, fused != 0)) all[u.code] = u;
+        if (emits_general(M, mode))
+            for (int fused = 0; fused < 2; ++fused)
+                for (auto& u : units_for(M, mode, fused != 0)) all[u.code] = u;
         if (mode == M_CONS || mode == M_JPROD)
             for (size_t a = 0; a < M.pats.size(); ++a)
                 if (M.pats[a].kind == EXA_AUG && M.pats[a].ndata > 0) {
@@ -1345,9 +1751,17 @@ __device__ __forceinline__ int exa_term(int j, int je) { return j < je ? j : (je
             cases.push_back("case " + std::to_string(kv.first) + ": unit_" + mode_name(mode) + "_" +
                             std::to_string(kv.first) + "(C, I, T, lds); break;");
         }
+        if (const OwnPlan* plan = own_plan(M, mode, true)) {
+            os << own_units(M, mode, ntmp, live);
+            for (const OwnUnit& u : plan->units)
+                cases.push_back("case " + std::to_string(u.code) + ": own_" + mode_name(mode) + "_" +
+                                std::to_string(u.code) + "(C, I, T, lds); break;");
+            if (mode != M_GRAD)
+                cases.push_back("case " + std::to_string(EXA_ZERO_TILE) + ": " + own_fill(mode, "C", "I") + "; break;");
+        }
         if (mode == M_GRAD)  // entries of g no objective term touches
-            cases.push_back("case " + std::to_string(EXA_ZERO_TILE) + ": exa_zero_fill(C.out0 + I.off[" +
-                            std::to_string(EXA_OFF_X) + "] + T.start, T.count); break;");
+            cases.push_back("case " + std::to_string(EXA_ZERO_TILE) + ": exa_fill((C.direct ? C.out0 : C.out1) + I.off[" +
+                            std::to_string(EXA_OFF_X) + "] + T.start, T.count, 0.0); break;");
         kernel(kernel_name(mode), mode_lds_doubles(M, mode), cases);
     }
     // Several callbacks in one launch: a tile's mode sits above
@@ -1373,19 +1787,31 @@ __device__ __forceinline__ int exa_term(int j, int je) { return j < je ? j : (je
         os << "    }\n";
         os << "}\n";
     };
+    // the units of a mode in a several-callback kernel; M_LAG's tiles use the
+    // call record of J^T w
     auto mode_cases = [&](int mode, std::vector<std::string>& cases) {
         std::set<int> codes;
-        for (int fused = 0; fused < 2; ++fused)
-            for (auto& u : units_for(M, mode, fused != 0)) codes.insert(u.code);
-        const std::string K = "C.c[" + std::to_string(mode) + "]";
-        for (int c : codes)
-            cases.push_back("case " + std::to_string((mode << EXA_MODE_SHIFT) | c) + ": unit_" + mode_name(mode) + "_" +
+        if (mode != M_LAG && emits_general(M, mode))
+            for (int fused = 0; fused < 2; ++fused)
+                for (auto& u : units_for(M, mode, fused != 0)) codes.insert(u.code);
+        const std::string K = "C.c[" + std::to_string(mode == M_LAG ? (int)M_JTPROD : mode) + "]";
+        auto add = [&](int c, const char* pre) {
+            cases.push_back("case " + std::to_string((mode << EXA_MODE_SHIFT) | c) + ": " + pre + mode_name(mode) + "_" +
                             std::to_string(c) + "(" + K + ", " + K + ".inst[T.inst], T, lds); break;");
+        };
+        for (int c : codes) add(c, "unit_");
+        const OwnPlan* plan = own_plan(M, mode, true);
+        if (!plan) return;
+        for (const OwnUnit& u : plan->units) add(u.code, "own_");
+        if (mode != M_GRAD)
+            cases.push_back("case " + std::to_string((mode << EXA_MODE_SHIFT) | EXA_ZERO_TILE) + ": " +
+                            own_fill(mode, K, K + ".inst[T.inst]") + "; break;");
     };
     const std::string G = "C.c[" + std::to_string(M_GRAD) + "]";
     const std::string zero_case = "case " + std::to_string((M_GRAD << EXA_MODE_SHIFT) | EXA_ZERO_TILE) +
-                                  ": exa_zero_fill(" + G + ".out0 + " + G + ".inst[T.inst].off[" +
-                                  std::to_string(EXA_OFF_X) + "] + T.start, T.count); break;";
+                                  ": exa_fill((" + G + ".direct ? " + G + ".out0 : " + G + ".out1) + " + G +
+                                  ".inst[T.inst].off[" + std::to_string(EXA_OFF_X) + "] + T.start, T.count, 0.0); break;";
+    if (M.lag_units) os << own_units(M, M_LAG, ntmp, live);
     // every unit's tiles share a kernel's register budget: ask for at least
     // four waves per SIMD, so that one wave of the launch fits on the chip at
     // once.  The Jacobian + Hessian units need the most registers, so they
@@ -1400,6 +1826,7 @@ __device__ __forceinline__ int exa_term(int j, int je) { return j < je ? j : (je
             lds = std::max(lds, mode_lds_doubles(M, mode));
             mode_cases(mode, cases);
         }
+        if (M.lag_units) mode_cases(M_LAG, cases);
         cases.push_back(zero_case);
         multi_kernel(jh ? "exa_k_multijh" : "exa_k_multi", lds, cases, jh ? 4 : 5);
     }
@@ -1420,9 +1847,12 @@ __device__ __forceinline__ int exa_term(int j, int je) { return j < je ? j : (je
                                 "].inst[T.inst], T, lds); break;");
             }
         }
-        // the objective's and J^T w's tiles
+        // the objective's and J^T w's tiles, and those of sums whose units
+        // finish variables
         mode_cases(M_OBJ, cases);
         mode_cases(M_JTPROD, cases);
+        if (own_plan(M, M_HPROD, true)) mode_cases(M_HPROD, cases);
+        if (own_plan(M, M_GRAD, true)) mode_cases(M_GRAD, cases);
         lds = std::max(lds, mode_lds_doubles(M, M_JTPROD));
         cases.push_back(zero_case);
         multi_kernel("exa_k_onepass", lds, cases, 0);

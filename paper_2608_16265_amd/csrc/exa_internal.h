@@ -46,10 +46,23 @@ void set_last_error(const std::string& msg);
 #define EXA_MAX_REFS 48
 // Tile code of a zero-fill tile (entries of g no objective term touches).
 #define EXA_ZERO_TILE 1023
+// Codes of the units that finish variables themselves (OwnUnit): data set g
+// -> EXA_OWN_CODE + g, the j-th unit over variables -> EXA_OWN_VCODE + j.
+#define EXA_OWN_CODE 128
+#define EXA_OWN_VCODE 256
+#define EXA_MAX_VUNITS 32
 #define EXA_PAD_TILE 4095  // a tile that matches no unit: does nothing
 
 // ExaPatDev::hvd: bit r set when the pattern's group stores H v reference r
 // straight into the output (Group::hv_direct, for this instance's data).
+// ExaPatDev::vd, inv, icmin, icmax, runl, nrun are filled for the first
+// pattern of a data set: vd[r] is the shift of group reference r (variable =
+// data point + vd[r] when its index column counts up by one; variable =
+// column value + vd[r] when the column's inverse table inv[c] is used), inv[c]
+// maps column values icmin[c] .. icmax[c] to their data point or -1, runl[s]
+// and nrun[s] are the 64-lane chunks per run and the runs of the data set's
+// unit for sum s (SumKind).  ExaInstDev::vlo[s][j]: the first variable of the
+// j-th unit over variables of sum s.
 #define EXA_DEVICE_STRUCTS                                                       \
     struct ExaPatDev {                                                           \
         const int* ic[8];                                                        \
@@ -68,11 +81,18 @@ void set_last_error(const std::string& msg);
         const int* rptr;                                                         \
         const int* ridx;                                                         \
         long long roff[48];                                                      \
+        long long vd[48];                                                        \
+        const int* inv[8];                                                       \
+        int icmin[8];                                                            \
+        int icmax[8];                                                            \
+        int runl[4];                                                             \
+        int nrun[4];                                                             \
     };                                                                           \
     struct ExaInstDev {                                                          \
         long long off[12];                                                       \
         const double* theta;                                                     \
         long long pad1;                                                          \
+        long long vlo[4][32];                                                    \
         struct ExaPatDev pat[32];                                                \
     };                                                                           \
     struct ExaTile {                                                             \
@@ -133,8 +153,11 @@ static_assert(M_COUNT == 10, "ExaMulti holds one call per mode");
 // M_SIPM:  grad, cons, jac, hess (an interior-point iterate).
 constexpr int M_SFULL = 10, M_SIPM = 11;
 inline bool multi_unit_mode(int mode) { return mode == M_SFULL || mode == M_SIPM; }
-// Component modes of a unit mode (itself for plain modes, jac + hess for JH).
-const std::vector<int>& job_modes(int mode);
+// The Lagrangian gradient of variables whose J^T y and objective gradient the
+// units finish themselves: M_LAG runs the J^T w units with sigma * gradient
+// added (call record of M_JTPROD), M_GRADL the gradient's tiles of the other
+// variables (call record and code of M_GRAD).
+constexpr int M_LAG = 12, M_GRADL = 13;
 // Tiles of the several-callback kernel carry their mode above this bit of
 // the unit code (unit codes stay below 1 << EXA_MODE_SHIFT).
 #define EXA_MODE_SHIFT 12
@@ -161,9 +184,14 @@ struct Pattern {
     int64_t ndata = 0;
     int n_icols = 0, n_fcols = 0;
     std::vector<std::vector<int32_t>> icols;   // host copies (index columns)
-    // index column c holds 0, 1, ..., ndata - 1 (at least kIdentMin points):
-    // the generated code uses the data point itself instead of loading it
+    // index column c holds c0, c0 + 1, ..., c0 + ndata - 1 (at least kIdentMin
+    // points): the generated code uses the data point itself instead of
+    // loading it (c0 sits in the references' offsets)
     std::vector<char> ident;
+    // index column c holds c0, c0 + 1, ... (any length); c0 = icols[c][0].
+    // The generated code counts such columns of at least kIdentMin points
+    // from the data point (ident), with c0 folded into the index offsets
+    std::vector<char> affine;
     std::vector<const double*> fcols_src;      // caller's float columns (create only)
     std::vector<RefKey> vslots;       // unique var refs, first-visit order
     std::vector<RefKey> pslots;       // unique param refs
@@ -255,6 +283,7 @@ struct UnitLive {
     int weights = 0;                   // y entries (one per member that needs it)
     int64_t outputs = 0;               // doubles written per data point
     bool pulls = false;                // base rows pull augmentation terms
+    int64_t extra = 0;                 // bytes per point or variable of pulled contributions
 };
 
 // Sorted reduction map (CSR): segment s sums buf[idx[ptr[s] .. ptr[s+1])].
@@ -264,6 +293,67 @@ struct SegMap {
     // no entries, its output is written by the evaluation kernel
     std::vector<char> skip;
     int64_t nseg() const { return ptr.empty() ? 0 : (int64_t)ptr.size() - 1; }
+};
+
+// ---- sums finished by the units themselves -----------------------------------
+// A variable whose contributions to a sum all come through strictly increasing
+// index columns gets at most one from each (data set, reference), at a data
+// point that follows from the variable.  Such a variable needs no work buffer
+// and no map: a unit adds its contributions in the map's order (data set,
+// point, reference) and stores the sum.  plan_sums finds these variables per
+// sum, in clusters (intervals of variables whose references overlap), and the
+// units that own them:
+//  * the unit of a host data set whose columns count up by one: lane of point
+//    k owns variable k + top, takes the contributions of the references whose
+//    offset is smaller by s from the lane s further up (a wave's last lanes
+//    recompute the next wave's first points: W = 64 - S owners per wave), and
+//    evaluates ("pulls") the contributions of other data sets itself;
+//  * otherwise a unit over the cluster's variables, one lane each, which pulls
+//    every contribution (through the column's inverse table where a column
+//    has gaps).
+// References that few variables share (a literal index, or a column that
+// repeats with a period of 2 to 32 points) leave one partial sum per run of
+// chunks instead of one entry per point: a wave adds its lanes.
+enum SumKind : int { SUM_JT = 0, SUM_HV = 1, SUM_GRAD = 2, SUM_COUNT = 3 };
+struct OwnSrc {
+    int group = 0, ref = 0;  // data set and group reference
+    int how = 0;             // OWN_AFFINE or OWN_INVERSE
+    int wread = -1;          // augmentation pattern whose +-w[row] this is
+    int pat = -1;            // objective pattern (gradient contributions)
+    bool sparse = false;     // hits under three quarters of the unit's variables: behind a branch
+};
+constexpr int OWN_AFFINE = 0, OWN_INVERSE = 1;
+constexpr int kOwnSpan = 8;  // largest lane shift of a chain
+struct OwnChain {
+    int top = 0;                             // reference with the largest offset
+    std::vector<std::pair<int, int>> refs;   // (lane shift, reference), summation order
+    std::vector<OwnSrc> before, after;       // pulled, from data sets before / after the host
+    std::vector<OwnSrc> grad;                // pulled objective gradient (Lagrangian gradient only)
+};
+struct OwnUnit {
+    int code = 0;
+    int group = -1;                  // host data set, or -1: a unit over variables
+    std::vector<OwnChain> chains;    // host units
+    int S = 0;                       // largest lane shift
+    std::vector<int> bufrefs;        // references that go to the work buffer, one entry per point
+    std::vector<std::pair<int, int>> shared;  // (reference, period): partial sums
+    std::vector<int> direct;         // H v references stored straight into the output
+    int vunit = -1;                  // units over variables: index j, and their pulled sources in order
+    std::vector<OwnSrc> srcs, grad;
+    int64_t lo = 0, n = 0;           // units over variables: this instance's range
+    // host units: this instance's points, chunks per run and runs
+    int64_t npts = 0;
+    int64_t runl = 1, nrun = 0;
+    // lanes take points as in any unit (no shifts, no sums over a wave)
+    bool plain() const { return S == 0 && shared.empty(); }
+};
+struct OwnPlan {
+    bool on = false;
+    std::vector<OwnUnit> units;
+    std::vector<std::pair<int64_t, int64_t>> fill;  // (first, count): variables nothing contributes to
+    std::vector<char> skip;   // variables the units write (owned, filled or direct)
+    std::vector<char> drop;   // per objective pattern: its gradient is owned (M_GRADL leaves it out)
+    std::vector<std::pair<int64_t, int64_t>> lag_zero;  // gradient zero ranges of M_GRADL
 };
 
 struct DeviceState;  // defined in exa_runtime.cpp
@@ -283,6 +373,13 @@ struct Model {
     std::vector<double> xl, xu, theta;
     // reduction maps (positions in the first-order buffer: grad part first)
     SegMap grad_map, jt_map, h_map, par_map;
+    // sums finished by the units (per SumKind); device models run them, and
+    // their maps hold the other variables only (host-only models, and batches
+    // whose instances' plans differ, use the general maps and units)
+    OwnPlan own[SUM_COUNT];
+    bool use_own = false;
+    std::string own_sig;     // what the plans fix in the generated code
+    bool lag_units = false;  // the Lagrangian gradient runs M_LAG units
     bool host_only = false;
     int block = 256, epl = 4;
     bool autotune = false, fuse = false;
@@ -320,7 +417,19 @@ std::string pattern_signature(const Model& M);
 // of one size.  The generated pulls of such augmentations share one walk.
 bool same_walk(const Model& M, int a, int b);
 
+// exa_owner.cpp
+void plan_sums(Model& M);
+// The map of a sum: with own, of the variables the plan's units leave to the
+// reduction; without, of every variable.
+void sum_map(const Model& M, SumKind s, bool own, SegMap& out);
+// The plan a mode's launch runs on (nullptr: general units).
+const OwnPlan* own_plan(const Model& M, int mode, bool own);
+
 // exa_codegen.cpp
+// Component modes of a unit mode (itself for plain modes, jac + hess for JH);
+// one-pass units leave out the gradient or H v when own units finish them.
+const std::vector<int>& job_modes(const Model& M, int mode);
+const std::vector<int>& job_modes(int mode);
 #define EXA_BLOCK_MAX 256
 bool pattern_in_mode(const Pattern& P, int mode);
 // Modes the several-callback kernels evaluate: exa_k_multi (Jacobian and

@@ -19,7 +19,9 @@ hipError_t exa_launch_copy(const void* src, void* dst, int64_t bytes, hipStream_
 //   lpart[2r] (the segment's parts are numbered from its first part up).
 //   Part blocks are interleaved over the segments (the i-th part of every
 //   long segment before any (i+1)-th), so a contiguous range of part blocks
-//   covers the same range of points for every long segment;
+//   covers the same range of points for every long segment.  With
+//   longs[5i+4] = 0 the segment's one block adds all its entries, strided per
+//   lane and by the same tree, and writes the result itself;
 // * the other segments, unless chunked is set: one lane per segment, entries
 //   in ascending j;
 // A position below zero is a weight entry ~(2 row + neg): the value is
@@ -35,6 +37,11 @@ hipError_t exa_launch_copy(const void* src, void* dst, int64_t bytes, hipStream_
 constexpr int kExaChunk = 4;
 constexpr int kExaLongSeg = 256 * kExaChunk;
 constexpr int kExaShortSeg = 16;
+// Maps of what units that finish sums leave over: segments longer than
+// kExaWholeSeg and up to kExaWholeMax are added by one workgroup each
+// (longs[5i+4] = 0).  A first lane adding more than 64 chunk sums one after
+// another, or part sums with a second launch, takes longer.
+constexpr int kExaWholeSeg = 256, kExaWholeMax = 16384;
 struct ExaSegJob {
     const void* ptr;
     const void* idx;
@@ -51,6 +58,8 @@ struct ExaSegJob {
     double* lsum;
     int32_t wide;    // ptr/idx are int64 when set, else int32
     int32_t chunked;
+    // one-lane segments longer than this are left to the part blocks (0: none are)
+    int32_t long_len;
 };
 constexpr int kExaReduceJobs = 3;
 // Up to three segment-sum jobs and, when part is not null, the sum of the
@@ -98,7 +107,7 @@ struct ExaBatchJob {
     int64_t nseg, nlanes, nparts, nlong;
     int64_t buf_off, out_off;
     int64_t w_off;  // the instance's first row in the call's weights
-    int32_t wide, chunked;
+    int32_t wide, chunked, long_len;
     int32_t buf, out;
     int32_t kind;  // 0: segment sums; 1: objective partials (nseg of them) into one value
     int32_t ep;    // 1: out = alpha * out + sum, the product rounded first

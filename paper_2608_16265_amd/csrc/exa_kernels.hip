@@ -52,11 +52,11 @@ __device__ __forceinline__ double entry(const double* __restrict__ buf, const do
 template <class I>
 __device__ __forceinline__ void seg_body(const I* __restrict__ ptr, const I* __restrict__ idx,
                                          const double* __restrict__ buf, const double* __restrict__ w,
-                                         double* __restrict__ out, int64_t s, bool parts, bool ep, double alpha) {
+                                         double* __restrict__ out, int64_t s, int32_t long_len, bool ep, double alpha) {
     const I pb = ptr[s], pe = ptr[s + 1];
     if (pe < 0) return;
     const int64_t b = pb < 0 ? ~pb : pb, e = pe;
-    if (parts && e - b > kExaLongSeg) return;  // summed in parts
+    if (long_len && e - b > long_len) return;  // summed by blocks of its own
     double acc = 0.0;
     int64_t j = b;
     // four entries at a time: their index and value loads are issued
@@ -120,13 +120,33 @@ __device__ __forceinline__ double block_sum(double v, double* lds) {
 // Part block r (see ExaSegJob): part q of long segment ls, lane t adds
 // entries 4t .. 4t+3 of the part and the block adds the lanes by block_sum
 // into lsum[q].  Called by every lane of the workgroup.
-__device__ __forceinline__ void long_part_body(const ExaSegJob& J, int64_t r, double* lds) {
+__device__ __forceinline__ void long_part_body(const ExaSegJob& J, int64_t r, double* lds, bool ep, double alpha) {
 #pragma clang fp contract(off)
     const int32_t* __restrict__ idx = (const int32_t*)J.idx;
     const double* __restrict__ buf = J.buf;
     const int2 lq = ((const int2*)J.lpart)[r];
     const int32_t ls = lq.x, q = lq.y;
     const int32_t beg = J.longs[5 * ls + 1], len = J.longs[5 * ls + 2], part0 = J.longs[5 * ls + 3];
+    if (J.longs[5 * ls + 4] == 0) {
+        // the whole segment: lane t adds entries t, t + 256, ... in that
+        // order, eight positions and then eight values in flight (a segment
+        // of 4,096 partial sums is two rounds deep)
+        double acc = 0.0;
+        for (int32_t j = threadIdx.x; j < len; j += 256 * 8) {
+            int32_t ix[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) ix[u] = idx[beg + min(j + 256 * u, len - 1)];
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = entry(buf, J.w, ix[u]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (j + 256 * u < len) acc += v[u];
+        }
+        const double s = block_sum(acc, lds);
+        if (threadIdx.x == 0) put(J.out, J.longs[5 * ls], s, ep, alpha);
+        return;
+    }
     const int32_t pb = beg + ((int32_t)q - part0) * kExaLongSeg;
     const int32_t pe = min(beg + len, pb + kExaLongSeg);
     const int32_t j0 = pb + kExaChunk * (int32_t)threadIdx.x;
@@ -192,20 +212,20 @@ __global__ void __launch_bounds__(kSegBlock) k_reduce(ExaReduce R, int64_t per_x
         if (b < nlb)
             chunk_body(J, b * kSegBlock + threadIdx.x, lds, ep, R.ax_alpha);
         else
-            long_part_body(J, b - nlb, lds);
+            long_part_body(J, b - nlb, lds, ep, R.ax_alpha);
         return;
     }
     const int64_t nsb = (J.nseg + kSegBlock - 1) / kSegBlock;
     if (b >= nsb) {
-        long_part_body(J, b - nsb, lds);
+        long_part_body(J, b - nsb, lds, ep, R.ax_alpha);
         return;
     }
     const int64_t s = b * kSegBlock + threadIdx.x;
     if (s < J.nseg) {
         if (J.wide)
-            seg_body((const int64_t*)J.ptr, (const int64_t*)J.idx, J.buf, J.w, J.out, s, false, ep, R.ax_alpha);
+            seg_body((const int64_t*)J.ptr, (const int64_t*)J.idx, J.buf, J.w, J.out, s, 0, ep, R.ax_alpha);
         else
-            seg_body((const int32_t*)J.ptr, (const int32_t*)J.idx, J.buf, J.w, J.out, s, J.nparts > 0, ep,
+            seg_body((const int32_t*)J.ptr, (const int32_t*)J.idx, J.buf, J.w, J.out, s, J.long_len, ep,
                      R.ax_alpha);
     }
 }
@@ -221,6 +241,7 @@ __global__ void __launch_bounds__(kSegBlock) k_reduce_long(ExaReduce R) {
         if (b < J.nlong) {
             const int32_t* L = J.longs + 5 * b;
             const int32_t seg = L[0], part0 = L[3], nparts = L[4];
+            if (nparts == 0) return;  // added whole by the first launch
             // lane t adds parts t, t + 256, ... in that order; eight loads
             // are issued before their adds, so a segment of thousands of
             // parts is a few dependent round trips deep, not one per part
@@ -258,6 +279,7 @@ __device__ __forceinline__ ExaSegJob batch_seg(const ExaBatchReduce& R, const Ex
     J.nparts = B.nparts;
     J.nlong = B.nlong;
     J.lsum = B.lsum;
+    J.long_len = B.long_len;
     J.wide = B.wide;
     J.chunked = B.chunked;
     return J;
@@ -293,20 +315,20 @@ __global__ void __launch_bounds__(kSegBlock) k_reduce_batch(ExaBatchReduce R) {
         if (b < nlb)
             chunk_body(J, b * kSegBlock + threadIdx.x, lds, ep, R.alpha);
         else
-            long_part_body(J, b - nlb, lds);
+            long_part_body(J, b - nlb, lds, ep, R.alpha);
         return;
     }
     const int64_t nsb = (J.nseg + kSegBlock - 1) / kSegBlock;
     if (b >= nsb) {
-        long_part_body(J, b - nsb, lds);
+        long_part_body(J, b - nsb, lds, ep, R.alpha);
         return;
     }
     const int64_t s = b * kSegBlock + threadIdx.x;
     if (s < J.nseg) {
         if (J.wide)
-            seg_body((const int64_t*)J.ptr, (const int64_t*)J.idx, J.buf, J.w, J.out, s, false, ep, R.alpha);
+            seg_body((const int64_t*)J.ptr, (const int64_t*)J.idx, J.buf, J.w, J.out, s, 0, ep, R.alpha);
         else
-            seg_body((const int32_t*)J.ptr, (const int32_t*)J.idx, J.buf, J.w, J.out, s, J.nparts > 0, ep, R.alpha);
+            seg_body((const int32_t*)J.ptr, (const int32_t*)J.idx, J.buf, J.w, J.out, s, J.long_len, ep, R.alpha);
     }
 }
 
@@ -319,6 +341,7 @@ __global__ void __launch_bounds__(kSegBlock) k_reduce_batch_long(ExaBatchReduce 
     const ExaSegJob J = batch_seg(R, B);
     const int32_t* L = J.longs + 5 * jl.y;
     const int32_t seg = L[0], part0 = L[3], nparts = L[4];
+    if (nparts == 0) return;  // added whole by the first launch
     double acc = 0.0;
     for (int32_t i0 = threadIdx.x; i0 < nparts; i0 += 256 * 8) {
         double v[8];
@@ -377,7 +400,8 @@ hipError_t exa_launch_reduce(const ExaReduce& r, hipStream_t s) {
         const ExaSegJob& J = r.job[k];
         if (J.chunked && (J.nlanes % kSegBlock || J.wide || (J.nlanes && !(J.lanes && J.lidx))))
             return hipErrorInvalidValue;
-        if (J.nparts && (J.wide || !(J.longs && J.lpart && J.lsum && J.nlong > 0))) return hipErrorInvalidValue;
+        if (J.nparts && (J.wide || !(J.longs && J.lpart) || (J.nlong > 0 && !J.lsum)))
+            return hipErrorInvalidValue;
         blocks += job_blocks(J);
         nlong += J.nparts ? J.nlong : 0;
     }

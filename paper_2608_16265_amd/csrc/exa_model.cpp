@@ -498,7 +498,7 @@ void build_host(Model& M, const exa_pattern_desc* pats, int32_t npats) {
     // The work buffers hold each pattern's block slot-major: slot s of data
     // point k at block + s * bstride() + k (the constraint part of the
     // first-order buffer after the objective part).
-    std::vector<std::pair<int64_t, int64_t>> g, jt, h, pr;
+    std::vector<std::pair<int64_t, int64_t>> g, pr;
     auto gvar = [&](const Group& G, int r, int64_t k) {
         const RefKey& rk = G.vrefs[r];
         return rk.col < 0 ? rk.off : (int64_t)M.pats[G.members[0]].icols[rk.col][k] + rk.off;
@@ -519,39 +519,6 @@ void build_host(Model& M, const exa_pattern_desc* pats, int32_t npats) {
             G.hv_direct[j] = alone ? 1 : 0;
         }
     }
-    std::vector<char> hskip(M.nvar, 0);
-    for (const Group& G : M.groups) {
-        const int64_t bs = (G.ndata + 15) & ~(int64_t)15;
-        // weight entries (Pattern::wread) by reference: ~(2 row + negated)
-        std::map<int, int> wr;
-        for (int p : G.members)
-            if (M.pats[p].wread) wr[M.pats[p].vg[0]] = p;
-        std::vector<int> jall(G.jt_refs.begin(), G.jt_refs.end());
-        for (auto& x : wr) jall.push_back(x.first);
-        std::sort(jall.begin(), jall.end());
-        // a variable sums its group entries in (group, data point, reference)
-        // order
-        for (int64_t k = 0; k < G.ndata; ++k) {
-            for (int r : jall) {
-                const auto w = wr.find(r);
-                if (w != wr.end()) {
-                    const Pattern& A = M.pats[w->second];
-                    const int64_t row = A.tgt0 + (int64_t)A.icols[A.row_icol][k] + A.row_off;
-                    jt.emplace_back(gvar(G, r, k), ~(2 * row + (A.wread < 0 ? 1 : 0)));
-                    continue;
-                }
-                const int64_t j = std::find(G.jt_refs.begin(), G.jt_refs.end(), r) - G.jt_refs.begin();
-                jt.emplace_back(gvar(G, r, k), M.fo_obj_len + G.ob + j * bs + k);
-            }
-            for (size_t j = 0; j < G.hv_refs.size(); ++j) {
-                const int64_t v = gvar(G, G.hv_refs[j], k);
-                if (G.hv_direct[j])
-                    hskip[v] = 1;
-                else
-                    h.emplace_back(v, G.oh + (int64_t)j * bs + k);
-            }
-        }
-    }
     for (auto& P : M.pats) {
         const int st = P.o1step();
         const int64_t bs = P.bstride();
@@ -570,16 +537,6 @@ void build_host(Model& M, const exa_pattern_desc* pats, int32_t npats) {
             if (x.second < 0 || x.second >= len) fail(EXA_EINVAL, std::string("internal: work-buffer position outside the ") + what);
     };
     inside(g, M.fo_obj_len, "objective part of the first-order buffer");
-    for (auto& x : jt)  // weight entries name a constraint row
-        if (x.second < 0 && (~x.second >> 1) >= M.ncon)
-            fail(EXA_EINVAL, "internal: a J^T w weight entry outside the constraint rows");
-    {
-        std::vector<std::pair<int64_t, int64_t>> jb;
-        for (auto& x : jt)
-            if (x.second >= 0) jb.push_back(x);
-        inside(jb, M.fo_obj_len + M.fo_con_len, "first-order buffer");
-    }
-    inside(h, M.hv_len, "H v buffer");
     inside(pr, M.par_len, "parameter buffer");
     for (auto& P : M.pats) {
         const int64_t bs = P.bstride();
@@ -603,18 +560,23 @@ void build_host(Model& M, const exa_pattern_desc* pats, int32_t npats) {
         M.grad_zero.emplace_back(v, e - v);
         v = e;
     }
-    build_map(M.jt_map, M.nvar, jt);
-    build_map(M.h_map, M.nvar, h);
-    if (std::find(hskip.begin(), hskip.end(), 1) != hskip.end()) M.h_map.skip = std::move(hskip);
     build_map(M.par_map, M.ntheta, pr);
+    // which sums the units finish themselves, and the maps of the others
+    plan_sums(M);
+    M.use_own = !M.host_only;
+    sum_map(M, SUM_JT, M.use_own, M.jt_map);
+    sum_map(M, SUM_HV, M.use_own, M.h_map);
+    if (M.use_own && M.own[SUM_GRAD].on) sum_map(M, SUM_GRAD, true, M.grad_map);
+    auto map_inside = [&](const SegMap& S, int64_t lo, int64_t hi, const char* what) {
+        for (int64_t i : S.idx)
+            if (i >= 0 ? (i < lo || i >= hi) : (~i >> 1) >= M.ncon)
+                fail(EXA_EINVAL, std::string("internal: work-buffer position or weight entry outside the ") + what);
+    };
+    map_inside(M.jt_map, M.fo_obj_len, M.fo_obj_len + M.fo_con_len, "first-order buffer");
+    map_inside(M.h_map, 0, M.hv_len, "H v buffer");
     for (auto& P : M.pats) {
         P.ident.assign(P.n_icols, 0);
-        if (P.ndata < kIdentMin) continue;
-        for (int c = 0; c < P.n_icols; ++c) {
-            bool id = true;
-            for (int64_t k = 0; k < P.ndata && id; ++k) id = P.icols[c][k] == k;
-            P.ident[c] = id ? 1 : 0;
-        }
+        for (int c = 0; c < P.n_icols; ++c) P.ident[c] = P.affine[c] && P.ndata >= kIdentMin ? 1 : 0;
     }
     M.signature = pattern_signature(M);
 }

@@ -66,7 +66,7 @@ exa_status exa_hprod_noalloc(exa_model* m, const double* x, const double* y, dou
         DeviceState& D = *M.dev;
         // the H v buffer, then the part sums of long segments (a 128-byte line apart)
         const int64_t hv_len = (M.hv_len + 15) / 16 * 16;
-        const int64_t need_len = hv_len + D.h_map.nparts;
+        const int64_t need_len = hv_len + (D.h_map.nlong > 0 ? D.h_map.nparts : 0);
         if (need_len > kScratchDoubles)
             fail(EXA_EINVAL, "exa_hprod_noalloc: the model needs " + std::to_string(need_len) +
                                  " doubles of work space, more than its fixed " + std::to_string(kScratchDoubles) +
@@ -86,7 +86,7 @@ exa_status exa_hprod_noalloc(exa_model* m, const double* x, const double* y, dou
         c.out1 = Hv;
         launch_mode_untuned(M, M_HPROD, c, s);
         DevMap map = D.h_map;
-        if (map.nparts > 0) map.lsum = sp + hv_len;
+        if (map.nlong > 0) map.lsum = sp + hv_len;
         segsum(map, sp, Hv, s);
         M.counters[7]++;
     });

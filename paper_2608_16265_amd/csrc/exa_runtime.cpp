@@ -243,6 +243,31 @@ void DeviceState::release(void* p) {
 // Tiles of `tile_pts` consecutive data points over the units of a callback.
 std::vector<ExaTile> make_tiles(const Model& M, int mode, int inst, int64_t tile_pts, bool fused, bool fills) {
     std::vector<ExaTile> tiles;
+    auto cut = [&](int code, int64_t first, int64_t n, int64_t per) {
+        for (int64_t s = 0; s < n; s += per) {
+            ExaTile t{};
+            t.pat = code;
+            t.inst = inst;
+            t.start = first + s;
+            t.count = std::min(per, n - s);
+            t.slot = (int64_t)tiles.size();
+            tiles.push_back(t);
+        }
+    };
+    const OwnPlan* plan = mode == M_GRADL ? nullptr : own_plan(M, mode, M.use_own);
+    if (plan) {
+        // units that finish sums: tiles of runs (a run per wave, at least four,
+        // so that a 256-wide workgroup has work for every wave), of variables,
+        // and fills of the variables nothing contributes to
+        for (const OwnUnit& U : plan->units) {
+            if (U.vunit >= 0 || U.plain())
+                cut(U.code, 0, U.vunit >= 0 ? U.n : U.npts, tile_pts);
+            else
+                cut(U.code, 0, U.nrun, std::max<int64_t>(4, tile_pts / (64 * U.runl)));
+        }
+        for (auto& z : plan->fill) cut(EXA_ZERO_TILE, z.first, z.second, std::max(tile_pts, kZeroTileEntries));
+        return tiles;
+    }
     for (const Unit& u : units_for(M, mode, fused)) {
         // a unit whose code reads nothing (constant derivatives only, such as
         // the Jacobian entries of a linear augmentation) is a plain fill: far
@@ -250,7 +275,7 @@ std::vector<ExaTile> make_tiles(const Model& M, int mode, int inst, int64_t tile
         // objective keeps its fixed tiles, which fix its summation order).
         // A launch bound by latency rather than bandwidth keeps short tiles.
         int64_t tp = tile_pts;
-        const auto lv = M.live.find({mode, u.code});
+        const auto lv = M.live.find({tile_mode(mode), u.code});
         const bool many = u.ndata > (int64_t)4096 * tile_pts;
         if (mode != M_OBJ && (fills || many) && lv != M.live.end()) {
             const UnitLive& L = lv->second;
@@ -258,17 +283,50 @@ std::vector<ExaTile> make_tiles(const Model& M, int mode, int inst, int64_t tile
                 L.weights == 0 && !L.pulls)
                 tp = std::max<int64_t>(tp, kZeroTileEntries);
         }
-        for (int64_t s = 0; s < u.ndata; s += tp) {
-            ExaTile t{};
-            t.pat = u.code;
-            t.inst = inst;
-            t.start = s;
-            t.count = std::min(tp, u.ndata - s);
-            t.slot = (int64_t)tiles.size();
-            tiles.push_back(t);
-        }
+        cut(u.code, 0, u.ndata, tp);
     }
+    if (mode == M_GRADL)
+        for (auto& z : M.own[SUM_JT].lag_zero) cut(EXA_ZERO_TILE, z.first, z.second, std::max(tile_pts, kZeroTileEntries));
     return tiles;
+}
+
+// The tables of the units that finish sums (see EXA_DEVICE_STRUCTS).
+void fill_own(const Model& M, DeviceState& D, ExaInstDev& inst) {
+    if (!M.use_own) return;
+    auto source = [&](const OwnSrc& s) {
+        const Group& G = M.groups[s.group];
+        const Pattern& P0 = M.pats[G.members[0]];
+        ExaPatDev& d = inst.pat[G.members[0]];
+        const RefKey& k = G.vrefs[s.ref];
+        d.vd[s.ref] = k.off + (k.col >= 0 && s.how == OWN_AFFINE ? (int64_t)P0.icols[k.col][0] : 0);
+        if (s.how != OWN_INVERSE || d.inv[k.col]) return;
+        const std::vector<int32_t>& c = P0.icols[k.col];
+        std::vector<int32_t> inv((int64_t)c.back() - c.front() + 1, -1);
+        for (size_t q = 0; q < c.size(); ++q) inv[c[q] - c.front()] = (int32_t)q;
+        d.inv[k.col] = (const int*)D.upload(inv.data(), inv.size() * sizeof(int32_t));
+        d.icmin[k.col] = c.front();
+        d.icmax[k.col] = c.back();
+    };
+    for (int k = 0; k < SUM_COUNT; ++k)
+        for (const OwnUnit& U : M.own[k].units) {
+            if (U.vunit >= 0) {
+                inst.vlo[k][U.vunit] = U.lo;
+            } else {
+                ExaPatDev& d = inst.pat[M.groups[U.group].members[0]];
+                d.runl[k] = (int)U.runl;
+                d.nrun[k] = (int)U.nrun;
+            }
+            for (const std::vector<OwnSrc>* v : {&U.srcs, &U.grad})
+                for (const OwnSrc& x : *v) source(x);
+            for (const OwnChain& c : U.chains) {
+                OwnSrc top;
+                top.group = U.group;
+                top.ref = c.top;
+                source(top);
+                for (const std::vector<OwnSrc>* v : {&c.before, &c.after, &c.grad})
+                    for (const OwnSrc& x : *v) source(x);
+            }
+        }
 }
 
 void fill_patdev(const Model& M, DeviceState& D, ExaInstDev& inst) {
@@ -276,11 +334,11 @@ void fill_patdev(const Model& M, DeviceState& D, ExaInstDev& inst) {
     for (size_t p = 0; p < M.pats.size(); ++p) {
         const Pattern& P = M.pats[p];
         ExaPatDev& d = inst.pat[p];
-        const int first = M.groups[P.group].members[0];
-        if (first != (int)p) {
+        const int lead = M.groups[P.group].members[0];
+        if (lead != (int)p) {
             // same data arrays as the group's first pattern: share the copies
-            for (int c = 0; c < P.n_icols; ++c) d.ic[c] = inst.pat[first].ic[c];
-            for (int c = 0; c < P.n_fcols; ++c) d.fc[c] = inst.pat[first].fc[c];
+            for (int c = 0; c < P.n_icols; ++c) d.ic[c] = inst.pat[lead].ic[c];
+            for (int c = 0; c < P.n_fcols; ++c) d.fc[c] = inst.pat[lead].fc[c];
         } else {
             for (int c = 0; c < P.n_icols; ++c)
                 d.ic[c] = (const int*)D.upload(P.icols[c].data(), P.ndata * sizeof(int32_t));
@@ -295,7 +353,10 @@ void fill_patdev(const Model& M, DeviceState& D, ExaInstDev& inst) {
         d.oh = P.oh;
         d.ob = P.ob;
         d.tgt0 = P.tgt0;
-        d.row_off = P.row_off;
+        // a column the code counts from the data point: its first value goes
+        // into the offsets of what it indexes
+        auto first = [&](int c) { return c >= 0 && P.ident[c] ? (int64_t)P.icols[c][0] : 0; };
+        d.row_off = P.row_off + (P.kind == EXA_AUG ? first(P.row_icol) : 0);
         d.row_ic = P.row_icol;
         const Group& G = M.groups[P.group];
         for (size_t j = 0; j < G.hv_direct.size(); ++j)
@@ -304,9 +365,10 @@ void fill_patdev(const Model& M, DeviceState& D, ExaInstDev& inst) {
             d.rptr = (const int*)D.upload(P.rptr.data(), P.rptr.size() * sizeof(int32_t));
             d.ridx = (const int*)D.upload(P.ridx.data(), P.ridx.size() * sizeof(int32_t));
         }
-        for (int r = 0; r < P.o1step(); ++r) d.roff[r] = P.vslots[r].off;
-        for (int r = 0; r < P.pstep(); ++r) d.roff[P.o1step() + r] = P.pslots[r].off;
+        for (int r = 0; r < P.o1step(); ++r) d.roff[r] = P.vslots[r].off + first(P.vslots[r].col);
+        for (int r = 0; r < P.pstep(); ++r) d.roff[P.o1step() + r] = P.pslots[r].off + first(P.pslots[r].col);
     }
+    fill_own(M, D, inst);
 }
 
 int64_t estimate_device_bytes(const Model& M) {
@@ -325,6 +387,10 @@ int64_t estimate_device_bytes(const Model& M) {
     }
     const int64_t nobj = (int64_t)make_tiles(M, M_OBJ, 0, (int64_t)kObjBlock * kObjEpl, kObjFused).size();
     b += 8 * (M.fo_obj_len + M.fo_con_len + M.par_len + M.hv_len + std::max<int64_t>(1, nobj) + M.nvar + 1);
+    // inverse tables of strictly increasing columns (at most one per column)
+    for (const Group& G : M.groups)
+        for (const std::vector<int32_t>& c : M.pats[G.members[0]].icols)
+            if (!c.empty() && c.back() > c.front()) b += 4 * ((int64_t)c.back() - c.front() + 1);
     // maps: pointers and positions, plus at most a 24-byte record per four
     // entries (chunked sums, with padding) and part sums
     for (const SegMap* S : {&M.grad_map, &M.jt_map, &M.h_map, &M.par_map}) {
@@ -380,9 +446,9 @@ void build_device(Model& M) {
     if (hipHostMalloc((void**)&D.fhost, sizeof(double), hipHostMallocDefault) != hipSuccess)
         fail(EXA_ENOMEM, "hipHostMalloc of the objective's host copy failed");
 
-    upload_map(D, M.grad_map, D.grad_map);
-    upload_map(D, M.jt_map, D.jt_map);
-    upload_map(D, M.h_map, D.h_map);
+    upload_map(D, M.grad_map, D.grad_map, M.own[SUM_GRAD].on);
+    upload_map(D, M.jt_map, D.jt_map, M.own[SUM_JT].on);
+    upload_map(D, M.h_map, D.h_map, M.own[SUM_HV].on);
     upload_map(D, M.par_map, D.par_map);
     // the caller's float columns are not kept past create
     for (auto& P : M.pats) P.fcols_src.assign(P.fcols_src.size(), nullptr);
@@ -416,8 +482,9 @@ int64_t visited_segments(const SegMap& S) {
     return n;
 }
 
-void upload_map(DeviceState& D, const SegMap& S, DevMap& d) {
+void upload_map(DeviceState& D, const SegMap& S, DevMap& d, bool own) {
     d.nseg = visited_segments(S);
+    if (d.nseg == 0) return;  // nothing to sum: no job
     int64_t top = S.idx.empty() ? 0 : *std::max_element(S.idx.begin(), S.idx.end());
     const int64_t low = S.idx.empty() ? 0 : *std::min_element(S.idx.begin(), S.idx.end());
     top = std::max<int64_t>(top, S.ptr.empty() ? 0 : S.ptr.back());
@@ -435,7 +502,7 @@ void upload_map(DeviceState& D, const SegMap& S, DevMap& d) {
     std::vector<int32_t> p32(ptr.begin(), ptr.end()), i32(S.idx.begin(), S.idx.end());
     d.ptr = D.upload(p32.data(), p32.size() * sizeof(int32_t));
     d.idx = D.upload(i32.data(), i32.size() * sizeof(int32_t));
-    const ChunkPlan P = chunk_plan(S);
+    const ChunkPlan P = chunk_plan(S, own);
     d.chunked = P.chunked ? 1 : 0;
     if (P.nlanes()) {
         d.lanes = (const int32_t*)D.upload(P.meta.data(), P.meta.size() * sizeof(int32_t));
@@ -446,8 +513,9 @@ void upload_map(DeviceState& D, const SegMap& S, DevMap& d) {
         d.longs = (const int32_t*)D.upload(P.longs.data(), P.longs.size() * sizeof(int32_t));
         d.lpart = (const int32_t*)D.upload(P.lpart.data(), P.lpart.size() * sizeof(int32_t));  // 2 per part
         d.nparts = P.nparts();
-        d.nlong = P.nlong();
-        d.lsum = (double*)D.alloc(P.nparts() * sizeof(double));
+        d.long_len = P.long_len;
+        d.nlong = P.nsplit ? P.nlong() : 0;
+        if (P.nsplit) d.lsum = (double*)D.alloc(P.nparts() * sizeof(double));
     }
 }
 
@@ -497,8 +565,12 @@ Model::Csc& csc_form(Model& M, int which) {
     return C;
 }
 
-ChunkPlan chunk_plan(const SegMap& S) {
+ChunkPlan chunk_plan(const SegMap& S, bool own) {
     ChunkPlan P;
+    // maps of what finishing units leave: a shared variable's partial sums are
+    // at most a few thousand entries, which one workgroup adds at once (no
+    // part sums, no second launch)
+    const int64_t long_seg = own ? kExaWholeSeg : kExaLongSeg;
     int64_t longest = 0, top = S.ptr.empty() ? 0 : S.ptr.back(), low = 0;
     for (int64_t s = 0; s < S.nseg(); ++s) longest = std::max(longest, S.ptr[s + 1] - S.ptr[s]);
     for (int64_t i : S.idx) top = std::max(top, i), low = std::min(low, i);
@@ -506,7 +578,7 @@ ChunkPlan chunk_plan(const SegMap& S) {
     int64_t longest_short = 0, long_nnz = 0;
     for (int64_t s = 0; s < S.nseg(); ++s) {
         const int64_t len = S.ptr[s + 1] - S.ptr[s];
-        if (len > kExaLongSeg)
+        if (len > long_seg)
             long_nnz += len;
         else
             longest_short = std::max(longest_short, len);
@@ -524,9 +596,12 @@ ChunkPlan chunk_plan(const SegMap& S) {
     int64_t nparts = 0, most = 0;
     for (int64_t s = 0; s < S.nseg(); ++s) {
         const int64_t b = S.ptr[s], len = S.ptr[s + 1] - b;
-        if (len > kExaLongSeg) {
-            const int64_t parts = (len + kExaLongSeg - 1) / kExaLongSeg;
-            P.longs.insert(P.longs.end(), {(int32_t)s, (int32_t)b, (int32_t)len, (int32_t)nparts, (int32_t)parts});
+        if (len > long_seg) {
+            P.long_len = (int32_t)long_seg;
+            const bool whole = own && len <= kExaWholeMax;
+            const int64_t parts = whole ? 1 : (len + kExaLongSeg - 1) / kExaLongSeg;
+            P.nsplit += whole ? 0 : 1;
+            P.longs.insert(P.longs.end(), {(int32_t)s, (int32_t)b, (int32_t)len, (int32_t)nparts, whole ? 0 : (int32_t)parts});
             nparts += parts;
             most = std::max(most, parts);
             continue;
@@ -551,7 +626,7 @@ ChunkPlan chunk_plan(const SegMap& S) {
     // XCD, instead of each XCD reading every line of it
     for (int64_t i = 0; i < most; ++i)
         for (int64_t ls = 0; ls < P.nlong(); ++ls)
-            if (i < P.longs[5 * ls + 4]) P.lpart.insert(P.lpart.end(), {(int32_t)ls, (int32_t)(P.longs[5 * ls + 3] + i)});
+            if (i < std::max(1, P.longs[5 * ls + 4])) P.lpart.insert(P.lpart.end(), {(int32_t)ls, (int32_t)(P.longs[5 * ls + 3] + i)});
     return P;
 }
 
@@ -712,8 +787,11 @@ void launch_mode_untuned(Model& M, int mode, ExaCall call, hipStream_t s) { raw_
 // JH units (both jobs of a point from one set of loads).
 std::vector<int> eval_modes(uint32_t mask, bool jh) {
     std::vector<int> m;
+    // EXA_EV_LAG beside GRAD and JTPROD: the units that finish the Lagrangian
+    // gradient, and the gradient's tiles of the other variables
+    const bool lag = (mask & EXA_EV_LAG) != 0;
     if (mask & EXA_EV_OBJ) m.push_back(M_OBJ);
-    if (mask & EXA_EV_GRAD) m.push_back(M_GRAD);
+    if (mask & EXA_EV_GRAD) m.push_back(lag ? M_GRADL : (int)M_GRAD);
     if (mask & EXA_EV_CONS) m.push_back(M_CONS);
     if (jh && (mask & EXA_EV_JAC) && (mask & EXA_EV_HESS))
         m.push_back(M_JH);
@@ -726,7 +804,7 @@ std::vector<int> eval_modes(uint32_t mask, bool jh) {
     else if (mask & EXA_EV_HESS)
         m.push_back(M_HESS);
     if (mask & EXA_EV_JPROD) m.push_back(M_JPROD);
-    if (mask & EXA_EV_JTPROD) m.push_back(M_JTPROD);
+    if (mask & EXA_EV_JTPROD) m.push_back(lag ? M_LAG : (int)M_JTPROD);
     if (mask & EXA_EV_HPROD) m.push_back(M_HPROD);
     return m;
 }
@@ -734,6 +812,7 @@ std::vector<int> eval_modes(uint32_t mask, bool jh) {
 // Multi-unit mode that covers a mask's callbacks besides the objective in
 // one pass per point, or -1.
 int combined_mode_of(uint32_t mask) {
+    if (mask & EXA_EV_LAG) return -1;
     const uint32_t full = EXA_EV_GRAD | EXA_EV_CONS | EXA_EV_JAC | EXA_EV_HESS | EXA_EV_JPROD | EXA_EV_HPROD;
     const uint32_t ipm = EXA_EV_GRAD | EXA_EV_CONS | EXA_EV_JAC | EXA_EV_HESS;
     // the objective and J^T w run as tiles of their own beside the units
@@ -754,13 +833,16 @@ int valid_units(uint32_t mask, int units) {
 }
 
 // Modes whose tiles make up a mask's launch.
-std::vector<int> launch_modes(uint32_t mask, int units) {
+std::vector<int> launch_modes(const Model& M, uint32_t mask, int units) {
     units = valid_units(mask, units);
     if (units != EXA_UNITS_ONE_PASS) return eval_modes(mask, units == EXA_UNITS_JAC_HESS);
     std::vector<int> m;
     if (mask & EXA_EV_OBJ) m.push_back(M_OBJ);
     m.push_back(combined_mode_of(mask));
     if (mask & EXA_EV_JTPROD) m.push_back(M_JTPROD);
+    // jobs the one-pass units leave to units that finish sums
+    if ((mask & EXA_EV_GRAD) && own_plan(M, M_GRAD, M.use_own)) m.push_back(M_GRAD);
+    if ((mask & EXA_EV_HPROD) && own_plan(M, M_HPROD, M.use_own)) m.push_back(M_HPROD);
     return m;
 }
 
@@ -776,10 +858,10 @@ void set_multi_schedule(Model& M, uint32_t mask, int block, int epl, bool fused,
     units = valid_units(mask, units);
     const int64_t tp = (int64_t)block * epl;
     std::vector<std::vector<ExaTile>> per;
-    for (int mode : launch_modes(mask, units)) {
+    for (int mode : launch_modes(M, mask, units)) {
         std::vector<ExaTile> t = mode == M_OBJ ? make_tiles(M, M_OBJ, 0, (int64_t)kObjBlock * kObjEpl, kObjFused)
                                                : make_tiles(M, mode, 0, tp, fused);
-        for (ExaTile& x : t) x.pat |= mode << EXA_MODE_SHIFT;
+        for (ExaTile& x : t) x.pat |= tile_mode(mode) << EXA_MODE_SHIFT;
         if (mode == M_GRAD || (multi_unit_mode(mode) && (mask & EXA_EV_GRAD))) {
             std::vector<ExaTile> z;
             add_zero_tiles(M, tp, z);
@@ -918,24 +1000,64 @@ void kernel_bytes(const Model& M, const std::vector<int>& modes, bool fused, int
     const std::map<std::pair<int, int>, UnitLive>& LV = live ? *live : M.live;
     rd = wr = 0;
     std::vector<char> xs(M.nvar, 0), vs(M.nvar, 0), ts(M.ntheta, 0);
-    for (int mode : modes)
-    // the objective always runs its fixed schedule
-    for (const Unit& u : units_for(M, mode, mode == M_OBJ ? kObjFused : fused)) {
+    struct Counted {
+        int mode, code, group;
+        int64_t n;
+    };
+    std::vector<Counted> units;
+    for (int mode : modes) {
+        const OwnPlan* plan = mode == M_GRADL ? nullptr : own_plan(M, mode, M.use_own);
+        if (plan) {
+            for (const OwnUnit& U : plan->units) units.push_back({mode, U.code, U.group, U.vunit >= 0 ? U.n : U.npts});
+            for (auto& z : plan->fill) wr += 8 * z.second;
+            // entries the pulled contributions read
+            for (const OwnUnit& U : plan->units) {
+                std::vector<OwnSrc> v = U.srcs;
+                for (const OwnChain& c : U.chains) {
+                    v.insert(v.end(), c.before.begin(), c.before.end());
+                    v.insert(v.end(), c.after.begin(), c.after.end());
+                }
+                for (const OwnSrc& s : v) {
+                    const Group& G = M.groups[s.group];
+                    if (s.wread >= 0) continue;
+                    for (const RefKey& r : G.vrefs)
+                        for (int64_t k = 0; k < G.ndata; ++k) {
+                            const int64_t i = r.col < 0 ? r.off : (int64_t)M.pats[G.members[0]].icols[r.col][k] + r.off;
+                            xs[i] = 1;
+                            if (mode == M_HPROD) vs[i] = 1;
+                        }
+                }
+            }
+            continue;
+        }
+        // the objective always runs its fixed schedule
+        for (const Unit& u : units_for(M, mode, mode == M_OBJ ? kObjFused : fused))
+            units.push_back({tile_mode(mode), u.code, u.group, u.ndata});
+        if (mode == M_GRADL)
+            for (auto& z : M.own[SUM_JT].lag_zero) wr += 8 * z.second;
+    }
+    for (const Counted& u : units) {
+        const int mode = u.mode;
         auto it = LV.find({mode, u.code});
         if (it == LV.end()) continue;
         const UnitLive& L = it->second;
+        if (u.group < 0) {
+            rd += u.n * L.extra;
+            wr += u.n * 8 * L.outputs;
+            continue;
+        }
         const Group& G = M.groups[u.group];
         const Pattern& P0 = M.pats[G.members[0]];
-        rd += u.ndata * (4 * (int64_t)L.icols.size() + 8 * (int64_t)L.fcols.size() + 8 * (int64_t)L.weights);
+        rd += u.n * (4 * (int64_t)L.icols.size() + 8 * (int64_t)L.fcols.size() + 8 * (int64_t)L.weights + L.extra);
         // the objective writes one partial sum per tile, not per data point
-        if (mode != M_OBJ) wr += u.ndata * 8 * L.outputs;
+        if (mode != M_OBJ) wr += u.n * 8 * L.outputs;
         auto mark = [&](const RefKey& r, std::vector<char>& seen) {
             if (r.col < 0) {
                 if (r.off >= 0 && r.off < (int64_t)seen.size()) seen[r.off] = 1;
                 return;
             }
             const std::vector<int32_t>& c = P0.icols[r.col];
-            for (int64_t k = 0; k < u.ndata; ++k) seen[(int64_t)c[k] + r.off] = 1;
+            for (int64_t k = 0; k < u.n; ++k) seen[(int64_t)c[k] + r.off] = 1;
         };
         for (int r : L.vrefs) mark(G.vrefs[r], xs);
         for (int r : L.vseeds) mark(G.vrefs[r], vs);
@@ -944,7 +1066,7 @@ void kernel_bytes(const Model& M, const std::vector<int>& modes, bool fused, int
     // augmentation terms pulled by their base rows (cons, jprod)
     std::vector<int> pulled;
     for (int m : modes)
-        for (int jm : job_modes(m)) pulled.push_back(jm);
+        for (int jm : job_modes(M, m)) pulled.push_back(jm);
     for (int mode : pulled) {
         if (mode != M_CONS && mode != M_JPROD) continue;
         for (size_t a = 0; a < M.pats.size(); ++a) {
@@ -980,12 +1102,13 @@ void kernel_bytes(const Model& M, const std::vector<int>& modes, bool fused, int
 // fits), buffer entries once, outputs once; objective partials when several.
 void reduce_bytes(const Model& M, uint32_t mask, int64_t& rr, int64_t& rw) {
     rr = rw = 0;
-    auto seg = [&](const SegMap& S) {
+    auto seg = [&](const SegMap& S, bool own) {
         const int64_t nseg = visited_segments(S), nnz = (int64_t)S.idx.size();
         const int64_t top = std::max<int64_t>(nnz, S.idx.empty() ? 0 : *std::max_element(S.idx.begin(), S.idx.end()));
         const int64_t low = S.idx.empty() ? 0 : *std::min_element(S.idx.begin(), S.idx.end());
         const int64_t w = top >= INT32_MAX || low < INT32_MIN ? 8 : 4;
-        const ChunkPlan P = chunk_plan(S);
+        if (nseg == 0) return;
+        const ChunkPlan P = chunk_plan(S, own);
         // chunked maps read a 24-byte record per lane (segment, count,
         // four positions) instead of segment pointers and positions, and
         // positions only for the entries of long segments; maps with
@@ -998,12 +1121,12 @@ void reduce_bytes(const Model& M, uint32_t mask, int64_t& rr, int64_t& rw) {
               16 * P.nparts() + 8 * nnz;
         // segments written by the evaluation kernel are not written here
         const int64_t nskip = (int64_t)std::count(S.skip.begin(), S.skip.begin() + (S.skip.empty() ? 0 : nseg), 1);
-        rw += 8 * (nseg - nskip) + 8 * P.nparts();
+        rw += 8 * (nseg - nskip) + (P.nsplit ? 8 * P.nparts() : 0);
     };
-    if ((mask & (EXA_EV_GRAD | EXA_EV_LAG)) && !M.grad_direct) seg(M.grad_map);
-    if (mask & (EXA_EV_JTPROD | EXA_EV_LAG)) seg(M.jt_map);
-    if (mask & EXA_EV_HPROD) seg(M.h_map);
-    if (mask & EXA_EV_ADJ) seg(M.par_map);
+    if ((mask & (EXA_EV_GRAD | EXA_EV_LAG)) && !M.grad_direct) seg(M.grad_map, M.use_own && M.own[SUM_GRAD].on);
+    if (mask & (EXA_EV_JTPROD | EXA_EV_LAG)) seg(M.jt_map, M.use_own && M.own[SUM_JT].on);
+    if (mask & EXA_EV_HPROD) seg(M.h_map, M.use_own && M.own[SUM_HV].on);
+    if (mask & EXA_EV_ADJ) seg(M.par_map, false);
     if (mask & EXA_EV_OBJ) {
         const int64_t nobj = (int64_t)make_tiles(M, M_OBJ, 0, (int64_t)kObjBlock * kObjEpl, kObjFused).size();
         if (nobj != 1) {
@@ -1029,6 +1152,7 @@ ExaSegJob seg_job(const DevMap& m, const double* buf, double* out, const double*
     J.nparts = m.nparts;
     J.nlong = m.nlong;
     J.lsum = m.lsum;
+    J.long_len = m.long_len;
     J.buf = buf;
     J.w = w;
     J.out = out;
@@ -1281,6 +1405,7 @@ exa_status exa_grad(exa_model* m, const double* x, double* g, exa_stream_t strea
             launch_mode(M, M_GRAD, c, s);
         } else {
             c.out0 = M.dev->fo;
+            c.out1 = g;
             launch_mode(M, M_GRAD, c, s);
             segsum(M.dev->grad_map, M.dev->fo, g, s);
         }
@@ -1379,6 +1504,7 @@ exa_status exa_jtprod(exa_model* m, const double* x, const double* w, double* Jt
         c.x = x;
         c.y = w;
         c.out0 = M.dev->fo;
+        c.out1 = Jtw;
         launch_mode(M, M_JTPROD, c, s);
         segsum(M.dev->jt_map, M.dev->fo, Jtw, s, w);
         M.counters[6]++;
@@ -1443,6 +1569,7 @@ void eval_body(Model& M, const exa_eval_args* a, hipStream_t s, bool lag = false
             case M_OBJ: c.out0 = nobj == 1 ? a->f : D.tilesum; break;
             case M_GRAD:
                 c.out0 = M.grad_direct ? a->g : D.fo;
+                c.out1 = a->g;
                 c.direct = M.grad_direct ? 1 : 0;
                 break;
             case M_CONS: c.out0 = a->c; break;
@@ -1464,7 +1591,9 @@ void eval_body(Model& M, const exa_eval_args* a, hipStream_t s, bool lag = false
                 break;
             case M_JTPROD:
                 c.y = a->w;
+                c.sigma = lag_sigma;
                 c.out0 = D.fo;
+                c.out1 = lag && M.lag_units ? a->g : a->jtw;
                 break;
             case M_HPROD:
                 c.y = a->y;
@@ -1522,25 +1651,27 @@ void eval_body(Model& M, const exa_eval_args* a, hipStream_t s, bool lag = false
         }
         return R;
     };
-    auto it = D.multi.find(mask);
+    // the Lagrangian gradient's launch has a schedule of its own when units
+    // finish it
+    const uint32_t key = mask | (lag && M.lag_units ? EXA_EV_LAG : 0u);
+    auto it = D.multi.find(key);
     if (it == D.multi.end() || !it->second.tuned) {
         // untuned: per-callback tiles (the kind the tuner picks on most
         // models; one-pass units hold many registers), patterns over the
         // same data in one lane
-        set_multi_schedule(M, mask, M.block, M.epl, true, EXA_UNITS_PER_CALLBACK);
+        set_multi_schedule(M, key, M.block, M.epl, true, EXA_UNITS_PER_CALLBACK);
         if (M.autotune)
-            tune_multi(M, mask, mc, s, [&]() {
-                raw_launch_multi(M, mask, mc, s);
+            tune_multi(M, key, mc, s, [&]() {
+                raw_launch_multi(M, key, mc, s);
                 hip_check(exa_launch_reduce(reduce_of(), s), "exa_eval reductions");
             });
-        D.multi[mask].tuned = true;
+        D.multi[key].tuned = true;
     }
-    const DeviceState::MultiSched& S = D.multi.at(mask);
     DeviceState::EvalTiming& Tm = D.timing;
     const bool timed = Tm.on && Tm.used < (int64_t)Tm.reduced.size();
     hipEvent_t* ev = timed ? &Tm.ev[4 * Tm.used] : nullptr;
     if (timed) hip_check(hipEventRecord(ev[0], s), "hipEventRecord");
-    raw_launch_multi(M, mask, mc, s);
+    raw_launch_multi(M, key, mc, s);
     if (timed) hip_check(hipEventRecord(ev[1], s), "hipEventRecord");
     const ExaReduce R = reduce_of();
     const bool reduce = R.njobs > 0 || R.part;
@@ -1686,7 +1817,7 @@ exa_status exa_eval_bytes(const exa_model* m, uint32_t mask, int64_t* out4) {
             }
         }
         int64_t rd = 0, wr = 0;
-        kernel_bytes(M, launch_modes(mask, valid_units(mask, units)), fused, rd, wr);
+        kernel_bytes(M, launch_modes(M, mask, valid_units(mask, units)), fused, rd, wr);
         out4[0] = rd;
         out4[1] = wr;
         int64_t rr = 0, rw = 0;
@@ -1714,6 +1845,11 @@ exa_status exa_eval_set_schedule(exa_model* m, uint32_t mask, int32_t block, int
         set_multi_schedule(M, mask, block, epl, fused != 0, units);
         M.dev->multi[mask].unstaged = unstaged;
         M.dev->multi[mask].tuned = true;
+        // the Lagrangian gradient evaluates the same two callbacks
+        if (M.lag_units && mask == (EXA_EV_GRAD | EXA_EV_JTPROD)) {
+            set_multi_schedule(M, mask | EXA_EV_LAG, block, epl, fused != 0, units);
+            M.dev->multi[mask | EXA_EV_LAG].tuned = true;
+        }
     });
 }
 
@@ -1722,6 +1858,7 @@ exa_status exa_eval_schedule(const exa_model* m, uint32_t mask, int64_t* out4) {
         if (!m || !out4) fail(EXA_EINVAL, "null argument");
         if (!m->impl.dev) fail(EXA_ESTATE, "host-only model has no schedule");
         auto it = m->impl.dev->multi.find(mask);
+        if (it == m->impl.dev->multi.end()) it = m->impl.dev->multi.find(mask | EXA_EV_LAG);
         if (it == m->impl.dev->multi.end()) fail(EXA_ESTATE, "no exa_eval call with this mask yet");
         out4[0] = it->second.block;
         out4[1] = it->second.epl;

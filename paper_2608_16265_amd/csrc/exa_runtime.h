@@ -36,6 +36,7 @@ struct DevMap {
     const int32_t* longs = nullptr;
     const int32_t* lpart = nullptr;
     int64_t nparts = 0, nlong = 0;
+    int32_t long_len = 0;
     double* lsum = nullptr;
 };
 
@@ -117,7 +118,9 @@ std::vector<int> eval_modes(uint32_t mask, bool jh);
 int combined_mode_of(uint32_t mask);
 bool has_jh(uint32_t mask);
 int valid_units(uint32_t mask, int units);
-std::vector<int> launch_modes(uint32_t mask, int units);
+std::vector<int> launch_modes(const Model& M, uint32_t mask, int units);
+// The mode in a tile's code: M_GRADL runs the gradient's units.
+inline int tile_mode(int mode) { return mode == M_GRADL ? (int)M_GRAD : mode; }
 // Algorithmic bytes of the reduction launch of a mask (maps, buffer entries,
 // outputs, objective partials when there are several).
 void reduce_bytes(const Model& M, uint32_t mask, int64_t& rd, int64_t& wr);
@@ -147,6 +150,8 @@ void set_schedule(Model& M, int mode, int block, int epl, bool fused);
 // all short (at most kExaShortSeg entries), where one lane per segment reads
 // fewer bytes than a 24-byte lane record per segment.
 struct ChunkPlan {
+    int32_t long_len = 0;  // segments longer than this have blocks of their own (0: none do)
+    int64_t nsplit = 0;    // long segments summed in parts (the others by one workgroup each)
     bool chunked = false;  // chunk lanes (else one lane per segment)
     std::vector<int32_t> meta, lidx;    // 2 and 4 per lane, a multiple of 256 lanes
     std::vector<int32_t> longs, lpart;  // 5 per long segment; 2 per part block
@@ -154,13 +159,13 @@ struct ChunkPlan {
     int64_t nlong() const { return (int64_t)longs.size() / 5; }
     int64_t nparts() const { return (int64_t)lpart.size() / 2; }
 };
-ChunkPlan chunk_plan(const SegMap& S);
+ChunkPlan chunk_plan(const SegMap& S, bool own = false);
 // live: the liveness records of the code that runs (default: the model's own)
 void kernel_bytes(const Model& M, const std::vector<int>& modes, bool fused, int64_t& rd, int64_t& wr,
                   const std::map<std::pair<int, int>, UnitLive>* live = nullptr);
 // Map and tables of a segment map on the device (int32 when positions fit,
 // chunked when segments are long).
-void upload_map(DeviceState& D, const SegMap& S, DevMap& d);
+void upload_map(DeviceState& D, const SegMap& S, DevMap& d, bool own = false);
 // CSC analysis of the Jacobian (which = 0) or Hessian (1) on first use.
 Model::Csc& csc_form(Model& M, int which);
 void jac_structure_host(const Model& M, int32_t* rows, int32_t* cols);
