@@ -267,10 +267,59 @@ void instance_tiles(const exa_batch& b, int i, const std::vector<int>& modes, bo
     }
 }
 
+// Tiles that read the inputs of instance i's tiles `mine`; returns the bytes.
+int64_t ahead_tiles(const exa_batch& b, int i, const std::vector<ExaTile>& mine, const std::vector<int>& modes, bool tagged,
+                 std::vector<ExaTile>& out) {
+    const Model& M = b.models[i]->impl;
+    const AheadRecs rec = ahead_recs(M, modes);
+    Ahead in;
+    for (size_t s = 0; s < mine.size();) {
+        size_t e = s;
+        while (e < mine.size() && mine[e].pat == mine[s].pat) ++e;
+        const int mode = tagged ? mine[s].pat >> EXA_MODE_SHIFT : modes[0];
+        if ((mine[s].pat & ((1 << EXA_MODE_SHIFT) - 1)) != EXA_AHEAD_TILE) ahead_unit(M, mode, &mine[s], e - s, rec, in);
+        s = e;
+    }
+    in.tiles(i, tagged, out);
+    return in.bytes();
+}
+
+int64_t instance_outputs(const exa_batch& b, int i, const std::vector<ExaTile>& mine, const std::vector<int>& modes,
+                         bool tagged) {
+    int64_t total = 0;
+    for (size_t s = 0; s < mine.size();) {
+        size_t e = s;
+        while (e < mine.size() && mine[e].pat == mine[s].pat) ++e;
+        total += tile_outputs(b.models[i]->impl, tagged ? mine[s].pat >> EXA_MODE_SHIFT : modes[0], &mine[s], e - s);
+        s = e;
+    }
+    return total;
+}
+
 // Bin j's tiles, then bin j+1's, each bin padded with no-op tiles to the
 // longest, so that XCD j (workgroups w with w % 8 == j) takes exactly bin j.
-ExaTile* upload_binned(exa_batch& b, const exa_batch::Sched& S, const std::vector<std::vector<ExaTile>>& per,
-                       int64_t& n) {
+// In a launch that reads ahead (reads_ahead), each instance's inputs are read
+// (EXA_AHEAD_TILE) while the instance before it in the bin runs.
+ExaTile* upload_binned(exa_batch& b, const exa_batch::Sched& S, std::vector<std::vector<ExaTile>>& per,
+                       const std::vector<int>& modes, bool tagged, int64_t& n) {
+    std::vector<std::vector<ExaTile>> ahead_of(b.B);
+    int64_t in = 0, written = 0;
+    for (int i = 0; i < b.B; ++i) written += instance_outputs(b, i, per[i], modes, tagged);
+    if (!tagged && !mode_reads_ahead(modes[0])) written = 0;
+    if (reads_ahead(0, written))
+        for (int i = 0; i < b.B; ++i) in += ahead_tiles(b, i, per[i], modes, tagged, ahead_of[i]);
+    for (const auto& bin : S.bins) {
+        int prev = -1;
+        if (!reads_ahead(in, written)) break;
+        for (int i : bin) {
+            if (per[i].empty()) continue;
+            if (prev >= 0) {
+                const std::vector<ExaTile>& ahead = ahead_of[i];
+                per[prev].insert(per[prev].begin(), ahead.begin(), ahead.end());
+            }
+            prev = i;
+        }
+    }
     int64_t longest = 0;
     for (const auto& bin : S.bins) {
         int64_t c = 0;
@@ -316,16 +365,16 @@ void set_batch_schedule(exa_batch& b, uint32_t mask, int block, int epl, bool fu
                 for (auto& v : per) v.clear();
                 for (int i : inst) instance_tiles(b, i, {mode}, false, em, tp, fused, per[i]);
                 exa_batch::Sched::Part part{mode, nullptr, 0};
-                part.tiles = upload_binned(b, S, per, part.ntiles);
+                part.tiles = upload_binned(b, S, per, {mode}, false, part.ntiles);
                 Lc.parts.push_back(part);
             }
         } else if (!modes.empty()) {
             for (int i : inst) instance_tiles(b, i, modes, !single_kernel(modes), em, tp, fused, per[i]);
-            Lc.tiles = upload_binned(b, S, per, Lc.ntiles);
+            Lc.tiles = upload_binned(b, S, per, modes, !single_kernel(modes), Lc.ntiles);
         }
         if (mask & EXA_EV_ADJ) {
             for (int i : inst) instance_tiles(b, i, {M_ADJ}, false, 0, tp, fused, adj[i]);
-            Lc.atiles = upload_binned(b, S, adj, Lc.antiles);
+            Lc.atiles = upload_binned(b, S, adj, {M_ADJ}, false, Lc.antiles);
         }
     }
 }

@@ -1710,11 +1710,30 @@ __device__ __forceinline__ int exa_term(int j, int je) { return j < je ? j : (je
     static_assert(kObjBlock * kObjEpl % 256 == 0, "objective tiles hold whole rounds of 256 virtual lanes");
     os << "// rounds of EXA_VLANES points in one objective tile\n#define EXA_OBJ_ROUNDS " << kObjBlock * kObjEpl / 256
        << "\n";
+    os << R"(
+// Reads a tile's input range into this XCD's L2, one dword per 128-byte line:
+// 256 lanes cover 32 KB with one load each.
+__device__ __forceinline__ void exa_ahead(const ExaCall& C, const ExaInstDev& I, const ExaTile& T) {
+    const char* p = T.slot == )" << EXA_AHEAD_X << " ? (const char*)(C.x + I.off[" << EXA_OFF_X << "] + T.start) : T.slot == "
+       << EXA_AHEAD_Y << " ? (const char*)(C.y + I.off[" << EXA_OFF_Y << "] + T.start) : T.slot == " << EXA_AHEAD_V
+       << " ? (const char*)(C.v + I.off[" << EXA_OFF_X << R"(] + T.start) : (const char*)T.slot + T.start;
+    const long long last = T.count - 4;
+    int acc = 0;
+    for (long long o = 128ll * threadIdx.x; o < T.count; o += 8 * 128ll * blockDim.x) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const long long q = o + u * 128ll * blockDim.x;
+            acc ^= *(const int*)(p + (q < last ? q : last));
+        }
+    }
+    asm volatile("" ::"v"(acc));
+}
+)";
     int ntmp = 0;
     // Tile loop shared by every kernel: one tile per workgroup; workgroup w
     // runs on XCD w % 8, so tile indices are remapped to give each XCD a
     // contiguous range.
-    auto kernel = [&](const std::string& name, int lds, const std::vector<std::string>& cases) {
+    auto kernel = [&](const std::string& name, int lds, const std::vector<std::string>& cases, bool ahead) {
         os << "extern \"C\" __global__ void __launch_bounds__(" << EXA_BLOCK_MAX << ") " << name << "(ExaCall C) {\n";
         os << "    __shared__ double lds[" << lds << "];\n";
         os << "    (void)lds;\n";
@@ -1725,6 +1744,7 @@ __device__ __forceinline__ int exa_term(int j, int je) { return j < je ? j : (je
         os << "        const ExaInstDev& I = C.inst[T.inst];\n";
         os << "        switch (T.pat) {\n";
         for (auto& c : cases) os << "            " << c << "\n";
+        if (ahead) os << "            case " << EXA_AHEAD_TILE << ": exa_ahead(C, I, T); break;\n";
         os << "            default: break;\n";
         os << "        }\n";
         os << "    }\n";
@@ -1762,7 +1782,7 @@ __device__ __forceinline__ int exa_term(int j, int je) { return j < je ? j : (je
         if (mode == M_GRAD)  // entries of g no objective term touches
             cases.push_back("case " + std::to_string(EXA_ZERO_TILE) + ": exa_fill((C.direct ? C.out0 : C.out1) + I.off[" +
                             std::to_string(EXA_OFF_X) + "] + T.start, T.count, 0.0); break;");
-        kernel(kernel_name(mode), mode_lds_doubles(M, mode), cases);
+        kernel(kernel_name(mode), mode_lds_doubles(M, mode), cases, mode_reads_ahead(mode));
     }
     // Several callbacks in one launch: a tile's mode sits above
     // EXA_MODE_SHIFT in its code, and its case passes that mode's call (a
@@ -1783,6 +1803,9 @@ __device__ __forceinline__ int exa_term(int j, int je) { return j < je ? j : (je
         os << "    const ExaTile T = C.tiles[w];\n";
         os << "    switch (T.pat) {\n";
         for (auto& c : cases) os << "        " << c << "\n";
+        for (int m = 0; m < M_COUNT; ++m)
+            os << "        case " << ((m << EXA_MODE_SHIFT) | EXA_AHEAD_TILE) << ": exa_ahead(C.c[" << m << "], C.c[" << m
+               << "].inst[T.inst], T); break;\n";
         os << "        default: break;\n";
         os << "    }\n";
         os << "}\n";

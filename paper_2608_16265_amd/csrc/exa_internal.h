@@ -52,6 +52,13 @@ void set_last_error(const std::string& msg);
 #define EXA_OWN_VCODE 256
 #define EXA_MAX_VUNITS 32
 #define EXA_PAD_TILE 4095  // a tile that matches no unit: does nothing
+// A tile that only reads T.count bytes of input ahead of the tiles that need
+// them: from entry T.start of x, y (the weights) or v of its mode's call
+// record (T.slot = EXA_AHEAD_*), or from the device address T.slot.
+#define EXA_AHEAD_TILE 4094
+#define EXA_AHEAD_X 0
+#define EXA_AHEAD_Y 1
+#define EXA_AHEAD_V 2
 
 // ExaPatDev::hvd: bit r set when the pattern's group stores H v reference r
 // straight into the output (Group::hv_direct, for this instance's data).
@@ -252,6 +259,8 @@ struct Group {
     std::vector<RefKey> vrefs, prefs;  // distinct references over all members
     std::vector<std::pair<int, int>> vsrc, psrc;  // first (member, slot) of each
     int64_t ndata = 0;
+    std::vector<char> inc;  // index columns that increase strictly (plan_sums)
+    std::vector<std::pair<int32_t, int32_t>> range;  // least and greatest value of each index column
     // J^T w and H v contributions are summed over the members of a point
     // before they leave the lane: one buffer slot per group-level reference
     // that some member contributes to (ascending reference index), blocks at
@@ -432,6 +441,10 @@ const std::vector<int>& job_modes(const Model& M, int mode);
 const std::vector<int>& job_modes(int mode);
 #define EXA_BLOCK_MAX 256
 bool pattern_in_mode(const Pattern& P, int mode);
+// Single-callback launches whose stores can outweigh their reads; only their
+// kernels hold code for read-ahead tiles (in the others it costs registers:
+// the constraints' kernel of the network model took 102 instead of 74).
+inline bool mode_reads_ahead(int mode) { return mode == M_JAC || mode == M_HESS || mode == M_JH; }
 // Modes the several-callback kernels evaluate: exa_k_multi (Jacobian and
 // Hessian apart) or exa_k_multijh (with Jacobian + Hessian units).
 const std::vector<int>& multi_modes(bool jh);

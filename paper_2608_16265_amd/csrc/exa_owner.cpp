@@ -501,6 +501,13 @@ void plan_sums(Model& M) {
             period[g].push_back(inc[g].back() ? 0 : period_of(P0.icols[c]));
         }
     }
+    for (size_t g = 0; g < M.groups.size(); ++g) {
+        M.groups[g].inc = inc[g];
+        for (const auto& c : M.pats[M.groups[g].members[0]].icols) {
+            auto mm = std::minmax_element(c.begin(), c.end());
+            M.groups[g].range.emplace_back(c.empty() ? 0 : *mm.first, c.empty() ? 0 : *mm.second);
+        }
+    }
     for (int s = 0; s < SUM_COUNT; ++s) plan_one(M, (SumKind)s, inc, period);
     M.lag_units = M.own[SUM_JT].on && M.grad_direct;
     std::ostringstream os;
