@@ -133,7 +133,8 @@ typedef struct exa_options {
                           memory, no kernel compilation; callbacks then return
                           EXA_ESTATE                                           */
     int32_t block;     /* threads per workgroup: 64, 128 or 256 (0: 256)      */
-    int32_t epl;       /* data points per lane per tile: 1..16 (0: 4)         */
+    int32_t epl;       /* data points per lane per tile: 1..16 (0: 4); fewer
+                          in launches of under 768 workgroups                 */
     int32_t autotune;  /* 1: at its first call, each callback times candidate
                           schedules (workgroup size, points per lane, fused or
                           separate patterns) and keeps the fastest; results do
@@ -534,7 +535,8 @@ typedef struct exa_batch_options {
                           schedules (workgroup size, points per lane, fused or
                           separate patterns, units) and keep the fastest      */
     int32_t block;     /* schedule without autotune: workgroup size (0: 256)   */
-    int32_t epl;       /*   points per lane 1..16 (0: 4)                       */
+    int32_t epl;       /*   points per lane 1..16 (0: 4; fewer in launches of
+                            under 768 workgroups)                             */
     int32_t fuse;      /*   1: patterns over the same data arrays share a lane */
     int32_t units;     /*   EXA_UNITS_* (a choice a mask does not allow falls
                             back to the next one down; EXA_UNITS_SEPARATE to

@@ -1060,7 +1060,20 @@ exa_status exa_batch_eval(exa_batch* b, uint32_t mask, const exa_batch_io* io, e
         auto it = b->sched.find(mask);
         if (it == b->sched.end() || !it->second.tuned) {
             // the options' units
-            set_batch_schedule(*b, mask, b->block, b->epl, b->fuse, b->units & ~EXA_UNSTAGED);
+            const int epl = untimed_epl(b->epl, [&](int e) {
+                int64_t n = 0;
+                for (size_t c = 0; c < b->classes.size(); ++c) {
+                    const Model& M = lead_of(*b, (int)c);
+                    const uint32_t em = eval_mask(M, mask);
+                    std::vector<ExaTile> t;
+                    for (int i : b->classes[c].inst)
+                        instance_tiles(*b, i, modes_of(M, em, batch_units(em, b->units & ~EXA_UNSTAGED)), false, em,
+                                       (int64_t)b->block * e, b->fuse, t);
+                    n += (int64_t)t.size();
+                }
+                return n;
+            });
+            set_batch_schedule(*b, mask, b->block, epl, b->fuse, b->units & ~EXA_UNSTAGED);
             b->sched[mask].unstaged = (b->units & EXA_UNSTAGED) != 0;
             b->sched[mask].reduce_built = false;
             if (b->autotune) tune_batch(*b, mask, *io, s);

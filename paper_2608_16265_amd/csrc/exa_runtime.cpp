@@ -371,6 +371,11 @@ void fill_patdev(const Model& M, DeviceState& D, ExaInstDev& inst) {
     fill_own(M, D, inst);
 }
 
+// Points per lane of callback `mode` under the model's options.
+int option_epl(const Model& M, int mode) {
+    return untimed_epl(M.epl, [&](int e) { return (int64_t)make_tiles(M, mode, 0, (int64_t)M.block * e, M.fuse).size(); });
+}
+
 int64_t estimate_device_bytes(const Model& M) {
     int64_t b = 0;
     for (const Group& G : M.groups) {
@@ -382,7 +387,7 @@ int64_t estimate_device_bytes(const Model& M) {
     b += 8 * M.ntheta + (int64_t)sizeof(ExaInstDev);
     for (int mode = 0; mode < M_COUNT; ++mode) {
         const bool fixed = mode == M_OBJ;
-        const int64_t tp = fixed ? (int64_t)kObjBlock * kObjEpl : (int64_t)M.block * M.epl;
+        const int64_t tp = fixed ? (int64_t)kObjBlock * kObjEpl : (int64_t)M.block * option_epl(M, mode);
         b += (int64_t)sizeof(ExaTile) * (int64_t)make_tiles(M, mode, 0, tp, fixed ? kObjFused : M.fuse).size();
     }
     const int64_t nobj = (int64_t)make_tiles(M, M_OBJ, 0, (int64_t)kObjBlock * kObjEpl, kObjFused).size();
@@ -434,7 +439,8 @@ void build_device(Model& M) {
         // the objective keeps one fixed schedule, so that its reduction order
         // (and hence its value) never depends on tuning
         const bool fixed = mode == M_OBJ;
-        set_schedule(M, mode, fixed ? kObjBlock : M.block, fixed ? kObjEpl : M.epl, fixed ? kObjFused : M.fuse);
+        set_schedule(M, mode, fixed ? kObjBlock : M.block, fixed ? kObjEpl : option_epl(M, mode),
+                     fixed ? kObjFused : M.fuse);
         D.sched[mode].tuned = fixed || !M.autotune;
     }
     D.fo = (double*)D.alloc((M.fo_obj_len + M.fo_con_len) * sizeof(double));
@@ -1853,7 +1859,13 @@ void eval_body(Model& M, const exa_eval_args* a, hipStream_t s, bool lag = false
         // untuned: per-callback tiles (the kind the tuner picks on most
         // models; one-pass units hold many registers), patterns over the
         // same data in one lane
-        set_multi_schedule(M, key, M.block, M.epl, true, EXA_UNITS_PER_CALLBACK);
+        const int epl = untimed_epl(M.epl, [&](int e) {
+            int64_t n = 0;
+            for (int mode : launch_modes(M, key, EXA_UNITS_PER_CALLBACK))
+                if (mode != M_OBJ) n += (int64_t)make_tiles(M, mode, 0, (int64_t)M.block * e, true).size();
+            return n;
+        });
+        set_multi_schedule(M, key, M.block, epl, true, EXA_UNITS_PER_CALLBACK);
         if (M.autotune)
             tune_multi(M, key, mc, s, [&]() {
                 raw_launch_multi(M, key, mc, s);
