@@ -238,7 +238,11 @@ void make_bins(exa_batch& b, exa_batch::Sched& S, uint32_t mask) {
         S.bins[j].push_back(i);
         load[j] += cost[i];
     }
-    for (auto& bin : S.bins) std::sort(bin.begin(), bin.end());
+    // the smallest first: its inputs are the ones no instance before it lets
+    // the launch read ahead (64 networks of 500 to 20,000 buses, every callback
+    // with inputs from HBM: 198 us in order, 182 smallest first)
+    for (auto& bin : S.bins)
+        std::stable_sort(bin.begin(), bin.end(), [&](int a, int c) { return cost[a] != cost[c] ? cost[a] < cost[c] : a < c; });
 }
 
 // Tiles of instance i for one launch of `modes` (mode bits in the codes when
