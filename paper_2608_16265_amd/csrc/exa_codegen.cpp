@@ -1276,6 +1276,99 @@ std::string own_vunit(const Model& M, int mode, const OwnUnit& U, int sum, UnitL
     return os.str();
 }
 
+// A unit over variables that pulls a data set's contributions through
+// incidence lists: a lane per list entry evaluates its point's members and
+// leaves the entry's contribution (one per output) in LDS, a lane per variable
+// adds its entries from there, in the lists' order.
+// This takes the place of one work-buffer entry per point and reference and
+// of the reduction launch that added them: the trigonometry of a branch is
+// done twice (once for each end), against 24 bytes written, read back and
+// indexed per reference and a launch that could only start when all was
+// written.  A lane per entry, not per variable: lists are uneven, and a wave
+// would wait for its longest.  Before / after: every callback of 118 buses
+// 9.8 / 6.4 us, of 10,000 buses 14.4 / 10.0; J v, J^T w and H v of 78,484
+// buses 44.0 / 34.7.  Bound by the chain entry, columns, x and by the trigonometry.
+std::string own_lunit(const Model& M, int mode, const OwnUnit& U, int sum, int& ntmp, UnitLive& live) {
+    const Group& G = M.groups[U.lgroup];
+    const int m0 = G.members[0], jm = mode == M_LAG ? M_JTPROD : mode;
+    std::set<int> need;
+    for (const OwnUnit::Out& o : U.outs) need.insert(o.refs.begin(), o.refs.end());
+    std::vector<int> members;
+    for (int p : G.members) {
+        if (!adds_to(M.pats[p], jm)) continue;
+        const std::vector<char> f = slots_to(M.pats[p], jm, need);
+        if (std::find(f.begin(), f.end(), 1) != f.end()) members.push_back(p);
+    }
+    std::ostringstream os;
+    os << "__device__ __forceinline__ void own_" << mode_name(mode) << "_" << U.code
+       << "(const ExaCall& C, const ExaInstDev& I, const ExaTile& T, double* lds) {\n";
+    os << own_prologue(M, members, m0);
+    os << "    double* __restrict__ OUT = C.out1 + I.off[" << EXA_OFF_X << "];\n";
+    os << "    const int ne = (int)(T.slot >> 40), nv = (int)T.count, nthr = (int)blockDim.x, t = (int)threadIdx.x;\n";
+    os << "    const int e0 = (int)(T.slot & ((1LL << 40) - 1));\n";
+    os << "    const int* __restrict__ LE = I.lent[" << sum << "][" << U.lunit << "] + e0;\n";
+    os << "    const int* __restrict__ LP = I.lptr[" << sum << "][" << U.lunit << "] + T.start;\n";
+    os << "    int pa = LP[t < nv ? t : nv], pb = LP[t < nv ? t + 1 : nv];\n";
+    os << "    for (int q0 = 0; q0 < ne; q0 += nthr) {\n";
+    os << "        const int q = q0 + t;\n";
+    os << "        const int en = LE[q < ne ? q : ne - 1];\n";
+    os << "        const long long k = en >> 2;\n";
+    os << "        const int sl = en & 3;\n        (void)sl;\n";
+    for (int r : need) os << "        double g" << r << " = 0.0;\n";
+    for (int p : members) os << "        double o" << p << "[" << std::max(1, out_step(M.pats[p], jm)) << "] = {};\n";
+    Em e(ntmp);
+    const Loads L = record_loads(M, G, members, true, jm == M_HPROD, e);
+    for (int p : members) {
+        const Pattern& P = M.pats[p];
+        Names nm = input_names(P);
+        nm.wgt = record_weight(e, P, p, jm == M_JTPROD, "C.sigma");
+        const std::vector<char> want = slots_to(P, jm, need);
+        PatternCg cg(P, jm, e, nm);
+        cg.body("o" + std::to_string(p), &want);
+        for (size_t i = 0; i < want.size(); ++i) {
+            if (!want[i]) continue;
+            const std::string g = "g" + std::to_string(P.vg[jm == M_HPROD ? P.hvs[i] : i]);
+            e.out(g, g + " + o" + std::to_string(p) + "[" + std::to_string(i) + "]");
+        }
+    }
+    const std::set<std::string> names = e.emit(os, "        ");
+    os << "        if (q < ne) {\n";
+    for (size_t o = 0; o < U.outs.size(); ++o) {
+        const std::vector<int>& refs = U.outs[o].refs;
+        os << "            lds[" << o * EXA_LIST_TILE << " + q] = ";
+        for (size_t j = 0; j + 1 < refs.size(); ++j) os << "sl == " << j << " ? g" << refs[j] << " : ";
+        os << "g" << refs.back() << ";\n";
+    }
+    os << "        }\n    }\n";
+    os << "    __syncthreads();\n";
+    os << "    for (int i = t; i < nv; i += nthr) {\n";
+    os << "        if (i != t) { pa = LP[i]; pb = LP[i + 1]; }\n";
+    for (size_t o = 0; o < U.outs.size(); ++o) {
+        const OwnUnit::Out& O = U.outs[o];
+        const std::string n = std::to_string(o), v = "v" + n, ind = "        ";
+        os << ind << "const long long " << v << " = I.vlo[" << sum << "][" << O.vunit << "] + T.start + i;\n";
+        emit_pulls(M, jm, O.before, v, "b" + n + "_", ind, os);
+        emit_pulls(M, jm, O.after, v, "c" + n + "_", ind, os);
+        if (mode == M_LAG) emit_pulls(M, jm, O.grad, v, "q" + n + "_", ind, os);
+        os << ind << "double a" << n << " = 0.0;\n";
+        emit_adds(O.before.size(), "a" + n, "b" + n + "_", ind, os);
+    }
+    os << "        for (int q = pa - e0; q < pb - e0; ++q) {\n";
+    for (size_t o = 0; o < U.outs.size(); ++o)
+        os << "            a" << o << " += lds[" << o * EXA_LIST_TILE << " + q];\n";
+    os << "        }\n";
+    for (size_t o = 0; o < U.outs.size(); ++o) {
+        const OwnUnit::Out& O = U.outs[o];
+        const std::string n = std::to_string(o), ind = "        ";
+        emit_adds(O.after.size(), "a" + n, "c" + n + "_", ind, os);
+        emit_result(mode, O.grad.size(), "a" + n, "q" + n + "_", ind, "OUT[v" + n + "]", "", os);
+    }
+    os << "    }\n}\n";
+    record_live(M, members, L, names, live);
+    live.outputs += (int64_t)U.outs.size();
+    return os.str();
+}
+
 // A host unit: one data set's members in the lane of a point, in chunks of 64
 // lanes whose first W = 64 - S own a point each (the last S repeat the next
 // chunk's first points), a wave per run of chunks.  Contributions of
@@ -1446,7 +1539,12 @@ std::string own_units(const Model& M, int mode, int& ntmp, std::map<std::pair<in
             need(c.after, L);
             if (mode == M_LAG) need(c.grad, L);
         }
-        os << (U.vunit >= 0 ? own_vunit(M, mode, U, sum, L) : own_hunit(M, mode, U, sum, ntmp, L));
+        for (const OwnUnit::Out& o : U.outs) {
+            need(o.before, L);
+            need(o.after, L);
+            if (mode == M_LAG) need(o.grad, L);
+        }
+        os << (U.lgroup >= 0 ? own_lunit(M, mode, U, sum, ntmp, L) : U.vunit >= 0 ? own_vunit(M, mode, U, sum, L) : own_hunit(M, mode, U, sum, ntmp, L));
         if (live) (*live)[{mode, U.code}] = L;
     }
     return os.str();
@@ -1560,7 +1658,10 @@ int mode_lds_doubles(const Model& M, int mode) {
     if (!buffer_mode(mode))
         for (auto& P : M.pats)
             if (pattern_in_mode(P, mode) && staged(P, mode)) st = std::max(st, out_step(P, mode));
-    return st * EXA_BLOCK_MAX;
+    int d = st * EXA_BLOCK_MAX;
+    if (mode == M_JTPROD || mode == M_HPROD)
+        for (const OwnUnit& U : M.own[sum_of(mode)].units) d = std::max(d, (int)U.outs.size() * EXA_LIST_TILE);
+    return d;
 }
 
 std::string kernel_name(int mode) { return std::string("exa_k_") + mode_name(mode); }

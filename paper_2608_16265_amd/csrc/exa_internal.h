@@ -51,6 +51,10 @@ void set_last_error(const std::string& msg);
 #define EXA_OWN_CODE 128
 #define EXA_OWN_VCODE 256
 #define EXA_MAX_VUNITS 32
+// Units over variables that pull through incidence lists: at most this many
+// per sum, of at most EXA_LIST_TILE entries and variables per tile.
+#define EXA_MAX_LISTS 4
+#define EXA_LIST_TILE 256
 #define EXA_PAD_TILE 4095  // a tile that matches no unit: does nothing
 // A tile that only reads T.count bytes of input ahead of the tiles that need
 // them: from entry T.start of x, y (the weights) or v of its mode's call
@@ -69,7 +73,9 @@ void set_last_error(const std::string& msg);
 // maps column values icmin[c] .. icmax[c] to their data point or -1, runl[s]
 // and nrun[s] are the 64-lane chunks per run and the runs of the data set's
 // unit for sum s (SumKind).  ExaInstDev::vlo[s][j]: the first variable of the
-// j-th unit over variables of sum s.
+// j-th unit over variables of sum s.  ExaInstDev::lptr[s][j], lent[s][j] (J^T w
+// and H v): incidence lists of its j-th list unit, entries lptr[i] .. lptr[i+1]
+// of the unit's i-th variable, each a data point * 4 + the slot (OwnUnit::slots).
 #define EXA_DEVICE_STRUCTS                                                       \
     struct ExaPatDev {                                                           \
         const int* ic[8];                                                        \
@@ -100,6 +106,8 @@ void set_last_error(const std::string& msg);
         const double* theta;                                                     \
         long long pad1;                                                          \
         long long vlo[4][32];                                                    \
+        const int* lptr[2][4];                                                   \
+        const int* lent[2][4];                                                   \
         struct ExaPatDev pat[32];                                                \
     };                                                                           \
     struct ExaTile {                                                             \
@@ -326,12 +334,12 @@ struct SegMap {
 enum SumKind : int { SUM_JT = 0, SUM_HV = 1, SUM_GRAD = 2, SUM_COUNT = 3 };
 struct OwnSrc {
     int group = 0, ref = 0;  // data set and group reference
-    int how = 0;             // OWN_AFFINE or OWN_INVERSE
+    int how = 0;             // OWN_AFFINE, OWN_INVERSE or OWN_LIST
     int wread = -1;          // augmentation pattern whose +-w[row] this is
     int pat = -1;            // objective pattern (gradient contributions)
     bool sparse = false;     // hits under three quarters of the unit's variables: behind a branch
 };
-constexpr int OWN_AFFINE = 0, OWN_INVERSE = 1;
+constexpr int OWN_AFFINE = 0, OWN_INVERSE = 1, OWN_LIST = 2;
 constexpr int kOwnSpan = 8;  // largest lane shift of a chain
 struct OwnChain {
     int top = 0;                             // reference with the largest offset
@@ -350,6 +358,22 @@ struct OwnUnit {
     int vunit = -1;                  // units over variables: index j, and their pulled sources in order
     std::vector<OwnSrc> srcs, grad;
     int64_t lo = 0, n = 0;           // units over variables: this instance's range
+    // units over variables that pull data set lgroup's contributions through
+    // incidence lists: an entry is a point and one of up to four slots (an
+    // index column and an offset), its contribution to output o that of
+    // reference outs[o].refs[slot]; output o's variables are lo .. lo + n - 1
+    // of range vunit, its other sources before / after the data set's
+    int lgroup = -1, lunit = -1;
+    struct Out {
+        int vunit = 0;
+        int64_t lo = 0;
+        std::vector<int> refs;
+        std::vector<OwnSrc> before, after, grad;
+    };
+    std::vector<Out> outs;
+    std::vector<std::pair<int, int64_t>> slots;  // (column, offset from the range's first variable)
+    std::vector<int32_t> lptr, lent;             // this instance's lists
+    double spread = 0;  // 128-byte lines 256 entries touch, over those of 256 points in a row
     // host units: this instance's points, chunks per run and runs
     int64_t npts = 0;
     int64_t runl = 1, nrun = 0;

@@ -16,13 +16,28 @@ namespace {
 // (The grid model's J^T w pulls 5 references of a 21-node row: 5 x 21 = 105
 // nodes, of which the constant derivatives cost nothing once emitted.)
 constexpr int kPullNodes = 160, kHostPullNodes = 64;
+// A unit that pulls through incidence lists evaluates a point once per slot
+// (a branch once for each end); longest list (a lane adds it from LDS, and it
+// has to fit the smallest tile), and limit of the points' nodes.
+constexpr int kListLength = 64, kListNodes = 400, kListSlots = 4;
+// A list's points are gathered, line by line, where the data set's own unit
+// streams them and leaves one number per reference to gather.  That pays while
+// the points' data fits in an XCD's L2 beside the rest (kListBytes), or while
+// the lists follow the points' order: 256 entries in turn touch at most
+// kListSpread times the lines that 256 points in a row would.  Measured, map /
+// lists: networks of nodes linked at random J^T w 20,000 nodes and 30,000
+// links (1 MB) 7.8 / 5.2 us, H v 9.5 / 5.5; 100,000 and 150,000 (5 MB, spread
+// 16) 17.0 / 17.5 and 19 / 25; 500,000 and 700,000 75 / 146 and 125 / 194; a
+// ring of 78,484 buses with chords (spread 5) 18.2 / 13.4 and 16.7 / 12.6.
+constexpr int64_t kListBytes = (int64_t)2 << 20;
+constexpr int kListSpread = 8;
 // Lanes of a run's partial sums: at most this many runs per data set, so that
 // one workgroup can add a variable's partial sums.
 constexpr int64_t kMaxRuns = 4096;
 
 struct Src {
     OwnSrc s;
-    int kind = 0;         // 0 usable, 1 shared, 2 other (its variables stay in the map)
+    int kind = 0;         // 0 usable, 1 shared, 2 other (its variables stay in the map), 3 by incidence lists
     int64_t lo = 0, hi = 0;  // first and last variable
     int nodes = 0;
     bool grad = false;
@@ -93,7 +108,8 @@ Src make_src(const Model& M, int g, int r, SumKind s, const std::vector<std::vec
     } else if (inc[g][k.col]) {
         o.s.how = OWN_INVERSE;
     } else {
-        o.kind = period[g][k.col] ? 1 : 2;
+        o.kind = period[g][k.col] ? 1 : s == SUM_GRAD ? 2 : 3;
+        if (o.kind == 3) o.s.how = OWN_LIST;
     }
     if (G.ndata > 0) {
         if (k.col < 0) {
@@ -101,6 +117,9 @@ Src make_src(const Model& M, int g, int r, SumKind s, const std::vector<std::vec
         } else if (o.kind == 0) {
             o.lo = P0.icols[k.col].front() + k.off;
             o.hi = P0.icols[k.col].back() + k.off;
+        } else if (o.kind == 3) {
+            o.lo = G.range[k.col].first + k.off;
+            o.hi = G.range[k.col].second + k.off;
         }
     }
     return o;
@@ -210,8 +229,102 @@ std::vector<OwnChain> host_chains(const Model& M, const Cluster& C, int g, SumKi
     return out;
 }
 
+// The lists of U's slots over data set G (none when one is too long), and how
+// far they are from the points' order.
+void fill_lists(const Model& M, const Group& G, OwnUnit& U) {
+    auto at = [&](const std::pair<int, int64_t>& sl, int64_t k) {
+        return (sl.first < 0 ? 0 : (int64_t)col_of(M, G, sl.first)[k]) + sl.second;
+    };
+    U.lptr.assign(U.n + 1, 0);
+    for (int64_t k = 0; k < G.ndata; ++k)
+        for (auto& sl : U.slots) ++U.lptr[at(sl, k) + 1];
+    for (int64_t i = 0; i < U.n; ++i) {
+        if (U.lptr[i + 1] > kListLength) {
+            U.lptr.clear();
+            return;
+        }
+        U.lptr[i + 1] += U.lptr[i];
+    }
+    U.lent.assign(U.lptr[U.n] + 1, 0);
+    std::vector<int32_t> fill(U.lptr.begin(), U.lptr.end() - 1);
+    for (int64_t k = 0; k < G.ndata; ++k)
+        for (size_t j = 0; j < U.slots.size(); ++j) U.lent[fill[at(U.slots[j], k)]++] = (int32_t)(4 * k + j);
+    int64_t lines = 0;
+    const int64_t ne = U.lptr[U.n];
+    std::vector<int32_t> w;
+    for (int64_t e = 0; e < ne; e += 256) {
+        w.assign(U.lent.begin() + e, U.lent.begin() + std::min(ne, e + 256));
+        for (int32_t& x : w) x >>= 6;  // 16 points: 128 bytes of a column
+        std::sort(w.begin(), w.end());
+        lines += std::unique(w.begin(), w.end()) - w.begin();
+    }
+    U.spread = ne ? 16.0 * lines / ne : 0.0;
+}
+
+// The unit that pulls a cluster through incidence lists (of the one data set
+// with references in no order), or one without a data set.  Lists made before
+// (another sum's, another of the cluster's ranges) are taken from `made`.
+OwnUnit list_unit(const Model& M, const Cluster& C, SumKind s, std::vector<OwnUnit>& made) {
+    OwnUnit U;
+    int g = -1;
+    for (const Src& x : C.src)
+        if (x.kind == 3) {
+            if (g >= 0 && x.s.group != g) return U;
+            g = x.s.group;
+        }
+    const Group& G = M.groups[g];
+    std::vector<Src> mine, others;
+    for (const Src& x : C.src) (x.s.group == g ? mine : others).push_back(x);
+    const int64_t entries = (int64_t)mine.size() * G.ndata;
+    if (mine.size() > kListSlots || G.ndata >= (int64_t)1 << 29 || entries >= INT32_MAX) return U;
+    std::stable_sort(mine.begin(), mine.end(), [](const Src& a, const Src& b) { return a.s.ref < b.s.ref; });
+    std::vector<int> hit(M.pats.size(), 0);
+    OwnUnit::Out o;
+    o.lo = C.lo;
+    for (const Src& x : mine) {
+        if (x.s.wread >= 0) return U;
+        const RefKey& k = G.vrefs[x.s.ref];
+        U.slots.emplace_back(k.col, k.off - C.lo);
+        o.refs.push_back(x.s.ref);
+        for (int p : G.members)
+            if (in_sum(M.pats[p], s) && std::find(M.pats[p].vg.begin(), M.pats[p].vg.end(), x.s.ref) != M.pats[p].vg.end())
+                hit[p] = (int)M.pats[p].nodes.size();
+    }
+    int nodes = 0;
+    for (int n : hit) nodes += n;
+    if (nodes * (int)mine.size() > kListNodes || !order_known(M, others) || weight_nodes(M, others) > kPullNodes) return U;
+    U.lo = C.lo;
+    U.n = C.hi - C.lo + 1;
+    if (U.n > 8 * entries + 64) return U;  // mostly variables without entries
+    auto same = std::find_if(made.begin(), made.end(), [&](const OwnUnit& V) {
+        return V.lgroup == g && V.n == U.n && V.slots == U.slots;
+    });
+    if (same == made.end()) {
+        OwnUnit V;
+        V.lgroup = g;
+        V.n = U.n;
+        V.slots = U.slots;
+        fill_lists(M, G, V);
+        same = made.insert(made.end(), std::move(V));
+    }
+    if (same->lptr.empty()) return U;
+    int64_t bytes = 0;
+    for (size_t p = 0; p < hit.size(); ++p) bytes += hit[p] ? 8 * G.ndata : 0;
+    const Pattern& P0 = M.pats[G.members[0]];
+    bytes += G.ndata * (4 * P0.n_icols + 8 * P0.n_fcols);
+    if (bytes > kListBytes && same->spread > kListSpread) return U;
+    U.lptr = same->lptr;
+    U.lent = same->lent;
+    order_pulled(others, s);
+    for (const Src& x : others) (x.s.group < g ? o.before : o.after).push_back(within(x, C.lo, C.hi));
+    for (const Src& x : C.grad) o.grad.push_back(within(x, C.lo, C.hi));
+    U.outs.push_back(o);
+    U.lgroup = g;
+    return U;
+}
+
 void plan_one(Model& M, SumKind s, const std::vector<std::vector<char>>& inc,
-              const std::vector<std::vector<int>>& period) {
+              const std::vector<std::vector<int>>& period, std::vector<OwnUnit>& made) {
     OwnPlan& plan = M.own[s];
     plan = OwnPlan();
     if (s == SUM_GRAD && M.grad_direct) return;
@@ -246,7 +359,7 @@ void plan_one(Model& M, SumKind s, const std::vector<std::vector<char>>& inc,
             auto w = wr.find(r);
             if (w != wr.end()) {
                 x.s.wread = w->second;
-                if (x.kind == 1) x.kind = 2;
+                if (x.kind == 1 || x.kind == 3) x.kind = 2;
             }
             all.push_back(x);
         }
@@ -270,7 +383,7 @@ void plan_one(Model& M, SumKind s, const std::vector<std::vector<char>>& inc,
             }
         }
     // ---- variables of the sources that cannot be owned, and of any source
-    std::vector<char> poison(M.nvar + 1, 0), touched(M.nvar, 0);
+    std::vector<char> touched(M.nvar, 0);
     auto each_var = [&](const Src& x, auto&& f) {
         const Group& G = M.groups[x.s.group];
         const RefKey& k = G.vrefs[x.s.ref];
@@ -280,11 +393,6 @@ void plan_one(Model& M, SumKind s, const std::vector<std::vector<char>>& inc,
         }
         for (int32_t c : col_of(M, G, k.col)) f((int64_t)c + k.off);
     };
-    for (const std::vector<Src>* v : {&all, &grads})
-        for (const Src& x : *v) each_var(x, [&](int64_t i) {
-            touched[i] = 1;
-            if (x.kind) poison[i] = 1;
-        });
     std::vector<char> direct(M.nvar, 0);
     if (s == SUM_HV)
         for (const Group& G : M.groups)
@@ -294,61 +402,89 @@ void plan_one(Model& M, SumKind s, const std::vector<std::vector<char>>& inc,
                     for (int64_t q = 0; q < G.ndata; ++q)
                         direct[k.col < 0 ? k.off : (int64_t)M.pats[G.members[0]].icols[k.col][q] + k.off] = 1;
                 }
-    std::vector<int64_t> npoison(M.nvar + 1, 0), ntouched(M.nvar + 1, 0), ndirect(M.nvar + 1, 0);
-    for (int64_t v = 0; v < M.nvar; ++v) {
-        npoison[v + 1] = npoison[v] + poison[v];
-        ntouched[v + 1] = ntouched[v] + touched[v];
-        ndirect[v + 1] = ndirect[v] + direct[v];
-    }
-    // ---- clusters: unions of overlapping intervals
-    std::vector<Src> order;
-    for (const std::vector<Src>* v : {&all, &grads})
-        for (const Src& x : *v)
-            if (x.kind == 0) order.push_back(x);
-    std::stable_sort(order.begin(), order.end(), [](const Src& a, const Src& b) { return a.lo < b.lo; });
     std::vector<Cluster> cl;
-    for (const Src& x : order) {
-        if (cl.empty() || x.lo > cl.back().hi) {
-            cl.emplace_back();
-            cl.back().lo = x.lo;
-            cl.back().hi = x.hi;
+    std::vector<std::vector<OwnChain>> chains;
+    std::vector<int> host;
+    std::vector<OwnUnit> lists;
+    for (;;) {
+        std::vector<char> poison(M.nvar + 1, 0);
+        for (const std::vector<Src>* v : {&all, &grads})
+            for (const Src& x : *v) each_var(x, [&](int64_t i) {
+                touched[i] = 1;
+                if (x.kind == 1 || x.kind == 2) poison[i] = 1;
+            });
+        std::vector<int64_t> npoison(M.nvar + 1, 0), ntouched(M.nvar + 1, 0), ndirect(M.nvar + 1, 0);
+        for (int64_t v = 0; v < M.nvar; ++v) {
+            npoison[v + 1] = npoison[v] + poison[v];
+            ntouched[v + 1] = ntouched[v] + touched[v];
+            ndirect[v + 1] = ndirect[v] + direct[v];
         }
-        Cluster& c = cl.back();
-        c.hi = std::max(c.hi, x.hi);
-        (x.grad ? c.grad : c.src).push_back(x);
-    }
-    // H v variables stored by the kernel never lie inside a cluster
-    for (Cluster& c : cl)
-        c.ok = npoison[c.hi + 1] == npoison[c.lo] && (s != SUM_HV || ndirect[c.hi + 1] == ndirect[c.lo]);
-    // ---- units: a host where one can, else over the variables
-    std::vector<std::vector<OwnChain>> chains(cl.size());
-    std::vector<int> host(cl.size(), -1);
-    for (size_t i = 0; i < cl.size(); ++i) {
-        Cluster& c = cl[i];
-        if (!c.ok) continue;
-        if (weight_nodes(M, c.grad) > kHostPullNodes) {
-            c.ok = false;
-            continue;
+        // ---- clusters: unions of overlapping intervals
+        std::vector<Src> order;
+        for (const std::vector<Src>* v : {&all, &grads})
+            for (const Src& x : *v)
+                if (x.kind == 0 || x.kind == 3) order.push_back(x);
+        std::stable_sort(order.begin(), order.end(), [](const Src& a, const Src& b) { return a.lo < b.lo; });
+        cl.clear();
+        for (const Src& x : order) {
+            if (cl.empty() || x.lo > cl.back().hi) {
+                cl.emplace_back();
+                cl.back().lo = x.lo;
+                cl.back().hi = x.hi;
+            }
+            Cluster& c = cl.back();
+            c.hi = std::max(c.hi, x.hi);
+            (x.grad ? c.grad : c.src).push_back(x);
         }
-        std::vector<std::pair<int, int>> cand;  // (nodes, group)
-        for (const Src& x : c.src)
-            if (x.s.wread < 0 && x.s.how == OWN_AFFINE) {
-                int n = 0;
-                for (int p : M.groups[x.s.group].members)
-                    if (in_sum(M.pats[p], s)) n += (int)M.pats[p].nodes.size();
-                if (M.groups[x.s.group].ndata > 1) cand.emplace_back(-n, x.s.group);
+        // H v variables stored by the kernel never lie inside a cluster
+        for (Cluster& c : cl)
+            c.ok = npoison[c.hi + 1] == npoison[c.lo] && (s != SUM_HV || ndirect[c.hi + 1] == ndirect[c.lo]);
+        // ---- units: a host where one can, else over the variables
+        chains.assign(cl.size(), {});
+        host.assign(cl.size(), -1);
+        lists.assign(cl.size(), OwnUnit());
+        bool again = false;
+        for (size_t i = 0; i < cl.size(); ++i) {
+            Cluster& c = cl[i];
+            if (!c.ok) continue;
+            if (weight_nodes(M, c.grad) > kHostPullNodes) {
+                c.ok = false;
+                continue;
             }
-        std::sort(cand.begin(), cand.end());
-        for (auto& x : cand)
-            if (host[i] < 0) {
-                chains[i] = host_chains(M, c, x.second, s);
-                if (!chains[i].empty()) host[i] = x.second;
+            if (std::any_of(c.src.begin(), c.src.end(), [](const Src& x) { return x.kind == 3; })) {
+                lists[i] = list_unit(M, c, s, made);
+                c.ok = lists[i].lgroup >= 0;
+                continue;
             }
-        if (host[i] < 0 && (!order_known(M, c.src) || weight_nodes(M, c.src) > kPullNodes)) c.ok = false;
+            std::vector<std::pair<int, int>> cand;  // (nodes, group)
+            for (const Src& x : c.src)
+                if (x.s.wread < 0 && x.s.how == OWN_AFFINE) {
+                    int n = 0;
+                    for (int p : M.groups[x.s.group].members)
+                        if (in_sum(M.pats[p], s)) n += (int)M.pats[p].nodes.size();
+                    if (M.groups[x.s.group].ndata > 1) cand.emplace_back(-n, x.s.group);
+                }
+            std::sort(cand.begin(), cand.end());
+            for (auto& x : cand)
+                if (host[i] < 0) {
+                    chains[i] = host_chains(M, c, x.second, s);
+                    if (!chains[i].empty()) host[i] = x.second;
+                }
+            if (host[i] < 0 && (!order_known(M, c.src) || weight_nodes(M, c.src) > kPullNodes)) c.ok = false;
+        }
+        // references in no order that no unit can pull: their variables stay in the
+        // map, and those beside them are looked at again
+        for (const Cluster& c : cl)
+            for (const Src& x : c.src)
+                if (!c.ok && x.kind == 3)
+                    for (Src& y : all)
+                        if (y.s.group == x.s.group && y.s.ref == x.s.ref) y.kind = 2, again = true;
+        if (!again) break;
     }
-    int nv = 0;
+    int nv = 0, nl = 0;
     for (size_t i = 0; i < cl.size(); ++i)
-        if (cl[i].ok && host[i] < 0 && ++nv > EXA_MAX_VUNITS) cl[i].ok = false;
+        if (cl[i].ok && host[i] < 0 && (++nv > EXA_MAX_VUNITS || (lists[i].lgroup >= 0 && ++nl > EXA_MAX_LISTS)))
+            cl[i].ok = false;
     // the Lagrangian gradient: an objective pattern is owned whole or not at all
     for (bool again = with_grad; again;) {
         again = false;
@@ -443,7 +579,7 @@ void plan_one(Model& M, SumKind s, const std::vector<std::vector<char>>& inc,
     }
     int j = 0;
     for (size_t i = 0; i < cl.size(); ++i) {
-        if (!cl[i].ok || host[i] >= 0) continue;
+        if (!cl[i].ok || host[i] >= 0 || lists[i].lgroup >= 0) continue;
         OwnUnit U;
         U.vunit = j;
         U.code = EXA_OWN_VCODE + j++;
@@ -455,6 +591,25 @@ void plan_one(Model& M, SumKind s, const std::vector<std::vector<char>>& inc,
         for (const Src& x : cl[i].grad) U.grad.push_back(within(x, cl[i].lo, cl[i].hi));
         plan.units.push_back(U);
     }
+    // lists: clusters with the same ones share a unit (a bus's angle and magnitude)
+    std::vector<OwnUnit> with_lists;
+    for (size_t i = 0; i < cl.size(); ++i) {
+        if (!cl[i].ok || lists[i].lgroup < 0) continue;
+        OwnUnit& U = lists[i];
+        U.outs[0].vunit = j++;
+        auto same = std::find_if(with_lists.begin(), with_lists.end(), [&](const OwnUnit& V) {
+            return V.lgroup == U.lgroup && V.n == U.n && V.slots == U.slots && V.outs.size() < 2;
+        });
+        if (same != with_lists.end()) {
+            same->outs.push_back(U.outs[0]);
+            continue;
+        }
+        U.vunit = U.outs[0].vunit;
+        U.code = EXA_OWN_VCODE + U.vunit;
+        U.lunit = (int)with_lists.size();
+        with_lists.push_back(std::move(U));
+    }
+    plan.units.insert(plan.units.end(), with_lists.begin(), with_lists.end());
     plan.on = any;
     if (!any) {
         plan = OwnPlan();
@@ -508,7 +663,8 @@ void plan_sums(Model& M) {
             M.groups[g].range.emplace_back(c.empty() ? 0 : *mm.first, c.empty() ? 0 : *mm.second);
         }
     }
-    for (int s = 0; s < SUM_COUNT; ++s) plan_one(M, (SumKind)s, inc, period);
+    std::vector<OwnUnit> made;
+    for (int s = 0; s < SUM_COUNT; ++s) plan_one(M, (SumKind)s, inc, period, made);
     M.lag_units = M.own[SUM_JT].on && M.grad_direct;
     std::ostringstream os;
     for (int s = 0; s < SUM_COUNT; ++s) {
@@ -532,6 +688,20 @@ void plan_sums(Model& M) {
             for (auto& r : U.shared) os << r.first << "/" << r.second << ",";
             os << "d";
             for (int r : U.direct) os << r << ",";
+            if (U.lgroup >= 0) {
+                os << "l" << U.lgroup << "." << U.lunit << ":";
+                for (auto& x : U.slots) os << x.first << ",";
+            }
+            for (const OwnUnit::Out& o : U.outs) {
+                os << "o" << o.vunit << ":";
+                for (int r : o.refs) os << r << ",";
+                os << "b";
+                for (auto& x : o.before) sign(os, x);
+                os << "a";
+                for (auto& x : o.after) sign(os, x);
+                os << "g";
+                for (auto& x : o.grad) sign(os, x);
+            }
             os << "v";
             for (auto& x : U.srcs) sign(os, x);
             os << "g";

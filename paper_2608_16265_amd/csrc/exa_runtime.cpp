@@ -260,7 +260,22 @@ std::vector<ExaTile> make_tiles(const Model& M, int mode, int inst, int64_t tile
         // so that a 256-wide workgroup has work for every wave), of variables,
         // and fills of the variables nothing contributes to
         for (const OwnUnit& U : plan->units) {
-            if (U.vunit >= 0 || U.plain())
+            if (U.lgroup >= 0) {
+                // variables whose lists' entries are one round of lanes
+                const int64_t cap = std::min<int64_t>(tile_pts, EXA_LIST_TILE);
+                for (int64_t i = 0; i < U.n;) {
+                    int64_t e = i + 1;
+                    while (e < U.n && e - i < cap && U.lptr[e + 1] - U.lptr[i] <= cap) ++e;
+                    ExaTile t{};
+                    t.pat = U.code;
+                    t.inst = inst;
+                    t.start = i;
+                    t.count = e - i;
+                    t.slot = ((int64_t)(U.lptr[e] - U.lptr[i]) << 40) | U.lptr[i];
+                    tiles.push_back(t);
+                    i = e;
+                }
+            } else if (U.vunit >= 0 || U.plain())
                 cut(U.code, 0, U.vunit >= 0 ? U.n : U.npts, tile_pts);
             else
                 cut(U.code, 0, U.nrun, std::max<int64_t>(4, tile_pts / (64 * U.runl)));
@@ -309,7 +324,24 @@ void fill_own(const Model& M, DeviceState& D, ExaInstDev& inst) {
     };
     for (int k = 0; k < SUM_COUNT; ++k)
         for (const OwnUnit& U : M.own[k].units) {
-            if (U.vunit >= 0) {
+            if (U.lgroup >= 0) {
+                for (const OwnUnit::Out& o : U.outs) {
+                    inst.vlo[k][o.vunit] = o.lo;
+                    for (const std::vector<OwnSrc>* v : {&o.before, &o.after, &o.grad})
+                        for (const OwnSrc& x : *v) source(x);
+                }
+                // J^T w and H v over the same lists share them
+                if (k == SUM_HV)
+                    for (const OwnUnit& J : M.own[SUM_JT].units)
+                        if (J.lgroup >= 0 && J.lptr == U.lptr && J.lent == U.lent) {
+                            inst.lptr[k][U.lunit] = inst.lptr[SUM_JT][J.lunit];
+                            inst.lent[k][U.lunit] = inst.lent[SUM_JT][J.lunit];
+                        }
+                if (!inst.lptr[k][U.lunit]) {
+                    inst.lptr[k][U.lunit] = (const int*)D.upload(U.lptr.data(), U.lptr.size() * sizeof(int32_t));
+                    inst.lent[k][U.lunit] = (const int*)D.upload(U.lent.data(), U.lent.size() * sizeof(int32_t));
+                }
+            } else if (U.vunit >= 0) {
                 inst.vlo[k][U.vunit] = U.lo;
             } else {
                 ExaPatDev& d = inst.pat[M.groups[U.group].members[0]];
@@ -396,6 +428,9 @@ int64_t estimate_device_bytes(const Model& M) {
     for (const Group& G : M.groups)
         for (const std::vector<int32_t>& c : M.pats[G.members[0]].icols)
             if (!c.empty() && c.back() > c.front()) b += 4 * ((int64_t)c.back() - c.front() + 1);
+    // incidence lists
+    for (int k : {(int)SUM_JT, (int)SUM_HV})
+        for (const OwnUnit& U : M.own[k].units) b += 4 * (int64_t)(U.lptr.size() + U.lent.size());
     // maps: pointers and positions, plus at most a 24-byte record per four
     // entries (chunked sums, with padding) and part sums
     for (const SegMap* S : {&M.grad_map, &M.jt_map, &M.h_map, &M.par_map}) {
@@ -772,6 +807,14 @@ void ahead_unit(const Model& M, int mode, const ExaTile* t, size_t n, const Ahea
     if (!plan) return;
     for (const OwnUnit& U : plan->units) {
         if (U.code != code) continue;
+        if (U.lgroup >= 0) {
+            const Group& G = M.groups[U.lgroup];
+            in.add(rec.x, (int64_t)M.dev->inst_host.lent[mode == M_HPROD ? SUM_HV : SUM_JT][U.lunit], 4 * U.lptr[a],
+                   4 * U.lptr[b]);
+            // the points in the lists' order only as a whole
+            if (a == 0 && b == U.n) ahead_points(M, G, G.members, L, mode, 0, G.ndata, rec, in);
+            continue;
+        }
         if (U.vunit < 0) {
             const Group& G = M.groups[U.group];
             const int64_t per = U.plain() ? 1 : U.runl * (64 - U.S);
@@ -1202,17 +1245,28 @@ void kernel_bytes(const Model& M, const std::vector<int>& modes, bool fused, int
     std::vector<char> xs(M.nvar, 0), vs(M.nvar, 0), ts(M.ntheta, 0);
     struct Counted {
         int mode, code, group;
-        int64_t n;
+        int64_t n, nout = -1;  // points (variables), and where they differ those written
     };
     std::vector<Counted> units;
     for (int mode : modes) {
         const OwnPlan* plan = mode == M_GRADL ? nullptr : own_plan(M, mode, M.use_own);
         if (plan) {
-            for (const OwnUnit& U : plan->units) units.push_back({mode, U.code, U.group, U.vunit >= 0 ? U.n : U.npts});
+            for (const OwnUnit& U : plan->units) {
+                if (U.lgroup < 0) {
+                    units.push_back({mode, U.code, U.group, U.vunit >= 0 ? U.n : U.npts});
+                    continue;
+                }
+                units.push_back({mode, U.code, U.lgroup, M.groups[U.lgroup].ndata, U.n});
+                rd += 4 * (int64_t)(U.lptr.size() + U.lent.size());
+            }
             for (auto& z : plan->fill) wr += 8 * z.second;
             // entries the pulled contributions read
             for (const OwnUnit& U : plan->units) {
                 std::vector<OwnSrc> v = U.srcs;
+                for (const OwnUnit::Out& o : U.outs) {
+                    v.insert(v.end(), o.before.begin(), o.before.end());
+                    v.insert(v.end(), o.after.begin(), o.after.end());
+                }
                 for (const OwnChain& c : U.chains) {
                     v.insert(v.end(), c.before.begin(), c.before.end());
                     v.insert(v.end(), c.after.begin(), c.after.end());
@@ -1250,7 +1304,7 @@ void kernel_bytes(const Model& M, const std::vector<int>& modes, bool fused, int
         const Pattern& P0 = M.pats[G.members[0]];
         rd += u.n * (4 * (int64_t)L.icols.size() + 8 * (int64_t)L.fcols.size() + 8 * (int64_t)L.weights + L.extra);
         // the objective writes one partial sum per tile, not per data point
-        if (mode != M_OBJ) wr += u.n * 8 * L.outputs;
+        if (mode != M_OBJ) wr += (u.nout < 0 ? u.n : u.nout) * 8 * L.outputs;
         auto mark = [&](const RefKey& r, std::vector<char>& seen) {
             if (r.col < 0) {
                 if (r.off >= 0 && r.off < (int64_t)seen.size()) seen[r.off] = 1;
