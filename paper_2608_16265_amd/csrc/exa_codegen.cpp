@@ -1939,10 +1939,13 @@ __device__ __forceinline__ void exa_ahead(const ExaCall& C, const ExaInstDev& I,
     // every unit's tiles share a kernel's register budget: ask for at least
     // four waves per SIMD, so that one wave of the launch fits on the chip at
     // once.  The Jacobian + Hessian units need the most registers, so they
-    // get a kernel of their own: exa_k_multi runs the Jacobian and the
-    // Hessian as separate tiles and asks for five waves (its latency-bound
-    // pulls and gathers gain more from the fifth wave than the few values
-    // it then keeps in scratch cost), exa_k_multijh runs them as JH units.
+    // get a kernel of their own, exa_k_multijh; exa_k_multi runs the Jacobian
+    // and the Hessian as separate tiles.  A fifth wave there put 49 values per
+    // lane into scratch on network models, read back between the loads of the
+    // pulls (inputs from HBM, five / four waves: 78,484 buses J v 14.8 / 13.0
+    // us, J^T w + H v 21.8 / 20.7; 64 networks J^T w + H v 88.9 / 85.1; every
+    // callback, the grid and the trajectory equal; two and three waves are no
+    // better, and three take the trajectory's J^T w + H v from 76 to 96).
     for (bool jh : {false, true}) {
         int lds = 0;
         std::vector<std::string> cases;
@@ -1952,7 +1955,7 @@ __device__ __forceinline__ void exa_ahead(const ExaCall& C, const ExaInstDev& I,
         }
         if (M.lag_units) mode_cases(M_LAG, cases);
         cases.push_back(zero_case);
-        multi_kernel(jh ? "exa_k_multijh" : "exa_k_multi", lds, cases, jh ? 4 : 5);
+        multi_kernel(jh ? "exa_k_multijh" : "exa_k_multi", lds, cases, 4);
     }
     {
         int lds = mode_lds_doubles(M, M_OBJ);
