@@ -1371,9 +1371,10 @@ std::string own_lunit(const Model& M, int mode, const OwnUnit& U, int sum, int& 
 
 // A host unit: one data set's members in the lane of a point, in chunks of 64
 // lanes whose first W = 64 - S own a point each (the last S repeat the next
-// chunk's first points), a wave per run of chunks.  Contributions of
-// references a chain owns are shifted down the wave and added in ascending
-// point order; shared references are added up over the run and by the wave;
+// chunk's first points).  Contributions of references a chain owns are shifted
+// down the wave and added in ascending point order; shared references are
+// added up over a run of chunks by each wave, over the wave's lanes, and over
+// a run's four waves through LDS, so that many waves leave few partial sums;
 // the others go to the work buffer or straight to the output.
 std::string own_hunit(const Model& M, int mode, const OwnUnit& U, int sum, int& ntmp, UnitLive& live) {
     const Group& G = M.groups[U.group];
@@ -1383,7 +1384,7 @@ std::string own_hunit(const Model& M, int mode, const OwnUnit& U, int sum, int& 
         if (adds_to(M.pats[p], jm)) members.push_back(p);
     std::ostringstream os;
     os << "__device__ __forceinline__ void own_" << mode_name(mode) << "_" << U.code
-       << "(const ExaCall& C, const ExaInstDev& I, const ExaTile& T, double*) {\n";
+       << "(const ExaCall& C, const ExaInstDev& I, const ExaTile& T, double* lds) {\n    (void)lds;\n";
     os << own_prologue(M, members, m0);
     os << "    double* __restrict__ OUT = C.out1 + I.off[" << EXA_OFF_X << "];\n    (void)OUT;\n";
     const std::string W = std::to_string(64 - U.S), S = std::to_string(U.S);
@@ -1405,10 +1406,16 @@ std::string own_hunit(const Model& M, int mode, const OwnUnit& U, int sum, int& 
     os << "    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));\n";
     os << "    const long long n = P0.ndata;\n";
     os << "    const int R = P0.runl[" << sum << "];\n";
+    if (U.shared.empty()) {
     os << "    for (long long run = T.start + wave; run < T.start + T.count; run += nwav) {\n";
+    } else {
+    os << "    for (long long run = T.start; run < T.start + T.count; ++run) {\n";
+    os << "        for (int sub = wave; sub < " << kOwnWaves << "; sub += nwav) {\n";
+    }
     for (auto& x : U.shared) os << "        double s" << x.first << " = 0.0;\n";
     os << "        for (int ch = 0; ch < R; ++ch) {\n";
-    os << "            const long long k0 = (run * R + ch) * " << W << " - " << S << ";\n";
+    os << "            const long long k0 = (" << (U.shared.empty() ? "run" : "(run * " + std::to_string(kOwnWaves) + " + sub)")
+       << " * R + ch) * " << W << " - " << S << ";\n";
     os << "            if (k0 >= n) break;\n";
     os << "            const long long kr = k0 + lane;\n";
     os << "            const long long k = kr < 0 ? 0 : kr < n ? kr : n - 1;\n";
@@ -1495,13 +1502,30 @@ std::string own_hunit(const Model& M, int mode, const OwnUnit& U, int sum, int& 
         emit_result(mode, c.grad.size(), a, tag(i, "q"), ind, "OUT[v" + std::to_string(i) + "_]", own, os);
     }
     os << "        }\n";
+    int at = 0;  // of a wave's partial sums in its LDS
+    int partials = 0;
+    for (auto& x : U.shared) partials += x.second;
     for (auto& x : U.shared) {
         const std::string sv = "s" + std::to_string(x.first);
         for (int st = 32; st >= x.second; st >>= 1) os << "        " << sv << " += __shfl_xor(" << sv << ", " << st << ");\n";
-        const int at = (int)(std::find(list.begin(), list.end(), x.first) - list.begin());
-        const std::string pd = "P" + std::to_string(members[0]) + "_";
-        os << "        if (lane < " << x.second << ") (" << dest(M.pats[members[0]], jm, pd, "C.out0", false) << ")[" << at
-           << " * ((n + 15) & ~15LL) + (long long)lane * P0.nrun[" << sum << "] + run] = " << sv << ";\n";
+        os << "        if (lane < " << x.second << ") lds[sub * " << partials << " + " << at << " + lane] = " << sv << ";\n";
+        at += x.second;
+    }
+    if (!U.shared.empty()) {
+        // the waves' partial sums in order, whatever the workgroup's size
+        os << "        }\n        __syncthreads();\n";
+        at = 0;
+        for (auto& x : U.shared) {
+            const int j = (int)(std::find(list.begin(), list.end(), x.first) - list.begin());
+            const std::string pd = "P" + std::to_string(members[0]) + "_";
+            os << "        if (threadIdx.x < " << x.second << ") {\n            double t = 0.0;\n";
+            for (int w = 0; w < kOwnWaves; ++w)
+                os << "            t += lds[" << w * partials + at << " + threadIdx.x];\n";
+            os << "            (" << dest(M.pats[members[0]], jm, pd, "C.out0", false) << ")[" << j
+               << " * ((n + 15) & ~15LL) + (long long)threadIdx.x * P0.nrun[" << sum << "] + run] = t;\n        }\n";
+            at += x.second;
+        }
+        os << "        __syncthreads();\n";
     }
     os << "    }\n}\n";
     record_live(M, members, L, names, live);
@@ -1660,7 +1684,11 @@ int mode_lds_doubles(const Model& M, int mode) {
             if (pattern_in_mode(P, mode) && staged(P, mode)) st = std::max(st, out_step(P, mode));
     int d = st * EXA_BLOCK_MAX;
     if (mode == M_JTPROD || mode == M_HPROD)
-        for (const OwnUnit& U : M.own[sum_of(mode)].units) d = std::max(d, (int)U.outs.size() * EXA_LIST_TILE);
+        for (const OwnUnit& U : M.own[sum_of(mode)].units) {
+            int partials = 0;
+            for (auto& x : U.shared) partials += x.second;
+            d = std::max({d, (int)U.outs.size() * EXA_LIST_TILE, kOwnWaves * partials});
+        }
     return d;
 }
 

@@ -71,7 +71,7 @@ void set_last_error(const std::string& msg);
 // data point + vd[r] when its index column counts up by one; variable =
 // column value + vd[r] when the column's inverse table inv[c] is used), inv[c]
 // maps column values icmin[c] .. icmax[c] to their data point or -1, runl[s]
-// and nrun[s] are the 64-lane chunks per run and the runs of the data set's
+// and nrun[s] are the 64-lane chunks per wave and the runs of the data set's
 // unit for sum s (SumKind).  ExaInstDev::vlo[s][j]: the first variable of the
 // j-th unit over variables of sum s.  ExaInstDev::lptr[s][j], lent[s][j] (J^T w
 // and H v): incidence lists of its j-th list unit, entries lptr[i] .. lptr[i+1]
@@ -340,6 +340,7 @@ struct OwnSrc {
     bool sparse = false;     // hits under three quarters of the unit's variables: behind a branch
 };
 constexpr int OWN_AFFINE = 0, OWN_INVERSE = 1, OWN_LIST = 2;
+constexpr int kOwnWaves = 4;
 constexpr int kOwnSpan = 8;  // largest lane shift of a chain
 struct OwnChain {
     int top = 0;                             // reference with the largest offset
@@ -374,9 +375,12 @@ struct OwnUnit {
     std::vector<std::pair<int, int64_t>> slots;  // (column, offset from the range's first variable)
     std::vector<int32_t> lptr, lent;             // this instance's lists
     double spread = 0;  // 128-byte lines 256 entries touch, over those of 256 points in a row
-    // host units: this instance's points, chunks per run and runs
+    // host units: this instance's points, chunks a wave takes in turn, and
+    // runs of one wave, or with shared references of kOwnWaves waves whose
+    // partial sums are added in order into one
     int64_t npts = 0;
     int64_t runl = 1, nrun = 0;
+    int64_t points_per_run() const { return runl * (64 - S) * (shared.empty() ? 1 : kOwnWaves); }
     // lanes take points as in any unit (no shifts, no sums over a wave)
     bool plain() const { return S == 0 && shared.empty(); }
 };

@@ -31,9 +31,15 @@ constexpr int kListLength = 64, kListNodes = 400, kListSlots = 4;
 // ring of 78,484 buses with chords (spread 5) 18.2 / 13.4 and 16.7 / 12.6.
 constexpr int64_t kListBytes = (int64_t)2 << 20;
 constexpr int kListSpread = 8;
-// Lanes of a run's partial sums: at most this many runs per data set, so that
-// one workgroup can add a variable's partial sums.
-constexpr int64_t kMaxRuns = 4096;
+// Runs per data set, so that one workgroup can add a variable's partial sums.
+// Each run is kOwnWaves waves' work (8192 waves at most: more than the chip
+// holds), added through LDS: 65,536 scenarios' J^T w 25.8 us with 4096 runs of
+// one wave, 23.2 with 2048 of four, H v 31.9 / 30.3; 4096 scenarios 9.3 / 8.1
+// and 9.7 / 8.4 (the reduction reads a quarter); a trajectory of 10,000 steps,
+// every callback 9.4 / 8.1.  1024 and 4096 runs of four: J^T w 22.7 and 24.5.
+constexpr int64_t kMaxRuns = 2048;
+// Doubles a workgroup holds for its waves' partial sums.
+constexpr int kMaxPartials = 2048;
 
 struct Src {
     OwnSrc s;
@@ -547,7 +553,9 @@ void plan_one(Model& M, SumKind s, const std::vector<std::vector<char>>& inc,
         for (const OwnChain& c : U.chains)
             for (auto& r : c.refs) U.S = std::max(U.S, r.first);
         const int64_t W = 64 - U.S, chunks = (G.ndata + U.S + W - 1) / W;
-        const int64_t runl = std::max<int64_t>(1, (chunks + kMaxRuns - 1) / kMaxRuns), nrun = (chunks + runl - 1) / runl;
+        const int64_t runl = std::max<int64_t>(1, (chunks + kMaxRuns * kOwnWaves - 1) / (kMaxRuns * kOwnWaves)),
+                      nrun = (chunks + runl * kOwnWaves - 1) / (runl * kOwnWaves);
+        int partials = 0;
         const std::vector<int>& list = s == SUM_JT ? G.jt_refs : s == SUM_HV ? G.hv_refs : refs[g];
         if (G.ndata == 0) continue;
         for (size_t j = 0; j < list.size(); ++j) {
@@ -566,15 +574,16 @@ void plan_one(Model& M, SumKind s, const std::vector<std::vector<char>>& inc,
                 P = period[g][k.col];
             // a chunk's phases are its lanes' only when chunks start at
             // multiples of 64; the partial sums take the reference's slot
-            if (P && (P == 1 || U.S == 0) && nrun * P <= bs) {
+            if (P && (P == 1 || U.S == 0) && nrun * P <= bs && kOwnWaves * (partials + P) <= kMaxPartials) {
+                partials += P;
                 U.shared.emplace_back(r, P);
                 any = true;
             } else {
                 U.bufrefs.push_back(r);
             }
         }
-        if (!U.shared.empty()) U.runl = runl;
-        U.nrun = (chunks + U.runl - 1) / U.runl;
+        U.nrun = chunks;
+        if (!U.shared.empty()) U.runl = runl, U.nrun = nrun;
         if (!U.chains.empty() || !U.bufrefs.empty() || !U.shared.empty() || !U.direct.empty()) plan.units.push_back(U);
     }
     int j = 0;

@@ -278,7 +278,8 @@ std::vector<ExaTile> make_tiles(const Model& M, int mode, int inst, int64_t tile
             } else if (U.vunit >= 0 || U.plain())
                 cut(U.code, 0, U.vunit >= 0 ? U.n : U.npts, tile_pts);
             else
-                cut(U.code, 0, U.nrun, std::max<int64_t>(4, tile_pts / (64 * U.runl)));
+                cut(U.code, 0, U.nrun,
+                    std::max<int64_t>(U.shared.empty() ? kOwnWaves : 1, tile_pts / U.points_per_run()));
         }
         for (auto& z : plan->fill) cut(EXA_ZERO_TILE, z.first, z.second, std::max(tile_pts, kZeroTileEntries));
         return tiles;
@@ -785,7 +786,7 @@ int64_t tile_outputs(const Model& M, int mode, const ExaTile* t, size_t n) {
     if (code >= EXA_OWN_CODE && code < EXA_OWN_VCODE)
         if (const OwnPlan* plan = own_plan(M, mode, true))
             for (const OwnUnit& U : plan->units)
-                if (U.code == code && !U.plain()) per = U.runl * (64 - U.S);
+                if (U.code == code && !U.plain()) per = U.points_per_run();
     return 8 * (b - a) * per * (code == EXA_ZERO_TILE ? 1 : it->second.outputs);
 }
 
@@ -817,7 +818,7 @@ void ahead_unit(const Model& M, int mode, const ExaTile* t, size_t n, const Ahea
         }
         if (U.vunit < 0) {
             const Group& G = M.groups[U.group];
-            const int64_t per = U.plain() ? 1 : U.runl * (64 - U.S);
+            const int64_t per = U.plain() ? 1 : U.points_per_run();
             ahead_points(M, G, G.members, L, mode, a * per - U.S, b * per, rec, in);
             continue;
         }
