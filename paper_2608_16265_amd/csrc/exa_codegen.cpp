@@ -701,11 +701,11 @@ std::string aug_fn(const Model& M, int mode, int a, int& ntmp, UnitLive& live) {
     const Pattern& P = M.pats[a];
     std::ostringstream os;
     os << "__device__ __forceinline__ double aug_" << mode_name(mode) << "_" << a
-       << "(const ExaCall& C, const ExaInstDev& I, long long k) {\n";
-    os << "    const ExaPatDev& Pa = I.pat[" << a << "];\n";
+       << "(const ExaCall& C, const EXA_K ExaInstDev& I, long long k) {\n";
+    os << "    const EXA_K ExaPatDev& Pa = I.pat[" << a << "];\n";
     os << "    const double* __restrict__ X = C.x + I.off[" << EXA_OFF_X << "];\n";
     os << "    const double* __restrict__ V = C.v + I.off[" << EXA_OFF_X << "];\n";
-    os << "    const double* __restrict__ TH = I.theta;\n";
+    os << "    const EXA_G double* __restrict__ TH = I.theta;\n";
     os << "    (void)X; (void)V; (void)TH;\n";
     os << "    double r = 0.0;\n";
     Em e(ntmp);
@@ -839,6 +839,20 @@ void record_live(const Model& M, const std::vector<int>& members, const Loads& L
                 if (names.count(w + std::to_string(p))) live.weights++;
 }
 
+// At the head of a round: the tables' fields are read in it, not kept in
+// registers over a tile's rounds (they are more than the scalar registers hold,
+// and the rest would take vector registers).
+std::string again(const std::string& ind) {
+    return ind + "const EXA_K ExaInstDev* I_ = exa_again(&I);\n" + ind + "const EXA_K ExaInstDev& I = *I_;\n";
+}
+
+std::string pattern_refs(const std::vector<int>& members, int m0, const std::string& ind) {
+    std::ostringstream os;
+    os << ind << "const EXA_K ExaPatDev& P0 = I.pat[" << m0 << "];\n" << ind << "(void)P0;\n";
+    for (int p : members) os << ind << "const EXA_K ExaPatDev& P" << p << "_ = I.pat[" << p << "];\n";
+    return os.str();
+}
+
 // Generates the tile function of one unit; fills `live`.  A plain unit runs
 // one callback's job per member (two for JH); a multi unit (M_SFULL,
 // M_SIPM) runs every job of its modes per member from one set of loads and
@@ -852,9 +866,9 @@ std::string unit_tile(const Model& M, int mode, const Unit& U, int& ntmp, UnitLi
     std::ostringstream os;
     const std::string fn = std::string("unit_") + mode_name(mode) + "_" + std::to_string(U.code);
     os << "__device__ __forceinline__ void " << fn << "(const " << (multi ? "ExaMulti" : "ExaCall")
-       << "& C, const ExaInstDev& I, const ExaTile& T, double* lds) {\n";
-    os << "    const ExaPatDev& P0 = I.pat[" << m0 << "];\n";
-    for (int p : U.members) os << "    const ExaPatDev& P" << p << "_ = I.pat[" << p << "];\n";
+       << "& C, const EXA_K ExaInstDev& I, const ExaTile& T, double* lds) {\n";
+    os << "    const EXA_K ExaPatDev& P0 = I.pat[" << m0 << "];\n";
+    for (int p : U.members) os << "    const EXA_K ExaPatDev& P" << p << "_ = I.pat[" << p << "];\n";
     // inputs: x for every job; v seeds jprod/hprod; y weighs hess/hprod
     // (sigma for objectives); w weighs jtprod (in a plain jtprod call it is C.y)
     const std::string cx = multi ? call(M_JAC) : "C", cv = multi ? call(M_JPROD) : "C",
@@ -863,7 +877,7 @@ std::string unit_tile(const Model& M, int mode, const Unit& U, int& ntmp, UnitLi
     os << "    const double* __restrict__ V = " << cv << ".v + I.off[" << EXA_OFF_X << "];\n";
     os << "    const double* __restrict__ Y = " << cy << ".y + I.off[" << EXA_OFF_Y << "];\n";
     os << "    const double* __restrict__ W = " << cw << ".y + I.off[" << EXA_OFF_Y << "];\n";
-    os << "    const double* __restrict__ TH = I.theta;\n";
+    os << "    const EXA_G double* __restrict__ TH = I.theta;\n";
     os << "    (void)X; (void)V; (void)Y; (void)W; (void)TH; (void)P0;\n";
     os << "    const int nthr = (int)blockDim.x;\n";
     os << "    const long long kend = T.start + T.count;\n";
@@ -889,6 +903,7 @@ std::string unit_tile(const Model& M, int mode, const Unit& U, int& ntmp, UnitLi
         // so that each job's staged store (workgroup barriers) can follow its
         // sweep: lanes past the end recompute the last point and store nothing
         os << "        const long long k = kr < kend ? kr : kend - 1;\n";
+        os << again("        ") << pattern_refs(U.members, m0, "        ");
     }
     const std::vector<Job> jobs = jobs_of(M, mode, U);
     const bool several = jm.size() > 1;
@@ -1122,13 +1137,13 @@ std::vector<char> slots_to(const Pattern& P, int mode, const std::set<int>& refs
 
 std::string own_prologue(const Model& M, const std::vector<int>& members, int m0) {
     std::ostringstream os;
-    os << "    const ExaPatDev& P0 = I.pat[" << m0 << "];\n";
-    for (int p : members) os << "    const ExaPatDev& P" << p << "_ = I.pat[" << p << "];\n";
+    os << "    const EXA_K ExaPatDev& P0 = I.pat[" << m0 << "];\n";
+    for (int p : members) os << "    const EXA_K ExaPatDev& P" << p << "_ = I.pat[" << p << "];\n";
     os << "    const double* __restrict__ X = C.x + I.off[" << EXA_OFF_X << "];\n";
     os << "    const double* __restrict__ V = C.v + I.off[" << EXA_OFF_X << "];\n";
     os << "    const double* __restrict__ Y = C.y + I.off[" << EXA_OFF_Y << "];\n";
     os << "    const double* __restrict__ W = C.y + I.off[" << EXA_OFF_Y << "];\n";
-    os << "    const double* __restrict__ TH = I.theta;\n";
+    os << "    const EXA_G double* __restrict__ TH = I.theta;\n";
     os << "    (void)X; (void)V; (void)Y; (void)W; (void)TH; (void)P0;\n";
     return os.str();
 }
@@ -1147,7 +1162,7 @@ std::string pull_fn(const Model& M, int mode, const OwnSrc& s, int& ntmp, UnitLi
     const int jm = s.pat >= 0 ? M_GRAD : mode;
     std::ostringstream os;
     os << "__device__ __forceinline__ double " << pull_name(s, mode)
-       << "(const ExaCall& C, const ExaInstDev& I, long long k, long long cv) {\n    (void)cv;\n";
+       << "(const ExaCall& C, const EXA_K ExaInstDev& I, long long k, long long cv) {\n    (void)cv;\n";
     std::vector<int> members;
     if (s.wread >= 0)
         members = {s.wread};
@@ -1261,10 +1276,10 @@ std::string own_vunit(const Model& M, int mode, const OwnUnit& U, int sum, UnitL
     std::ostringstream os;
     const int jm = mode == M_LAG ? M_JTPROD : mode;
     os << "__device__ __forceinline__ void own_" << mode_name(mode) << "_" << U.code
-       << "(const ExaCall& C, const ExaInstDev& I, const ExaTile& T, double*) {\n";
+       << "(const ExaCall& C, const EXA_K ExaInstDev& I, const ExaTile& T, double*) {\n";
     os << "    double* __restrict__ OUT = C.out1 + I.off[" << EXA_OFF_X << "];\n";
     os << "    for (long long i = T.start + threadIdx.x; i < T.start + T.count; i += blockDim.x) {\n";
-    os << "        const long long v = I.vlo[" << sum << "][" << U.vunit << "] + i;\n";
+    os << again("        ") << "        const long long v = I.vlo[" << sum << "][" << U.vunit << "] + i;\n";
     emit_pulls(M, jm, U.srcs, "v", "u", "        ", os);
     if (mode == M_LAG) emit_pulls(M, jm, U.grad, "v", "g", "        ", os);
     os << "        double a = 0.0;\n";
@@ -1301,16 +1316,17 @@ std::string own_lunit(const Model& M, int mode, const OwnUnit& U, int sum, int& 
     }
     std::ostringstream os;
     os << "__device__ __forceinline__ void own_" << mode_name(mode) << "_" << U.code
-       << "(const ExaCall& C, const ExaInstDev& I, const ExaTile& T, double* lds) {\n";
+       << "(const ExaCall& C, const EXA_K ExaInstDev& I, const ExaTile& T, double* lds) {\n";
     os << own_prologue(M, members, m0);
     os << "    double* __restrict__ OUT = C.out1 + I.off[" << EXA_OFF_X << "];\n";
     os << "    const int ne = (int)(T.slot >> 40), nv = (int)T.count, nthr = (int)blockDim.x, t = (int)threadIdx.x;\n";
     os << "    const int e0 = (int)(T.slot & ((1LL << 40) - 1));\n";
-    os << "    const int* __restrict__ LE = I.lent[" << sum << "][" << U.lunit << "] + e0;\n";
-    os << "    const int* __restrict__ LP = I.lptr[" << sum << "][" << U.lunit << "] + T.start;\n";
+    os << "    const EXA_G int* __restrict__ LE = I.lent[" << sum << "][" << U.lunit << "] + e0;\n";
+    os << "    const EXA_G int* __restrict__ LP = I.lptr[" << sum << "][" << U.lunit << "] + T.start;\n";
     os << "    int pa = LP[t < nv ? t : nv], pb = LP[t < nv ? t + 1 : nv];\n";
     os << "    for (int q0 = 0; q0 < ne; q0 += nthr) {\n";
     os << "        const int q = q0 + t;\n";
+    os << again("        ") << pattern_refs(members, m0, "        ");
     os << "        const int en = LE[q < ne ? q : ne - 1];\n";
     os << "        const long long k = en >> 2;\n";
     os << "        const int sl = en & 3;\n        (void)sl;\n";
@@ -1384,7 +1400,7 @@ std::string own_hunit(const Model& M, int mode, const OwnUnit& U, int sum, int& 
         if (adds_to(M.pats[p], jm)) members.push_back(p);
     std::ostringstream os;
     os << "__device__ __forceinline__ void own_" << mode_name(mode) << "_" << U.code
-       << "(const ExaCall& C, const ExaInstDev& I, const ExaTile& T, double* lds) {\n    (void)lds;\n";
+       << "(const ExaCall& C, const EXA_K ExaInstDev& I, const ExaTile& T, double* lds) {\n    (void)lds;\n";
     os << own_prologue(M, members, m0);
     os << "    double* __restrict__ OUT = C.out1 + I.off[" << EXA_OFF_X << "];\n    (void)OUT;\n";
     const std::string W = std::to_string(64 - U.S), S = std::to_string(U.S);
@@ -1400,7 +1416,7 @@ std::string own_hunit(const Model& M, int mode, const OwnUnit& U, int sum, int& 
         os << "        for (long long kb = T.start; kb < kend; kb += (int)blockDim.x) {\n";
         os << "            const long long kr = kb + threadIdx.x;\n";
         os << "            const long long k = kr < kend ? kr : kend - 1;\n";
-        os << "            asm volatile(\"\" ::: \"memory\");\n";
+        os << again("            ") << pattern_refs(members, m0, "            ");
     } else {
     os << "    const int lane = (int)(threadIdx.x & 63), nwav = (int)(blockDim.x >> 6);\n";
     os << "    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));\n";
@@ -1419,7 +1435,7 @@ std::string own_hunit(const Model& M, int mode, const OwnUnit& U, int sum, int& 
     os << "            if (k0 >= n) break;\n";
     os << "            const long long kr = k0 + lane;\n";
     os << "            const long long k = kr < 0 ? 0 : kr < n ? kr : n - 1;\n";
-    os << "            asm volatile(\"\" ::: \"memory\");\n";
+    os << again("            ") << pattern_refs(members, m0, "            ");
     os << "            const bool pt = " << (U.S ? "lane < " + W + " && kr >= 0 && " : std::string()) << "kr < n;\n";
     }
     // references this unit needs, and where they go
@@ -1712,6 +1728,7 @@ std::string generate_source(const Model& M, std::map<std::pair<int, int>, UnitLi
     g_hvd = hvd_flags;
     std::ostringstream os;
     os << "// generated: straight-line evaluation kernels for one pattern set\n";
+    os << "#define EXA_G __attribute__((address_space(1)))\n#define EXA_K __attribute__((address_space(4)))\n";
     os << EXA_STR(EXA_DEVICE_STRUCTS) << "\n";
     os << "static_assert(sizeof(ExaPatDev) == " << sizeof(ExaPatDev) << ", \"layout\");\n";
     os << "static_assert(sizeof(ExaInstDev) == " << sizeof(ExaInstDev) << ", \"layout\");\n";
@@ -1840,19 +1857,25 @@ __device__ __forceinline__ int exa_term(int j, int je) { return j < je ? j : (je
     os << "// rounds of EXA_VLANES points in one objective tile\n#define EXA_OBJ_ROUNDS " << kObjBlock * kObjEpl / 256
        << "\n";
     os << R"(
+// The tables anew: what a round reads from them is not kept in registers over
+// the rounds of a tile.
+__device__ __forceinline__ const EXA_K ExaInstDev* exa_again(const EXA_K ExaInstDev* p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
 // Reads a tile's input range into this XCD's L2, one dword per 128-byte line:
 // 256 lanes cover 32 KB with one load each.
-__device__ __forceinline__ void exa_ahead(const ExaCall& C, const ExaInstDev& I, const ExaTile& T) {
-    const char* p = T.slot == )" << EXA_AHEAD_X << " ? (const char*)(C.x + I.off[" << EXA_OFF_X << "] + T.start) : T.slot == "
-       << EXA_AHEAD_Y << " ? (const char*)(C.y + I.off[" << EXA_OFF_Y << "] + T.start) : T.slot == " << EXA_AHEAD_V
-       << " ? (const char*)(C.v + I.off[" << EXA_OFF_X << R"(] + T.start) : (const char*)T.slot + T.start;
+__device__ __forceinline__ void exa_ahead(const ExaCall& C, const EXA_K ExaInstDev& I, const ExaTile& T) {
+    const EXA_G char* p = T.slot == )" << EXA_AHEAD_X << " ? (const EXA_G char*)(C.x + I.off[" << EXA_OFF_X << "] + T.start) : T.slot == "
+       << EXA_AHEAD_Y << " ? (const EXA_G char*)(C.y + I.off[" << EXA_OFF_Y << "] + T.start) : T.slot == " << EXA_AHEAD_V
+       << " ? (const EXA_G char*)(C.v + I.off[" << EXA_OFF_X << R"(] + T.start) : (const EXA_G char*)T.slot + T.start;
     const long long last = T.count - 4;
     int acc = 0;
     for (long long o = 128ll * threadIdx.x; o < T.count; o += 8 * 128ll * blockDim.x) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const long long q = o + u * 128ll * blockDim.x;
-            acc ^= *(const int*)(p + (q < last ? q : last));
+            acc ^= *(const EXA_G int*)(p + (q < last ? q : last));
         }
     }
     asm volatile("" ::"v"(acc));
@@ -1870,7 +1893,7 @@ __device__ __forceinline__ void exa_ahead(const ExaCall& C, const ExaInstDev& I,
         os << "        const long long w = (blockIdx.x % 8) * C.per_xcd + blockIdx.x / 8;\n";
         os << "        if (w >= C.ntiles) return;\n";
         os << "        const ExaTile T = C.tiles[w];\n";
-        os << "        const ExaInstDev& I = C.inst[T.inst];\n";
+        os << "        const EXA_K ExaInstDev& I = C.inst[T.inst];\n";
         os << "        switch (T.pat) {\n";
         for (auto& c : cases) os << "            " << c << "\n";
         if (ahead) os << "            case " << EXA_AHEAD_TILE << ": exa_ahead(C, I, T); break;\n";

@@ -76,10 +76,20 @@ void set_last_error(const std::string& msg);
 // j-th unit over variables of sum s.  ExaInstDev::lptr[s][j], lent[s][j] (J^T w
 // and H v): incidence lists of its j-th list unit, entries lptr[i] .. lptr[i+1]
 // of the unit's i-th variable, each a data point * 4 + the slot (OwnUnit::slots).
+// EXA_G and EXA_K name the address spaces of data (global memory) and of the
+// tables (read-only for a launch) in the generated code; the host has one.
+// Without them a pointer read from a table is generic: its loads are flat ones
+// (which hold back every later wait, LDS included), and a table field behind a
+// store is read by a vector load, into registers: the network's jtprod kernel
+// took 90 vector registers instead of 60, exa_k_multi 119 instead of 91, the
+// trajectory's 149 instead of 120.  Before / after, inputs from HBM: every
+// callback of the trajectory 159 / 130 us, of the grid 61.7 / 54.4, of 64
+// networks 183 / 170, of 10,000 buses 10.3 / 8.8; Lagrangian gradient and H v
+// of 65,536 scenarios 79 / 62.
 #define EXA_DEVICE_STRUCTS                                                       \
     struct ExaPatDev {                                                           \
-        const int* ic[8];                                                        \
-        const double* fc[8];                                                     \
+        const EXA_G int* ic[8];                                                  \
+        const EXA_G double* fc[8];                                               \
         long long ndata;                                                         \
         long long o0;                                                            \
         long long o1;                                                            \
@@ -91,11 +101,11 @@ void set_last_error(const std::string& msg);
         long long row_off;                                                       \
         int row_ic;                                                              \
         int hvd;                                                                 \
-        const int* rptr;                                                         \
-        const int* ridx;                                                         \
+        const EXA_G int* rptr;                                                   \
+        const EXA_G int* ridx;                                                   \
         long long roff[48];                                                      \
         long long vd[48];                                                        \
-        const int* inv[8];                                                       \
+        const EXA_G int* inv[8];                                                 \
         int icmin[8];                                                            \
         int icmax[8];                                                            \
         int runl[4];                                                             \
@@ -103,11 +113,11 @@ void set_last_error(const std::string& msg);
     };                                                                           \
     struct ExaInstDev {                                                          \
         long long off[12];                                                       \
-        const double* theta;                                                     \
+        const EXA_G double* theta;                                               \
         long long pad1;                                                          \
         long long vlo[4][32];                                                    \
-        const int* lptr[2][4];                                                   \
-        const int* lent[2][4];                                                   \
+        const EXA_G int* lptr[2][4];                                             \
+        const EXA_G int* lent[2][4];                                             \
         struct ExaPatDev pat[32];                                                \
     };                                                                           \
     struct ExaTile {                                                             \
@@ -121,7 +131,7 @@ void set_last_error(const std::string& msg);
         const struct ExaTile* tiles;                                             \
         long long ntiles;                                                        \
         long long per_xcd;                                                       \
-        const struct ExaInstDev* inst;                                           \
+        const EXA_K struct ExaInstDev* inst;                                     \
         const double* x;                                                         \
         const double* y;                                                         \
         const double* v;                                                         \
@@ -138,7 +148,11 @@ void set_last_error(const std::string& msg);
         struct ExaCall c[10];                                                    \
     };
 
+#define EXA_G
+#define EXA_K
 EXA_DEVICE_STRUCTS
+#undef EXA_G
+#undef EXA_K
 
 #define EXA_STR2(...) #__VA_ARGS__
 #define EXA_STR(...) EXA_STR2(__VA_ARGS__)
