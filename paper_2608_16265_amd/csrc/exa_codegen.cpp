@@ -1112,6 +1112,7 @@ std::string unit_tile(const Model& M, int mode, const Unit& U, int& ntmp, UnitLi
     os << "    }\n";
     if (mode == M_OBJ) {
         os << "    const double tot = exa_vlane_sum(acc, lds);\n";
+        os << "    if (C.direct) {\n        exa_obj_finish(C, I.nobj, T.slot, tot, lds);\n        return;\n    }\n";
         os << "    if (threadIdx.x == 0) C.out0[I.off[" << EXA_OFF_TILE << "] + T.slot] = tot;\n";
     }
     os << "}\n";
@@ -1857,6 +1858,45 @@ __device__ __forceinline__ int exa_term(int j, int je) { return j < je ? j : (je
     os << "// rounds of EXA_VLANES points in one objective tile\n#define EXA_OBJ_ROUNDS " << kObjBlock * kObjEpl / 256
        << "\n";
     os << R"(
+// The objective from its tiles' partial sums by the last tile's workgroup, in
+// the order of the reduction kernel (256 lanes over the tiles, then a tree)
+// whichever that is, instead of by a launch of its own.  Each tile's partial
+// sum is stored past this XCD's caches (agent scope) and has arrived, by the
+// wait, when the tile is counted; the workgroup that counts last reads them
+// the same way and clears the count for the next launch.  No workgroup waits
+// for another.  A release or acquire at agent scope would write back and
+// invalidate the XCD's whole L2 for these few words.  f, the gradient and H v
+// of 200,000 variables 17.5 -> 14.3 us, every callback of the 1000 x 1000
+// grid 54.4 -> 53.0.
+__device__ __forceinline__ void exa_obj_finish(const ExaCall& C, long long n, long long slot, double tot, double* lds) {
+    __shared__ int last;
+    unsigned long long* P = (unsigned long long*)C.out0;
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(&P[slot], (unsigned long long)__double_as_longlong(tot), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_s_waitcnt(0);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        const unsigned long long c = __hip_atomic_fetch_add(&P[n], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = c + 1 == (unsigned long long)n;
+    }
+    __syncthreads();
+    if (!last) return;
+    const int nthr = (int)blockDim.x;
+    double acc[EXA_VLANES / 64] = {};
+#pragma unroll
+    for (int q = 0; q < EXA_VLANES / 64; ++q) {
+        if (q * nthr >= EXA_VLANES) break;
+        for (long long i = threadIdx.x + q * nthr; i < n; i += EXA_VLANES)
+            acc[q] += __longlong_as_double(
+                (long long)__hip_atomic_load(&P[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    }
+    const double f = exa_vlane_sum(acc, lds);
+    if (threadIdx.x == 0) {
+        C.out1[0] = f;
+        __hip_atomic_store(&P[n], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
 // The tables anew: what a round reads from them is not kept in registers over
 // the rounds of a tile.
 __device__ __forceinline__ const EXA_K ExaInstDev* exa_again(const EXA_K ExaInstDev* p) {

@@ -73,7 +73,8 @@ void set_last_error(const std::string& msg);
 // maps column values icmin[c] .. icmax[c] to their data point or -1, runl[s]
 // and nrun[s] are the 64-lane chunks per wave and the runs of the data set's
 // unit for sum s (SumKind).  ExaInstDev::vlo[s][j]: the first variable of the
-// j-th unit over variables of sum s.  ExaInstDev::lptr[s][j], lent[s][j] (J^T w
+// j-th unit over variables of sum s.  ExaInstDev::nobj: objective tiles, whose
+// partial sums the last of them adds (ExaCall::direct).  ExaInstDev::lptr[s][j], lent[s][j] (J^T w
 // and H v): incidence lists of its j-th list unit, entries lptr[i] .. lptr[i+1]
 // of the unit's i-th variable, each a data point * 4 + the slot (OwnUnit::slots).
 // EXA_G and EXA_K name the address spaces of data (global memory) and of the
@@ -114,7 +115,7 @@ void set_last_error(const std::string& msg);
     struct ExaInstDev {                                                          \
         long long off[12];                                                       \
         const EXA_G double* theta;                                               \
-        long long pad1;                                                          \
+        long long nobj;                                                          \
         long long vlo[4][32];                                                    \
         const EXA_G int* lptr[2][4];                                             \
         const EXA_G int* lent[2][4];                                             \

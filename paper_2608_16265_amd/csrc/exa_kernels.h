@@ -4,7 +4,6 @@
 
 #include <cstdint>
 
-hipError_t exa_launch_sum(const double* part, int64_t n, double* out, hipStream_t s);
 hipError_t exa_launch_fill(double* p, int64_t n, double v, hipStream_t s);
 hipError_t exa_launch_copy(const void* src, void* dst, int64_t bytes, hipStream_t s);
 

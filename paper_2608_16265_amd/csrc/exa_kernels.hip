@@ -177,17 +177,10 @@ __device__ __forceinline__ void sum_body(const double* __restrict__ part, int64_
     if (threadIdx.x == 0) out[0] = s;
 }
 
-__global__ void __launch_bounds__(256) k_sum(const double* __restrict__ part, int64_t n,
-                                             double* __restrict__ out) {
-    __shared__ double lds[256];
-    sum_body(part, n, out, lds);
-}
-
 // Several reductions in one launch: the segment sums of each job over
 // consecutive block ranges (one block per 256 segments; for a chunked job,
 // one per 256 lanes, then one per part of a long segment), then (when
-// R.part is set) one block for the objective partials, summed as k_sum
-// does.
+// R.part is set) one block for objective partials.
 __host__ __device__ inline int64_t job_blocks(const ExaSegJob& J) {
     return (J.chunked ? J.nlanes / kSegBlock : (J.nseg + kSegBlock - 1) / kSegBlock) + J.nparts;
 }
@@ -387,11 +380,6 @@ __global__ void __launch_bounds__(256) k_fill(double* __restrict__ p, int64_t n,
 }
 
 }  // namespace
-
-hipError_t exa_launch_sum(const double* part, int64_t n, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_sum, dim3(1), dim3(256), 0, s, part, n, out);
-    return hipGetLastError();
-}
 
 hipError_t exa_launch_reduce(const ExaReduce& r, hipStream_t s) {
     if (r.njobs < 0 || r.njobs > kExaReduceJobs) return hipErrorInvalidValue;

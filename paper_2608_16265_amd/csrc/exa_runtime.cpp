@@ -424,7 +424,7 @@ int64_t estimate_device_bytes(const Model& M) {
         b += (int64_t)sizeof(ExaTile) * (int64_t)make_tiles(M, mode, 0, tp, fixed ? kObjFused : M.fuse).size();
     }
     const int64_t nobj = (int64_t)make_tiles(M, M_OBJ, 0, (int64_t)kObjBlock * kObjEpl, kObjFused).size();
-    b += 8 * (M.fo_obj_len + M.fo_con_len + M.par_len + M.hv_len + std::max<int64_t>(1, nobj) + M.nvar + 1);
+    b += 8 * (M.fo_obj_len + M.fo_con_len + M.par_len + M.hv_len + nobj + 1 + M.nvar + 1);
     // inverse tables of strictly increasing columns (at most one per column)
     for (const Group& G : M.groups)
         for (const std::vector<int32_t>& c : M.pats[G.members[0]].icols)
@@ -468,6 +468,7 @@ void build_device(Model& M) {
     fill_patdev(M, D, inst);
     inst.theta = D.theta;
     inst.off[EXA_OFF_FO_CON] = M.fo_obj_len;
+    inst.nobj = (int64_t)make_tiles(M, M_OBJ, 0, (int64_t)kObjBlock * kObjEpl, kObjFused).size();
     D.inst_host = inst;
     D.inst = (ExaInstDev*)D.upload(&inst, sizeof inst);
 
@@ -482,7 +483,9 @@ void build_device(Model& M) {
     D.fo = (double*)D.alloc((M.fo_obj_len + M.fo_con_len) * sizeof(double));
     D.par = (double*)D.alloc(M.par_len * sizeof(double));
     D.hv = (double*)D.alloc(M.hv_len * sizeof(double));
-    D.tilesum = (double*)D.alloc(std::max<int64_t>(1, D.sched[M_OBJ].ntiles) * sizeof(double));
+    // partial sums, and the count of tiles that have stored theirs
+    const std::vector<double> zero(D.sched[M_OBJ].ntiles + 1, 0.0);
+    D.tilesum = (double*)D.upload(zero.data(), zero.size() * sizeof(double));
     D.lag_tmp = (double*)D.alloc(M.nvar * sizeof(double));
     D.fval = (double*)D.alloc(sizeof(double));
     if (hipHostMalloc((void**)&D.fhost, sizeof(double), hipHostMallocDefault) != hipSuccess)
@@ -1354,7 +1357,8 @@ void kernel_bytes(const Model& M, const std::vector<int>& modes, bool fused, int
 }
 
 // Reduction launch of an exa_eval mask: maps (int32 when every position
-// fits), buffer entries once, outputs once; objective partials when several.
+// fits), buffer entries once, outputs once; objective partials when several
+// (which a single model's last objective tile adds).
 void reduce_bytes(const Model& M, uint32_t mask, int64_t& rr, int64_t& rw) {
     rr = rw = 0;
     auto seg = [&](const SegMap& S, bool own) {
@@ -1611,13 +1615,15 @@ void obj_body(Model& M, const double* x, double* f, hipStream_t s) {
     if (D.sched[M_OBJ].ntiles == 0) {
         hip_check(exa_launch_fill(f, 1, 0.0, s), "fill");
     } else {
-        // one tile: its workgroup sum is the objective, written in place
+        // one tile: its workgroup sum is the objective, written in place;
+        // several: the last of them adds the partial sums
         const bool one = D.sched[M_OBJ].ntiles == 1;
         ExaCall c = blank_call();
         c.x = x;
         c.out0 = one ? f : D.tilesum;
+        c.out1 = f;
+        c.direct = one ? 0 : 1;
         launch_mode(M, M_OBJ, c, s);
-        if (!one) hip_check(exa_launch_sum(D.tilesum, D.sched[M_OBJ].ntiles, f, s), "objective reduction");
     }
     M.counters[0]++;
 }
@@ -1821,7 +1827,11 @@ void eval_body(Model& M, const exa_eval_args* a, hipStream_t s, bool lag = false
         c.inst = D.inst;
         c.x = a->x;
         switch (mode) {
-            case M_OBJ: c.out0 = nobj == 1 ? a->f : D.tilesum; break;
+            case M_OBJ:
+                c.out0 = nobj == 1 ? a->f : D.tilesum;
+                c.out1 = a->f;
+                c.direct = nobj == 1 ? 0 : 1;
+                break;
             case M_GRAD:
                 c.out0 = M.grad_direct ? a->g : D.fo;
                 c.out1 = a->g;
@@ -1893,7 +1903,7 @@ void eval_body(Model& M, const exa_eval_args* a, hipStream_t s, bool lag = false
             job(D.jt_map, D.fo, a->jtw, a->w);
         }
         if (mask & EXA_EV_HPROD) job(D.h_map, D.hv, a->hv);
-        if ((mask & EXA_EV_OBJ) && nobj != 1) {  // no tiles: the sum of nothing, 0
+        if ((mask & EXA_EV_OBJ) && nobj == 0) {  // no tiles: the sum of nothing, 0
             R.part = D.tilesum;
             R.npart = nobj;
             R.f = a->f;
