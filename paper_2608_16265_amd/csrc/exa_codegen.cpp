@@ -2071,7 +2071,7 @@ __device__ __forceinline__ void exa_ahead(const ExaCall& C, const EXA_K ExaInstD
         mode_cases(M_JTPROD, cases);
         if (own_plan(M, M_HPROD, true)) mode_cases(M_HPROD, cases);
         if (own_plan(M, M_GRAD, true)) mode_cases(M_GRAD, cases);
-        lds = std::max(lds, mode_lds_doubles(M, M_JTPROD));
+        lds = std::max({lds, mode_lds_doubles(M, M_JTPROD), mode_lds_doubles(M, M_HPROD)});
         cases.push_back(zero_case);
         multi_kernel("exa_k_onepass", lds, cases, 0);
     }
