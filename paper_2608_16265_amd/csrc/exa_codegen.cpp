@@ -1731,6 +1731,8 @@ std::string generate_source(const Model& M, std::map<std::pair<int, int>, UnitLi
     os << "// generated: straight-line evaluation kernels for one pattern set\n";
     os << "#define EXA_G __attribute__((address_space(1)))\n#define EXA_K __attribute__((address_space(4)))\n";
     os << EXA_STR(EXA_DEVICE_STRUCTS) << "\n";
+    os << "#define EXA_FN __device__ __forceinline__\n" << EXA_STR(EXA_ARRIVAL) << "\n";
+    os << "#define EXA_COUNT_AT(n) (((n) + 15) & ~15LL)\n";
     os << "static_assert(sizeof(ExaPatDev) == " << sizeof(ExaPatDev) << ", \"layout\");\n";
     os << "static_assert(sizeof(ExaInstDev) == " << sizeof(ExaInstDev) << ", \"layout\");\n";
     os << "static_assert(sizeof(ExaTile) == " << sizeof(ExaTile) << ", \"layout\");\n";
@@ -1862,23 +1864,28 @@ __device__ __forceinline__ int exa_term(int j, int je) { return j < je ? j : (je
 // the order of the reduction kernel (256 lanes over the tiles, then a tree)
 // whichever that is, instead of by a launch of its own.  Each tile's partial
 // sum is stored past this XCD's caches (agent scope) and has arrived, by the
-// wait, when the tile is counted; the workgroup that counts last reads them
-// the same way and clears the count for the next launch.  No workgroup waits
-// for another.  A release or acquire at agent scope would write back and
-// invalidate the XCD's whole L2 for these few words.  f, the gradient and H v
-// of 200,000 variables 17.5 -> 14.3 us, every callback of the 1000 x 1000
-// grid 54.4 -> 53.0.
+// wait, when the tile is counted (exa_arrival); the workgroup that completes
+// the count reads them the same way.  No workgroup waits for another.  A
+// release or acquire at agent scope would write back and invalidate the XCD's
+// whole L2 for these few words.  f, the gradient and H v of 200,000 variables
+// 17.5 -> 14.3 us, every callback of the 1000 x 1000 grid 54.4 -> 53.0.
 __device__ __forceinline__ void exa_obj_finish(const ExaCall& C, long long n, long long slot, double tot, double* lds) {
     __shared__ int last;
     unsigned long long* P = (unsigned long long*)C.out0;
     if (threadIdx.x == 0) {
+        unsigned* count = (unsigned*)(P + EXA_COUNT_AT(n));
+        const ExaArrival a = exa_arrival(slot, n);
         __hip_atomic_store(&P[slot], (unsigned long long)__double_as_longlong(tot), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         __builtin_amdgcn_s_waitcnt(0);
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        const unsigned long long c = __hip_atomic_fetch_add(&P[n], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        last = c + 1 == (unsigned long long)n;
+        unsigned c = __hip_atomic_fetch_add(&count[32 * a.line], a.weight, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = exa_completes(c, a.weight, a.bits);
+        if (last && a.group_bits) {
+            c = __hip_atomic_fetch_add(&count[0], a.group_weight, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last = exa_completes(c, a.group_weight, a.group_bits);
+        }
     }
     __syncthreads();
     if (!last) return;
@@ -1887,15 +1894,20 @@ __device__ __forceinline__ void exa_obj_finish(const ExaCall& C, long long n, lo
 #pragma unroll
     for (int q = 0; q < EXA_VLANES / 64; ++q) {
         if (q * nthr >= EXA_VLANES) break;
-        for (long long i = threadIdx.x + q * nthr; i < n; i += EXA_VLANES)
-            acc[q] += __longlong_as_double(
-                (long long)__hip_atomic_load(&P[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        // eight loads in flight before their additions
+        for (long long i0 = threadIdx.x + q * nthr; i0 < n; i0 += 8 * EXA_VLANES) {
+            unsigned long long v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                v[u] = __hip_atomic_load(&P[i0 + u * EXA_VLANES < n ? i0 + u * EXA_VLANES : n - 1], __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (i0 + u * EXA_VLANES < n) acc[q] += __longlong_as_double((long long)v[u]);
+        }
     }
     const double f = exa_vlane_sum(acc, lds);
-    if (threadIdx.x == 0) {
-        C.out1[0] = f;
-        __hip_atomic_store(&P[n], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (threadIdx.x == 0) C.out1[0] = f;
 }
 // The tables anew: what a round reads from them is not kept in registers over
 // the rounds of a tile.

@@ -424,7 +424,7 @@ int64_t estimate_device_bytes(const Model& M) {
         b += (int64_t)sizeof(ExaTile) * (int64_t)make_tiles(M, mode, 0, tp, fixed ? kObjFused : M.fuse).size();
     }
     const int64_t nobj = (int64_t)make_tiles(M, M_OBJ, 0, (int64_t)kObjBlock * kObjEpl, kObjFused).size();
-    b += 8 * (M.fo_obj_len + M.fo_con_len + M.par_len + M.hv_len + nobj + 1 + M.nvar + 1);
+    b += 8 * (M.fo_obj_len + M.fo_con_len + M.par_len + M.hv_len + count_words(nobj) + M.nvar + 1);
     // inverse tables of strictly increasing columns (at most one per column)
     for (const Group& G : M.groups)
         for (const std::vector<int32_t>& c : M.pats[G.members[0]].icols)
@@ -483,8 +483,8 @@ void build_device(Model& M) {
     D.fo = (double*)D.alloc((M.fo_obj_len + M.fo_con_len) * sizeof(double));
     D.par = (double*)D.alloc(M.par_len * sizeof(double));
     D.hv = (double*)D.alloc(M.hv_len * sizeof(double));
-    // partial sums, and the count of tiles that have stored theirs
-    const std::vector<double> zero(D.sched[M_OBJ].ntiles + 1, 0.0);
+    // partial sums, and the counts of tiles that have stored theirs
+    const std::vector<double> zero(count_words(inst.nobj), 0.0);
     D.tilesum = (double*)D.upload(zero.data(), zero.size() * sizeof(double));
     D.lag_tmp = (double*)D.alloc(M.nvar * sizeof(double));
     D.fval = (double*)D.alloc(sizeof(double));
