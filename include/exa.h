@@ -133,8 +133,8 @@ typedef struct exa_options {
                           memory, no kernel compilation; callbacks then return
                           EXA_ESTATE                                           */
     int32_t block;     /* threads per workgroup: 64, 128 or 256 (0: 256)      */
-    int32_t epl;       /* data points per lane per tile: 1..16 (0: 4); fewer
-                          in launches of under 768 workgroups                 */
+    int32_t epl;       /* data points per lane per tile: 1..16, kept as given
+                          unless epl_most is set (0: 4, with epl_most set)    */
     int32_t autotune;  /* 1: at its first call, each callback times candidate
                           schedules (workgroup size, points per lane, fused or
                           separate patterns) and keeps the fastest; results do
@@ -149,7 +149,9 @@ typedef struct exa_options {
                           them.  Without autotune exa_eval runs one tile per
                           callback, patterns over the same data in one lane,
                           with the block and epl above; results are the same  */
-    int32_t reserved[2];
+    int32_t epl_most;  /* 1: epl is the most a lane takes: launches nobody has
+                          timed halve it while they have under 768 workgroups */
+    int32_t reserved;
     const char* cache_dir; /* directory of the on-disk code-object cache (NULL
                           or "": the environment variable EXA_CACHE_DIR, else
                           no cache).  The compiled code of a pattern set is
@@ -535,8 +537,8 @@ typedef struct exa_batch_options {
                           schedules (workgroup size, points per lane, fused or
                           separate patterns, units) and keep the fastest      */
     int32_t block;     /* schedule without autotune: workgroup size (0: 256)   */
-    int32_t epl;       /*   points per lane 1..16 (0: 4; fewer in launches of
-                            under 768 workgroups)                             */
+    int32_t epl;       /*   points per lane 1..16, kept as given unless
+                            epl_most is set (0: 4, with epl_most set)         */
     int32_t fuse;      /*   1: patterns over the same data arrays share a lane */
     int32_t units;     /*   EXA_UNITS_* (a choice a mask does not allow falls
                             back to the next one down; EXA_UNITS_SEPARATE to
@@ -545,7 +547,8 @@ typedef struct exa_batch_options {
     int32_t xcd_aware; /* 1: instances are split over the 8 XCDs by cost and
                           each XCD takes its instances' tiles (an instance's x
                           stays in that XCD's L2); 0: tiles in instance order  */
-    int32_t reserved;
+    int32_t epl_most;  /* 1: epl is the most a lane takes: a launch nobody has
+                          timed halves it while it has under 768 workgroups    */
 } exa_batch_options;
 
 /* Batched-only selection bits, beside the EXA_EV_* callbacks:

@@ -39,13 +39,13 @@ class PatternDesc(C.Structure):
 class Options(C.Structure):
     _fields_ = [("host_only", C.c_int32), ("block", C.c_int32), ("epl", C.c_int32),
                 ("autotune", C.c_int32), ("fuse", C.c_int32), ("eval_per_mode", C.c_int32),
-                ("reserved", C.c_int32 * 2), ("cache_dir", C.c_char_p), ("max_device_bytes", C.c_int64)]
+                ("epl_most", C.c_int32), ("reserved", C.c_int32), ("cache_dir", C.c_char_p), ("max_device_bytes", C.c_int64)]
 
 
 class BatchOptions(C.Structure):
     _fields_ = [("autotune", C.c_int32), ("block", C.c_int32), ("epl", C.c_int32),
                 ("fuse", C.c_int32), ("units", C.c_int32), ("use_graph", C.c_int32),
-                ("xcd_aware", C.c_int32), ("reserved", C.c_int32)]
+                ("xcd_aware", C.c_int32), ("epl_most", C.c_int32)]
 
 
 class BatchIO(C.Structure):

@@ -28,11 +28,11 @@ _INS = {"x": "x", "y": "y", "v": "x", "w": "y", "wx": "x"}
 class ExaBatch:
     def __init__(self, models: Sequence[ExaModel], *, autotune: bool = True, block: int = 256,
                  epl: int = 4, fuse: bool = True, units: str = "jac_hess", use_graph: bool = True,
-                 xcd_aware: bool = True):
+                 xcd_aware: bool = True, epl_exact: bool = False):
         self.models = list(models)  # the models must outlive the batch
         arr = (C.c_void_p * len(self.models))(*[m.handle.value for m in self.models])
         opt = BatchOptions(1 if autotune else 0, block, epl, 1 if fuse else 0, UNITS[units],
-                           1 if use_graph else 0, 1 if xcd_aware else 0, 0)
+                           1 if use_graph else 0, 1 if xcd_aware else 0, 0 if epl_exact else 1)
         h = C.c_void_p()
         check(LIB.exa_batch_create(arr, len(self.models), C.byref(opt), C.byref(h)))
         self._h = h

@@ -84,6 +84,7 @@ struct exa_batch {
     // options
     bool autotune = true, use_graph = true, xcd_aware = true, fuse = true;
     int block = 256, epl = 4, units = EXA_UNITS_JAC_HESS;
+    bool epl_most = true;
     // per mask: schedule, tile lists, reduction table
     struct Sched {
         int block = 256, epl = 4, units = EXA_UNITS_PER_CALLBACK;
@@ -787,6 +788,7 @@ exa_status exa_batch_create(exa_model* const* models, int32_t B, const exa_batch
             b->autotune = opt->autotune != 0;
             if (opt->block) b->block = opt->block;
             if (opt->epl) b->epl = opt->epl;
+            b->epl_most = !opt->epl || opt->epl_most;
             b->fuse = opt->fuse != 0;
             b->units = opt->units;
             b->use_graph = opt->use_graph != 0;
@@ -1064,7 +1066,7 @@ exa_status exa_batch_eval(exa_batch* b, uint32_t mask, const exa_batch_io* io, e
         auto it = b->sched.find(mask);
         if (it == b->sched.end() || !it->second.tuned) {
             // the options' units
-            const int epl = untimed_epl(b->epl, [&](int e) {
+            const int epl = untimed_epl(b->epl, b->epl_most, [&](int e) {
                 int64_t n = 0;
                 for (size_t c = 0; c < b->classes.size(); ++c) {
                     const Model& M = lead_of(*b, (int)c);

@@ -471,6 +471,7 @@ struct Model {
     bool lag_units = false;  // the Lagrangian gradient runs M_LAG units
     bool host_only = false;
     int block = 256, epl = 4;
+    bool epl_most = true;  // untimed launches may take fewer points per lane than epl
     bool autotune = false, fuse = false;
     bool eval_per_mode = false;  // exa_eval: per-callback tiles only
     std::string signature;   // hash of the simplified trees (shared code)

@@ -406,7 +406,7 @@ void fill_patdev(const Model& M, DeviceState& D, ExaInstDev& inst) {
 
 // Points per lane of callback `mode` under the model's options.
 int option_epl(const Model& M, int mode) {
-    return untimed_epl(M.epl, [&](int e) { return (int64_t)make_tiles(M, mode, 0, (int64_t)M.block * e, M.fuse).size(); });
+    return untimed_epl(M.epl, M.epl_most, [&](int e) { return (int64_t)make_tiles(M, mode, 0, (int64_t)M.block * e, M.fuse).size(); });
 }
 
 int64_t estimate_device_bytes(const Model& M) {
@@ -1530,6 +1530,7 @@ exa_status exa_create(const exa_pattern_desc* pats, int32_t npats, int64_t nvar,
             M.host_only = opt->host_only != 0;
             if (opt->block) M.block = opt->block;
             if (opt->epl) M.epl = opt->epl;
+            M.epl_most = !opt->epl || opt->epl_most;
             M.autotune = opt->autotune != 0;
             M.fuse = opt->fuse != 0;
             M.eval_per_mode = opt->eval_per_mode != 0;
@@ -1938,7 +1939,7 @@ void eval_body(Model& M, const exa_eval_args* a, hipStream_t s, bool lag = false
         // untuned: per-callback tiles (the kind the tuner picks on most
         // models; one-pass units hold many registers), patterns over the
         // same data in one lane
-        const int epl = untimed_epl(M.epl, [&](int e) {
+        const int epl = untimed_epl(M.epl, M.epl_most, [&](int e) {
             int64_t n = 0;
             for (int mode : launch_modes(M, key, EXA_UNITS_PER_CALLBACK))
                 if (mode != M_OBJ) n += (int64_t)make_tiles(M, mode, 0, (int64_t)M.block * e, true).size();

@@ -105,8 +105,8 @@ void launch_mode_untuned(Model& M, int mode, ExaCall call, hipStream_t s);
 // plus one for long segments).
 void segsum(const DevMap& m, const double* buf, double* out, hipStream_t s, const double* w = nullptr);
 exa_status guard_status(const std::function<void()>& f);
-// Points per lane of a launch whose schedule nobody has timed: the options',
-// halved while the launch would have fewer than kFullLaunch workgroups (three
+// Points per lane of a launch whose schedule nobody has timed, where the
+// options leave it open (epl_most, or no epl given): theirs, halved while the launch would have fewer than kFullLaunch workgroups (three
 // per compute unit).  With fewer, a tile's points per lane are a serial chain
 // of loads on a chip that has room for them side by side.  Measured at 256
 // lanes, four points / one point per lane (iterates in turn): 10,000 buses
@@ -117,8 +117,8 @@ exa_status guard_status(const std::function<void()>& f);
 // of the 517 x 517 grid (over 2000) 15.5 / 18.0, 300,000 steps 49.3 / 51.3.
 constexpr int64_t kFullLaunch = 768;
 template <class Tiles>
-int untimed_epl(int epl, const Tiles& tiles) {
-    while (epl > 1 && tiles(epl) < kFullLaunch) epl /= 2;
+int untimed_epl(int epl, bool most, const Tiles& tiles) {
+    while (most && epl > 1 && tiles(epl) < kFullLaunch) epl /= 2;
     return epl;
 }
 // Tiles that write zeros to the gradient entries no objective term touches,

@@ -90,18 +90,21 @@ _F64 = torch.float64
 
 
 class ExaModel:
-    """A compiled model on the current HIP device (Sec. 3.2 ExaModel)."""
+    """A compiled model on the current HIP device (Sec. 3.2 ExaModel).
+
+    epl: points per lane of launches that are not tuned; launches of under 768
+    workgroups take fewer, unless epl_exact is set."""
 
     def __init__(self, model, *, host_only: bool = False, block: int = 256, epl: int = 4,
                  autotune: bool = False, fuse: bool = False, eval_per_mode: bool = False,
-                 cache_dir: str = None, max_device_bytes: int = 0):
+                 cache_dir: str = None, max_device_bytes: int = 0, epl_exact: bool = False):
         self.description = model
         desc = _Descriptors(model)
         xl = np.ascontiguousarray(model.xl, dtype=np.float64)
         xu = np.ascontiguousarray(model.xu, dtype=np.float64)
         th = np.ascontiguousarray(model.theta, dtype=np.float64)
         opt = Options(1 if host_only else 0, block, epl, 1 if autotune else 0, 1 if fuse else 0,
-                      1 if eval_per_mode else 0)
+                      1 if eval_per_mode else 0, 0 if epl_exact else 1)
         opt.cache_dir = cache_dir.encode() if cache_dir else None
         opt.max_device_bytes = int(max_device_bytes)
         h = C.c_void_p()
