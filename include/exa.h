@@ -166,7 +166,10 @@ typedef struct exa_options {
                           exa_create fails with EXA_ENOMEM when the footprint
                           estimated after the host analysis (see
                           exa_device_bytes) exceeds it, or when an allocation
-                          would take the model past it                     */
+                          would take the model past it.  Where only the lists
+                          and tables of the kernels that finish sums
+                          themselves do not fit, the model does without them
+                          (sums through the maps: the same values, slower) */
 } exa_options;
 
 /* ---- Library ------------------------------------------------------------ */
@@ -487,7 +490,8 @@ exa_status exa_pattern_info(const exa_model* m, int32_t p, int64_t* out8);
 
 /* Device memory of a model in bytes: what it holds (device models) or the
  * footprint estimated from the host analysis (host-only models: data
- * columns, tables, work buffers, reduction maps), into *bytes. */
+ * columns, tables, work buffers, reduction maps, with or without what the
+ * kernels that finish sums need, whichever is more), into *bytes. */
 exa_status exa_device_bytes(const exa_model* m, int64_t* bytes);
 /* Build statistics of a model (Sec. 8.6 compilation study), host array
  * out6 = {host analysis ms, code generation ms, compilation ms (or cache

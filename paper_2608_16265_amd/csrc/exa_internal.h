@@ -467,6 +467,10 @@ struct Model {
     // whose instances' plans differ, use the general maps and units)
     OwnPlan own[SUM_COUNT];
     bool use_own = false;
+    // a device-memory budget left no room for what finishing units need beside
+    // the buffers: every sum goes through its map, objectives of several tiles
+    // through the reduction launch
+    bool lean = false;
     std::string own_sig;     // what the plans fix in the generated code
     bool lag_units = false;  // the Lagrangian gradient runs M_LAG units
     bool host_only = false;
@@ -509,6 +513,25 @@ bool same_walk(const Model& M, int a, int b);
 
 // exa_owner.cpp
 void plan_sums(Model& M);
+// No sums finished by units (Model::lean).
+void drop_plans(Model& M);
+// Every source that a unit pulls from or counts its variables by.
+template <class F>
+void each_source(const OwnUnit& U, F&& f) {
+    for (const std::vector<OwnSrc>* v : {&U.srcs, &U.grad})
+        for (const OwnSrc& x : *v) f(x);
+    for (const OwnUnit::Out& o : U.outs)
+        for (const std::vector<OwnSrc>* v : {&o.before, &o.after, &o.grad})
+            for (const OwnSrc& x : *v) f(x);
+    for (const OwnChain& c : U.chains) {
+        OwnSrc top;
+        top.group = U.group;
+        top.ref = c.top;
+        f(top);
+        for (const std::vector<OwnSrc>* v : {&c.before, &c.after, &c.grad})
+            for (const OwnSrc& x : *v) f(x);
+    }
+}
 // The map of a sum: with own, of the variables the plan's units leave to the
 // reduction; without, of every variable.
 void sum_map(const Model& M, SumKind s, bool own, SegMap& out);
@@ -548,8 +571,11 @@ constexpr int64_t kIdentMin = 64;
 constexpr bool kObjFused = true;
 void build_device(Model& M);
 // Device memory a model needs (data columns, tables, work buffers, maps),
-// estimated from the host analysis before anything is allocated.
-int64_t estimate_device_bytes(const Model& M);
+// estimated from the host analysis before anything is allocated: as it is, or
+// lean (Model::lean).
+int64_t estimate_device_bytes(Model& M, bool lean);
+// The larger of the two, which any budget has room for.
+int64_t estimate_device_bytes(Model& M);
 
 }  // namespace exa
 

@@ -720,6 +720,18 @@ void plan_sums(Model& M) {
     M.own_sig = os.str();
 }
 
+void drop_plans(Model& M) {
+    const bool grad = M.use_own && M.own[SUM_GRAD].on;
+    for (OwnPlan& p : M.own) p = OwnPlan();
+    M.use_own = M.lag_units = false;
+    M.lean = true;
+    M.epl_most = false;
+    M.own_sig = "0-1-2-";
+    sum_map(M, SUM_JT, false, M.jt_map);
+    sum_map(M, SUM_HV, false, M.h_map);
+    if (grad) sum_map(M, SUM_GRAD, false, M.grad_map);
+}
+
 const OwnPlan* own_plan(const Model& M, int mode, bool own) {
     if (!own) return nullptr;
     const OwnPlan* p = mode == M_JTPROD || mode == M_LAG || mode == M_GRADL ? &M.own[SUM_JT]

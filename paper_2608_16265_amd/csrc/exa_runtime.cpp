@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <chrono>
+#include <cstddef>
 #include <functional>
 #include <map>
 #include <mutex>
@@ -326,11 +327,7 @@ void fill_own(const Model& M, DeviceState& D, ExaInstDev& inst) {
     for (int k = 0; k < SUM_COUNT; ++k)
         for (const OwnUnit& U : M.own[k].units) {
             if (U.lgroup >= 0) {
-                for (const OwnUnit::Out& o : U.outs) {
-                    inst.vlo[k][o.vunit] = o.lo;
-                    for (const std::vector<OwnSrc>* v : {&o.before, &o.after, &o.grad})
-                        for (const OwnSrc& x : *v) source(x);
-                }
+                for (const OwnUnit::Out& o : U.outs) inst.vlo[k][o.vunit] = o.lo;
                 // J^T w and H v over the same lists share them
                 if (k == SUM_HV)
                     for (const OwnUnit& J : M.own[SUM_JT].units)
@@ -349,16 +346,7 @@ void fill_own(const Model& M, DeviceState& D, ExaInstDev& inst) {
                 d.runl[k] = (int)U.runl;
                 d.nrun[k] = (int)U.nrun;
             }
-            for (const std::vector<OwnSrc>* v : {&U.srcs, &U.grad})
-                for (const OwnSrc& x : *v) source(x);
-            for (const OwnChain& c : U.chains) {
-                OwnSrc top;
-                top.group = U.group;
-                top.ref = c.top;
-                source(top);
-                for (const std::vector<OwnSrc>* v : {&c.before, &c.after, &c.grad})
-                    for (const OwnSrc& x : *v) source(x);
-            }
+            each_source(U, source);
         }
 }
 
@@ -409,36 +397,80 @@ int option_epl(const Model& M, int mode) {
     return untimed_epl(M.epl, M.epl_most, [&](int e) { return (int64_t)make_tiles(M, mode, 0, (int64_t)M.block * e, M.fuse).size(); });
 }
 
-int64_t estimate_device_bytes(const Model& M) {
-    int64_t b = 0;
+// A model's instance table holds the patterns it has.
+int64_t inst_bytes(const Model& M) {
+    return (int64_t)offsetof(ExaInstDev, pat) + (int64_t)std::max<size_t>(1, M.pats.size()) * (int64_t)sizeof(ExaPatDev);
+}
+
+// Partial sums of the objective's tiles, with the counts of those that have
+// stored theirs.
+int64_t tilesum_words(const Model& M, int64_t nobj) { return M.lean ? std::max<int64_t>(1, nobj) : count_words(nobj); }
+
+int64_t estimate_device_bytes(Model& M) {
+    const int64_t lean = estimate_device_bytes(M, true);
+    return M.lean ? lean : std::max(lean, estimate_device_bytes(M, false));
+}
+
+int64_t estimate_device_bytes(Model& M, bool lean) {
+    // a host-only model holds the general maps; the device model it stands for
+    // has those of its plans
+    struct Restore {
+        Model& M;
+        const bool own, was_lean, most;
+        ~Restore() { M.use_own = own, M.lean = was_lean, M.epl_most = most; }
+    } held{M, M.use_own, M.lean, M.epl_most};
+    M.use_own = !lean;
+    M.lean = lean;
+    M.epl_most = M.epl_most && !lean;
+    int64_t b = 8 * 64;  // empty arrays take a word each
     for (const Group& G : M.groups) {
         const Pattern& P = M.pats[G.members[0]];
-        b += P.ndata * (4 * (int64_t)P.n_icols + 8 * (int64_t)P.n_fcols);
+        b += 8 * (int64_t)(P.n_icols + P.n_fcols) + P.ndata * (4 * (int64_t)P.n_icols + 8 * (int64_t)P.n_fcols);
     }
     for (const Pattern& P : M.pats)
         if (P.kind == EXA_AUG) b += 4 * (int64_t)(P.rptr.size() + P.ridx.size());
-    b += 8 * M.ntheta + (int64_t)sizeof(ExaInstDev);
+    b += 8 * M.ntheta + inst_bytes(M);
     for (int mode = 0; mode < M_COUNT; ++mode) {
         const bool fixed = mode == M_OBJ;
         const int64_t tp = fixed ? (int64_t)kObjBlock * kObjEpl : (int64_t)M.block * option_epl(M, mode);
         b += (int64_t)sizeof(ExaTile) * (int64_t)make_tiles(M, mode, 0, tp, fixed ? kObjFused : M.fuse).size();
     }
     const int64_t nobj = (int64_t)make_tiles(M, M_OBJ, 0, (int64_t)kObjBlock * kObjEpl, kObjFused).size();
-    b += 8 * (M.fo_obj_len + M.fo_con_len + M.par_len + M.hv_len + count_words(nobj) + M.nvar + 1);
-    // inverse tables of strictly increasing columns (at most one per column)
-    for (const Group& G : M.groups)
-        for (const std::vector<int32_t>& c : M.pats[G.members[0]].icols)
-            if (!c.empty() && c.back() > c.front()) b += 4 * ((int64_t)c.back() - c.front() + 1);
-    // incidence lists
-    for (int k : {(int)SUM_JT, (int)SUM_HV})
-        for (const OwnUnit& U : M.own[k].units) b += 4 * (int64_t)(U.lptr.size() + U.lent.size());
-    // maps: pointers and positions, plus at most a 24-byte record per four
-    // entries (chunked sums, with padding) and part sums
-    for (const SegMap* S : {&M.grad_map, &M.jt_map, &M.h_map, &M.par_map}) {
-        const int64_t nnz = (int64_t)S->idx.size();
-        b += 8 * (S->nseg() + 1) + 8 * nnz + 8 * nnz + 24 * 256 + 8 * (nnz / kExaLongSeg + 1);
-    }
-    return b;
+    b += 8 * (M.fo_obj_len + M.fo_con_len + M.par_len + M.hv_len + tilesum_words(M, nobj) + M.nvar + 1);
+    // inverse tables, one per column, and incidence lists, one for J^T w and
+    // H v over the same (as fill_own uploads them)
+    std::map<std::pair<int, int>, int64_t> inverse;
+    for (int k = 0; k < SUM_COUNT && !lean; ++k)
+        for (const OwnUnit& U : M.own[k].units) {
+            each_source(U, [&](const OwnSrc& s) {
+                if (s.how != OWN_INVERSE) return;
+                const Group& G = M.groups[s.group];
+                const int col = G.vrefs[s.ref].col;
+                const std::vector<int32_t>& c = M.pats[G.members[0]].icols[col];
+                inverse[{s.group, col}] = 4 * ((int64_t)c.back() - c.front() + 1);
+            });
+            const auto same = [&](const OwnUnit& J) { return J.lgroup >= 0 && J.lptr == U.lptr && J.lent == U.lent; };
+            const std::vector<OwnUnit>& jt = M.own[SUM_JT].units;
+            if (U.lgroup >= 0 && (k != SUM_HV || std::none_of(jt.begin(), jt.end(), same)))
+                b += 4 * (int64_t)(U.lptr.size() + U.lent.size());
+        }
+    for (auto& t : inverse) b += t.second;
+    // maps: pointers and positions, plus where sums are chunked at most a
+    // 24-byte record per four entries, with padding, and part sums
+    auto map_bytes = [&](const SegMap& S) {
+        const int64_t nnz = (int64_t)S.idx.size();
+        int64_t longest = 0;
+        for (int64_t s = 0; s < S.nseg(); ++s) longest = std::max(longest, S.ptr[s + 1] - S.ptr[s]);
+        return 8 * (S.nseg() + 1) + 16 * nnz + (longest > 2 * kExaChunk ? 24 * 256 : 0) + 8 * (nnz / kExaLongSeg + 1);
+    };
+    auto sum_bytes = [&](SumKind k, const SegMap& S) {
+        if (held.own == M.use_own || !M.own[k].on) return map_bytes(S);
+        SegMap other;
+        sum_map(M, k, M.use_own, other);
+        return map_bytes(other);
+    };
+    return b + sum_bytes(SUM_GRAD, M.grad_map) + sum_bytes(SUM_JT, M.jt_map) + sum_bytes(SUM_HV, M.h_map) +
+           map_bytes(M.par_map);
 }
 
 void build_device(Model& M) {
@@ -470,7 +502,7 @@ void build_device(Model& M) {
     inst.off[EXA_OFF_FO_CON] = M.fo_obj_len;
     inst.nobj = (int64_t)make_tiles(M, M_OBJ, 0, (int64_t)kObjBlock * kObjEpl, kObjFused).size();
     D.inst_host = inst;
-    D.inst = (ExaInstDev*)D.upload(&inst, sizeof inst);
+    D.inst = (ExaInstDev*)D.upload(&inst, inst_bytes(M));
 
     for (int mode = 0; mode < M_COUNT; ++mode) {
         // the objective keeps one fixed schedule, so that its reduction order
@@ -484,7 +516,7 @@ void build_device(Model& M) {
     D.par = (double*)D.alloc(M.par_len * sizeof(double));
     D.hv = (double*)D.alloc(M.hv_len * sizeof(double));
     // partial sums, and the counts of tiles that have stored theirs
-    const std::vector<double> zero(count_words(inst.nobj), 0.0);
+    const std::vector<double> zero(tilesum_words(M, inst.nobj), 0.0);
     D.tilesum = (double*)D.upload(zero.data(), zero.size() * sizeof(double));
     D.lag_tmp = (double*)D.alloc(M.nvar * sizeof(double));
     D.fval = (double*)D.alloc(sizeof(double));
@@ -1545,13 +1577,27 @@ exa_status exa_create(const exa_pattern_desc* pats, int32_t npats, int64_t nvar,
         build_host(M, pats, npats);
         M.host_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         if (M.max_device_bytes > 0) {
-            const int64_t need = estimate_device_bytes(M);
+            // what was added for speed is given up first: shorter tiles, then
+            // what the units that finish sums need beside the buffers
+            if (estimate_device_bytes(M, false) > M.max_device_bytes) M.epl_most = false;
+            if (!M.epl_most && estimate_device_bytes(M, false) > M.max_device_bytes) drop_plans(M);
+            const int64_t need = M.lean ? estimate_device_bytes(M, true) : 0;
             if (need > M.max_device_bytes)
                 fail(EXA_ENOMEM, "the model needs about " + std::to_string(need) +
                                      " bytes of device memory, more than its budget of " +
                                      std::to_string(M.max_device_bytes));
         }
-        if (!M.host_only) build_device(M);
+        if (!M.host_only) {
+            try {
+                build_device(M);
+            } catch (const Error& e) {
+                if (e.code != EXA_ENOMEM || M.max_device_bytes == 0 || M.lean) throw;
+                M.dev.reset();
+                M.live.clear();
+                drop_plans(M);
+                build_device(M);
+            }
+        }
         if (log_on()) {
             char buf[400];
             std::snprintf(buf, sizeof buf,
@@ -1637,8 +1683,17 @@ void obj_body(Model& M, const double* x, double* f, hipStream_t s) {
         c.x = x;
         c.out0 = one ? f : D.tilesum;
         c.out1 = f;
-        c.direct = one ? 0 : 1;
+        c.direct = one || M.lean ? 0 : 1;
         launch_mode(M, M_OBJ, c, s);
+        if (!one && M.lean) {
+            ExaReduce R;
+            std::memset(&R, 0, sizeof R);
+            R.ep_job = -1;
+            R.part = D.tilesum;
+            R.npart = D.sched[M_OBJ].ntiles;
+            R.f = f;
+            hip_check(exa_launch_reduce(R, s), "objective sum");
+        }
     }
     M.counters[0]++;
 }
@@ -1845,7 +1900,7 @@ void eval_body(Model& M, const exa_eval_args* a, hipStream_t s, bool lag = false
             case M_OBJ:
                 c.out0 = nobj == 1 ? a->f : D.tilesum;
                 c.out1 = a->f;
-                c.direct = nobj == 1 ? 0 : 1;
+                c.direct = nobj == 1 || M.lean ? 0 : 1;
                 break;
             case M_GRAD:
                 c.out0 = M.grad_direct ? a->g : D.fo;
@@ -1918,7 +1973,7 @@ void eval_body(Model& M, const exa_eval_args* a, hipStream_t s, bool lag = false
             job(D.jt_map, D.fo, a->jtw, a->w);
         }
         if (mask & EXA_EV_HPROD) job(D.h_map, D.hv, a->hv);
-        if ((mask & EXA_EV_OBJ) && nobj == 0) {  // no tiles: the sum of nothing, 0
+        if ((mask & EXA_EV_OBJ) && (nobj == 0 || (nobj > 1 && M.lean))) {  // no tiles: the sum of nothing, 0
             R.part = D.tilesum;
             R.npart = nobj;
             R.f = a->f;
@@ -2235,7 +2290,7 @@ exa_status exa_compile_check(const exa_model* m) {
 exa_status exa_device_bytes(const exa_model* m, int64_t* bytes) {
     return guard([&] {
         if (!m || !bytes) fail(EXA_EINVAL, "null argument");
-        *bytes = m->impl.dev ? m->impl.dev->allocated : estimate_device_bytes(m->impl);
+        *bytes = m->impl.dev ? m->impl.dev->allocated : estimate_device_bytes(const_cast<exa_model*>(m)->impl);
     });
 }
 
@@ -2247,7 +2302,7 @@ exa_status exa_build_info(const exa_model* m, double* out6) {
         out6[1] = M.codegen_ms;
         out6[2] = M.compile_ms;
         out6[3] = M.host_only ? -1.0 : M.module_shared ? 2.0 : M.cache_hit ? 1.0 : 0.0;
-        out6[4] = (double)(M.dev ? M.dev->allocated : estimate_device_bytes(M));
+        out6[4] = (double)(M.dev ? M.dev->allocated : estimate_device_bytes(const_cast<exa_model*>(m)->impl));
         out6[5] = M.cache_dir.empty() ? 0.0 : 1.0;
     });
 }
