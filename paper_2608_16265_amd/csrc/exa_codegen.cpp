@@ -1547,6 +1547,9 @@ std::string own_hunit(const Model& M, int mode, const OwnUnit& U, int sum, int& 
     os << "    }\n}\n";
     record_live(M, members, L, names, live);
     live.outputs += (int64_t)(U.bufrefs.size() + U.direct.size() + U.chains.size());
+    for (const OwnChain& c : U.chains)
+        for (const std::vector<OwnSrc>* v : {&c.before, &c.after})
+            for (const OwnSrc& s : *v) live.extra += s.how == OWN_INVERSE ? 4 : 0;
     return os.str();
 }
 

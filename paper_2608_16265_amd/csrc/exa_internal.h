@@ -389,7 +389,7 @@ struct OwnSrc {
     int how = 0;             // OWN_AFFINE, OWN_INVERSE or OWN_LIST
     int wread = -1;          // augmentation pattern whose +-w[row] this is
     int pat = -1;            // objective pattern (gradient contributions)
-    bool sparse = false;     // hits under three quarters of the unit's variables: behind a branch
+    bool sparse = false;     // contributes to under three quarters of the unit's variables: behind a branch
 };
 constexpr int OWN_AFFINE = 0, OWN_INVERSE = 1, OWN_LIST = 2;
 constexpr int kOwnWaves = 4;

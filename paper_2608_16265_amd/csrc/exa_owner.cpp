@@ -38,6 +38,15 @@ constexpr int kListSpread = 8;
 // and 9.7 / 8.4 (the reduction reads a quarter); a trajectory of 10,000 steps,
 // every callback 9.4 / 8.1.  1024 and 4096 runs of four: J^T w 22.7 and 24.5.
 constexpr int64_t kMaxRuns = 2048;
+// A column with gaps costs the unit that pulls through it one 4-byte table
+// entry per variable it spans, in memory and in every launch, however few points
+// it has.  A cluster is left to the map when these come to more than the map's own
+// pointer per variable and kEntryBytes per contribution.  Measured on a chain
+// of two references over 1,000,000 variables beside k data sets of two far
+// points each, units / map: J^T w k = 1 8.3 / 15.7 us, 3 12.7 / 15.7, 9
+// 24.6 / 15.7 (2 us a table: equal at 4.7), and 25 with every pull evaluated
+// in full 252 / 15.7.
+constexpr int64_t kEntryBytes = 6;
 // Doubles a workgroup holds for its waves' partial sums.
 constexpr int kMaxPartials = 2048;
 
@@ -177,11 +186,28 @@ int weight_nodes(const Model& M, const std::vector<Src>& v) {
 }
 
 // A source as one unit over variables lo..hi pulls it.
-OwnSrc within(const Src& x, int64_t lo, int64_t hi) {
+OwnSrc within(const Model& M, const Src& x, int64_t lo, int64_t hi) {
     OwnSrc s = x.s;
-    const int64_t hit = std::min(hi, x.hi) - std::max(lo, x.lo) + 1;
+    int64_t hit = std::min(hi, x.hi) - std::max(lo, x.lo) + 1;
+    if (s.how == OWN_INVERSE) {
+        const RefKey& k = M.groups[s.group].vrefs[s.ref];
+        const std::vector<int32_t>& c = col_of(M, M.groups[s.group], k.col);
+        hit = std::upper_bound(c.begin(), c.end(), hi - k.off) - std::lower_bound(c.begin(), c.end(), lo - k.off);
+    }
     s.sparse = 4 * hit < 3 * (hi - lo + 1);
     return s;
+}
+
+// Whether the tables a cluster's sources need are worth it (kEntryBytes).
+bool tables_pay(const Model& M, const Cluster& c) {
+    int64_t entries = 0, table = 0;
+    std::map<std::pair<int, int>, int64_t> span;  // a column's references share its table
+    for (const Src& x : c.src) entries += M.groups[x.s.group].ndata;
+    for (const std::vector<Src>* v : {&c.src, &c.grad})
+        for (const Src& x : *v)
+            if (x.s.how == OWN_INVERSE) span[{x.s.group, M.groups[x.s.group].vrefs[x.s.ref].col}] = x.hi - x.lo + 1;
+    for (auto& t : span) table += 4 * t.second;
+    return table <= 4 * (c.hi - c.lo + 1) + kEntryBytes * entries;
 }
 
 // The chains of host group g over a cluster, or none when g cannot host it.
@@ -226,11 +252,11 @@ std::vector<OwnChain> host_chains(const Model& M, const Cluster& C, int g, SumKi
         for (const Src& x : others)
             if (x.lo <= dom[i].second && x.hi >= dom[i].first) {
                 const int there = s == SUM_GRAD ? x.s.pat : x.s.group;
-                (there < here ? out[i].before : out[i].after).push_back(within(x, dom[i].first, dom[i].second));
+                (there < here ? out[i].before : out[i].after).push_back(within(M, x, dom[i].first, dom[i].second));
             }
         for (const Src& x : C.grad)
             if (x.lo <= dom[i].second && x.hi >= dom[i].first)
-                out[i].grad.push_back(within(x, dom[i].first, dom[i].second));
+                out[i].grad.push_back(within(M, x, dom[i].first, dom[i].second));
     }
     return out;
 }
@@ -322,8 +348,8 @@ OwnUnit list_unit(const Model& M, const Cluster& C, SumKind s, std::vector<OwnUn
     U.lptr = same->lptr;
     U.lent = same->lent;
     order_pulled(others, s);
-    for (const Src& x : others) (x.s.group < g ? o.before : o.after).push_back(within(x, C.lo, C.hi));
-    for (const Src& x : C.grad) o.grad.push_back(within(x, C.lo, C.hi));
+    for (const Src& x : others) (x.s.group < g ? o.before : o.after).push_back(within(M, x, C.lo, C.hi));
+    for (const Src& x : C.grad) o.grad.push_back(within(M, x, C.lo, C.hi));
     U.outs.push_back(o);
     U.lgroup = g;
     return U;
@@ -453,7 +479,7 @@ void plan_one(Model& M, SumKind s, const std::vector<std::vector<char>>& inc,
         for (size_t i = 0; i < cl.size(); ++i) {
             Cluster& c = cl[i];
             if (!c.ok) continue;
-            if (weight_nodes(M, c.grad) > kHostPullNodes) {
+            if (weight_nodes(M, c.grad) > kHostPullNodes || !tables_pay(M, c)) {
                 c.ok = false;
                 continue;
             }
@@ -596,8 +622,8 @@ void plan_one(Model& M, SumKind s, const std::vector<std::vector<char>>& inc,
         U.n = cl[i].hi - cl[i].lo + 1;
         std::vector<Src> v = cl[i].src;
         order_pulled(v, s);
-        for (const Src& x : v) U.srcs.push_back(within(x, cl[i].lo, cl[i].hi));
-        for (const Src& x : cl[i].grad) U.grad.push_back(within(x, cl[i].lo, cl[i].hi));
+        for (const Src& x : v) U.srcs.push_back(within(M, x, cl[i].lo, cl[i].hi));
+        for (const Src& x : cl[i].grad) U.grad.push_back(within(M, x, cl[i].lo, cl[i].hi));
         plan.units.push_back(U);
     }
     // lists: clusters with the same ones share a unit (a bus's angle and magnitude)

@@ -1,0 +1,65 @@
+"""Which sums the evaluation units take over, read from the generated source
+of host-only models ("sums finished by units: ..."): values alone cannot tell,
+since the reduction gives the same ones."""
+import re
+
+import numpy as np
+import pytest
+
+from exa_modeling import DataSet, Model, sin
+from paper_2608_16265_amd import ExaModel
+
+JT, HV, GRAD = range(3)
+
+
+def plan(m):
+    """Per sum the text of its units (empty: every sum goes through the map)."""
+    line = ExaModel(m, host_only=True).generated_source().split("// sums finished by units: ")[1].split("\n")[0]
+    parts = re.split(r"[012][+-]L?", line)[1:]
+    assert len(parts) == 3, line
+    return parts
+
+
+def sources(text):
+    """(data set, reference, how, sparse) of every pulled source; how 0: counted
+    from the variable, 1: through an inverse table."""
+    return [(int(g), int(r), int(h), bool(s))
+            for g, r, h, s in re.findall(r"(\d+)\.(\d+)\.(\d+)\.-?\d+\.-?\d+(s?),", text)]
+
+
+def edges(n, k):
+    """A chain over n variables beside k data sets of two points each."""
+    m = Model("edges")
+    x = m.add_var(n)
+    d = DataSet(n - 1, i=np.arange(n - 1))
+    m.add_con(sin(x[d.i] * x[d.i + 1]), d)
+    for j in range(k):
+        e = DataSet(2, i=np.array([j, n - 1 - j]))
+        m.add_con(sin(x[e.i]), e)
+    return m
+
+
+@pytest.mark.parametrize("k,pulled", [(1, True), (4, True), (5, False)])
+def test_few_far_points_are_pulled_behind_a_branch(k, pulled):
+    for text in plan(edges(10_000, k))[:2]:
+        assert len(sources(text)) == (k if pulled else 0), text
+        assert all(s[2:] == (1, True) for s in sources(text)), text
+
+
+def test_tables_for_a_few_points_are_bounded():
+    """25 tables of 100,000 entries for 50 points: their variables, and the
+    chain they lie on, stay in the map; the code and the footprint stay small."""
+    few, many = edges(100_000, 2), edges(100_000, 25)
+    assert not any(sources(t) for t in plan(many))
+    a, b = (ExaModel(m, host_only=True) for m in (few, many))
+    assert len(b.generated_source()) < 8 * len(a.generated_source())
+    assert b.device_bytes() < 1.2 * a.device_bytes()
+
+
+def test_gaps_that_pay_keep_their_table():
+    n = 1000
+    m = Model("gaps")
+    x = m.add_var(4 * n)
+    d = DataSet(n, i=np.arange(n) * 3)
+    m.add_con(sin(x[d.i]), d)
+    assert sources(plan(m)[JT]) == [(0, 0, 1, True)]
