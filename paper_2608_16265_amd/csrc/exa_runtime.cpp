@@ -1994,19 +1994,37 @@ void eval_body(Model& M, const exa_eval_args* a, hipStream_t s, bool lag = false
         // untuned: per-callback tiles (the kind the tuner picks on most
         // models; one-pass units hold many registers), patterns over the
         // same data in one lane
-        const int epl = untimed_epl(M.epl, M.epl_most, [&](int e) {
-            int64_t n = 0;
-            for (int mode : launch_modes(M, key, EXA_UNITS_PER_CALLBACK))
-                if (mode != M_OBJ) n += (int64_t)make_tiles(M, mode, 0, (int64_t)M.block * e, true).size();
-            return n;
-        });
-        set_multi_schedule(M, key, M.block, epl, true, EXA_UNITS_PER_CALLBACK);
+        auto untuned = [&](uint32_t k) {
+            const int epl = untimed_epl(M.epl, M.epl_most, [&](int e) {
+                int64_t n = 0;
+                for (int mode : launch_modes(M, k, EXA_UNITS_PER_CALLBACK))
+                    if (mode != M_OBJ) n += (int64_t)make_tiles(M, mode, 0, (int64_t)M.block * e, true).size();
+                return n;
+            });
+            set_multi_schedule(M, k, M.block, epl, true, EXA_UNITS_PER_CALLBACK);
+        };
+        untuned(key);
         if (M.autotune)
             tune_multi(M, key, mc, s, [&]() {
                 raw_launch_multi(M, key, mc, s);
                 hip_check(exa_launch_reduce(reduce_of(), s), "exa_eval reductions");
             });
         D.multi[key].tuned = true;
+        // exa_lag_grad and exa_eval of the gradient and J^T w are one selection:
+        // the first of either prepares both, so that the other may be captured
+        const uint32_t twin = key ^ EXA_EV_LAG;
+        if (M.lag_units && mask == (EXA_EV_GRAD | EXA_EV_JTPROD) && !D.multi[twin].tuned) {
+            try {
+                const DeviceState::MultiSched S = D.multi[key];
+                if (M.autotune)
+                    set_multi_schedule(M, twin, S.block, S.epl, S.fused, S.units);
+                else
+                    untuned(twin);
+                D.multi[twin].tuned = true;
+            } catch (const Error&) {
+                D.multi.erase(twin);  // no room for it now: at its own first call
+            }
+        }
     }
     DeviceState::EvalTiming& Tm = D.timing;
     const bool timed = Tm.on && Tm.used < (int64_t)Tm.reduced.size();
