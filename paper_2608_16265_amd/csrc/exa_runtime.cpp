@@ -2033,7 +2033,8 @@ void eval_body(Model& M, const exa_eval_args* a, hipStream_t s, bool lag = false
     raw_launch_multi(M, key, mc, s);
     if (timed) hip_check(hipEventRecord(ev[1], s), "hipEventRecord");
     const ExaReduce R = reduce_of();
-    const bool reduce = R.njobs > 0 || R.part;
+    bool reduce = R.part || R.ax_out;  // anything to launch: a job may hold no segment
+    for (int k = 0; k < R.njobs; ++k) reduce = reduce || exa_job_blocks(R.job[k]) > 0;
     if (timed && reduce) hip_check(hipEventRecord(ev[2], s), "hipEventRecord");
     hip_check(exa_launch_reduce(R, s), "exa_eval reductions");
     if (timed && reduce) hip_check(hipEventRecord(ev[3], s), "hipEventRecord");
