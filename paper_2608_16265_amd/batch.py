@@ -113,13 +113,14 @@ class ExaBatch:
 
     def bind(self, x, y=None, obj_weight=1.0, v=None, w=None, wx=None, **outs):
         """A zero-argument callable evaluating the given outputs at fixed
-        tensors (the ctypes record is built once)."""
+        tensors (the ctypes record is built once).  It keeps the batch and the
+        tensors alive."""
         io, mask = self._io(x, y, obj_weight, v, w, wx, outs)
         keep = (x, y, v, w, wx, outs)
-        fn, h, dev = LIB.exa_batch_eval, self._h, x.get_device()
+        fn, dev = LIB.exa_batch_eval, x.get_device()
 
         def call():
-            check(fn(h, mask, C.byref(io), _stream(dev)))
+            check(fn(self._h, mask, C.byref(io), _stream(dev)))
         call._keep = keep
         return call
 
