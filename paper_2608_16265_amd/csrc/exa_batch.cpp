@@ -106,6 +106,15 @@ struct exa_batch {
             std::vector<Part> parts;
         };
         std::vector<Launch> launch;
+        // what a launch reads ahead of each instance, kept while the tuner tries
+        // tile sizes (which it does not depend on)
+        struct AheadOf {
+            int cls;
+            std::vector<int> modes;
+            bool tagged, fused;
+            std::vector<std::vector<ExaTile>> of;  // empty: the launch does not read ahead
+        };
+        std::vector<AheadOf> ahead;
         int64_t tuned_ns = 0;
         ExaBatchJob* jobs = nullptr;
         int32_t* blocks = nullptr;
@@ -301,27 +310,38 @@ int64_t instance_outputs(const exa_batch& b, int i, const std::vector<ExaTile>& 
     return total;
 }
 
+// The tiles that read each instance's inputs in a launch of class c that reads
+// ahead (reads_ahead); none otherwise.
+const std::vector<std::vector<ExaTile>>& ahead_of(const exa_batch& b, exa_batch::Sched& S, int c,
+                                                  const std::vector<std::vector<ExaTile>>& per,
+                                                  const std::vector<int>& modes, bool tagged) {
+    for (const auto& k : S.ahead)
+        if (k.cls == c && k.modes == modes && k.tagged == tagged && k.fused == S.fused) return k.of;
+    S.ahead.push_back({c, modes, tagged, S.fused, {}});
+    std::vector<std::vector<ExaTile>>& of = S.ahead.back().of;
+    int64_t in = 0, written = 0;
+    if (tagged || mode_reads_ahead(modes[0]))
+        for (int i : b.classes[c].inst) written += instance_outputs(b, i, per[i], modes, tagged);
+    if (!reads_ahead(0, written)) return of;
+    of.resize(b.B);
+    for (int i : b.classes[c].inst) in += ahead_tiles(b, i, per[i], modes, tagged, of[i]);
+    if (!reads_ahead(in, written)) of.clear();
+    return of;
+}
+
 // Bin j's tiles, then bin j+1's, each bin padded with no-op tiles to the
 // longest, so that XCD j (workgroups w with w % 8 == j) takes exactly bin j.
-// In a launch that reads ahead (reads_ahead), each instance's inputs are read
+// In a launch that reads ahead, each instance's inputs are read
 // (EXA_AHEAD_TILE) while the instance before it in the bin runs.
-ExaTile* upload_binned(exa_batch& b, const exa_batch::Sched& S, std::vector<std::vector<ExaTile>>& per,
+ExaTile* upload_binned(exa_batch& b, exa_batch::Sched& S, int c, std::vector<std::vector<ExaTile>>& per,
                        const std::vector<int>& modes, bool tagged, int64_t& n) {
-    std::vector<std::vector<ExaTile>> ahead_of(b.B);
-    int64_t in = 0, written = 0;
-    for (int i = 0; i < b.B; ++i) written += instance_outputs(b, i, per[i], modes, tagged);
-    if (!tagged && !mode_reads_ahead(modes[0])) written = 0;
-    if (reads_ahead(0, written))
-        for (int i = 0; i < b.B; ++i) in += ahead_tiles(b, i, per[i], modes, tagged, ahead_of[i]);
+    const std::vector<std::vector<ExaTile>>& ahead = ahead_of(b, S, c, per, modes, tagged);
     for (const auto& bin : S.bins) {
         int prev = -1;
-        if (!reads_ahead(in, written)) break;
+        if (ahead.empty()) break;
         for (int i : bin) {
             if (per[i].empty()) continue;
-            if (prev >= 0) {
-                const std::vector<ExaTile>& ahead = ahead_of[i];
-                per[prev].insert(per[prev].begin(), ahead.begin(), ahead.end());
-            }
+            if (prev >= 0) per[prev].insert(per[prev].begin(), ahead[i].begin(), ahead[i].end());
             prev = i;
         }
     }
@@ -370,16 +390,16 @@ void set_batch_schedule(exa_batch& b, uint32_t mask, int block, int epl, bool fu
                 for (auto& v : per) v.clear();
                 for (int i : inst) instance_tiles(b, i, {mode}, false, em, tp, fused, per[i]);
                 exa_batch::Sched::Part part{mode, nullptr, 0};
-                part.tiles = upload_binned(b, S, per, {mode}, false, part.ntiles);
+                part.tiles = upload_binned(b, S, (int)c, per, {mode}, false, part.ntiles);
                 Lc.parts.push_back(part);
             }
         } else if (!modes.empty()) {
             for (int i : inst) instance_tiles(b, i, modes, !single_kernel(modes), em, tp, fused, per[i]);
-            Lc.tiles = upload_binned(b, S, per, modes, !single_kernel(modes), Lc.ntiles);
+            Lc.tiles = upload_binned(b, S, (int)c, per, modes, !single_kernel(modes), Lc.ntiles);
         }
         if (mask & EXA_EV_ADJ) {
             for (int i : inst) instance_tiles(b, i, {M_ADJ}, false, 0, tp, fused, adj[i]);
-            Lc.atiles = upload_binned(b, S, adj, {M_ADJ}, false, Lc.antiles);
+            Lc.atiles = upload_binned(b, S, (int)c, adj, {M_ADJ}, false, Lc.antiles);
         }
     }
 }
@@ -974,6 +994,7 @@ exa_status exa_batch_set_schedule(exa_batch* b, uint32_t mask, int32_t block, in
         if (units < EXA_UNITS_PER_CALLBACK || units > EXA_UNITS_SEPARATE)
             fail(EXA_EINVAL, "units must be one of the EXA_UNITS_* values");
         set_batch_schedule(*b, mask, block, epl, fused != 0, units);
+        b->sched[mask].ahead.clear();
         b->sched[mask].unstaged = unstaged;
         b->sched[mask].reduce_built = false;
         b->sched[mask].tuned = true;
@@ -1066,7 +1087,7 @@ exa_status exa_batch_eval(exa_batch* b, uint32_t mask, const exa_batch_io* io, e
         auto it = b->sched.find(mask);
         if (it == b->sched.end() || !it->second.tuned) {
             // the options' units
-            const int epl = untimed_epl(b->epl, b->epl_most, [&](int e) {
+            const int epl = untimed_epl(b->epl, b->epl_most && !b->autotune, [&](int e) {
                 int64_t n = 0;
                 for (size_t c = 0; c < b->classes.size(); ++c) {
                     const Model& M = lead_of(*b, (int)c);
@@ -1083,6 +1104,7 @@ exa_status exa_batch_eval(exa_batch* b, uint32_t mask, const exa_batch_io* io, e
             b->sched[mask].unstaged = (b->units & EXA_UNSTAGED) != 0;
             b->sched[mask].reduce_built = false;
             if (b->autotune) tune_batch(*b, mask, *io, s);
+            b->sched[mask].ahead.clear();
             b->sched[mask].tuned = true;
             b->drop_graph();
         }

@@ -24,6 +24,7 @@
 #include <set>
 #include <sstream>
 #include <unordered_map>
+#include <unordered_set>
 
 #include "exa_internal.h"
 
@@ -60,6 +61,8 @@ struct Stmt {
     bool raw = false;  // a line emitted verbatim, in recorded order
 };
 
+using NameSet = std::unordered_set<std::string>;
+
 struct Em {
     std::vector<Stmt> st;
     std::unordered_map<std::string, int> byname;
@@ -86,8 +89,7 @@ struct Em {
         return byname.count(name) ? name : named(type, name, e);
     }
     std::string named(const std::string& type, const std::string& name, const std::string& e) {
-        Stmt s{type, name, e, deps_of(e), false};
-        st.push_back(s);
+        st.push_back(Stmt{type, name, e, deps_of(e), false});
         byname[name] = (int)st.size() - 1;
         return name;
     }
@@ -104,12 +106,10 @@ struct Em {
     // an output statement; names in its destination (e.g. the index of an
     // in-place gradient entry) are as live as those in its value
     void out(const std::string& lhs, const std::string& e) {
-        Stmt s{"", lhs, e, deps_of(lhs + " " + e), true};
-        st.push_back(s);
+        st.push_back(Stmt{"", lhs, e, deps_of(lhs + " " + e), true});
     }
     void raw(const std::string& line) {
-        Stmt s{"", "", line, deps_of(line), true, true};
-        st.push_back(s);
+        st.push_back(Stmt{"", "", line, deps_of(line), true, true});
     }
     std::string mul(const std::string& a, const std::string& b) {
         if (a == Z || b == Z) return Z;
@@ -136,7 +136,7 @@ struct Em {
         return def("-" + a);
     }
     // Emit live statements; returns the set of live names.
-    std::set<std::string> emit(std::ostream& os, const std::string& ind) const {
+    NameSet emit(std::ostream& os, const std::string& ind) const {
         std::vector<char> live(st.size(), 0);
         for (size_t i = st.size(); i-- > 0;) {
             if (st[i].out) live[i] = 1;
@@ -164,7 +164,7 @@ struct Em {
             auto it = trig.emplace(a, std::make_pair(-1, -1)).first;
             (is_sin ? it->second.first : it->second.second) = (int)i;
         }
-        std::set<std::string> names;
+        NameSet names;
         for (size_t i = 0; i < st.size(); ++i) {
             if (!live[i]) continue;
             const Stmt& s = st[i];
@@ -737,7 +737,7 @@ std::string aug_fn(const Model& M, int mode, int a, int& ntmp, UnitLive& live) {
     }
     PatternCg cg(P, mode, e, nm);
     cg.body("r");
-    const std::set<std::string> names = e.emit(os, "    ");
+    const NameSet names = e.emit(os, "    ");
     os << "    return r;\n}\n";
     for (int c : icols) if (names.count("ic" + std::to_string(c)) && !ident(M, a, c)) live.icols.push_back(c);
     for (int c : fcols) if (names.count("fc" + std::to_string(c))) live.fcols.push_back(c);
@@ -822,7 +822,7 @@ std::string record_weight(Em& e, const Pattern& P, int p, bool byw, const std::s
     return e.named_once("double", (byw ? "ww" : "wy") + std::to_string(p), w);
 }
 
-void record_live(const Model& M, const std::vector<int>& members, const Loads& L, const std::set<std::string>& names,
+void record_live(const Model& M, const std::vector<int>& members, const Loads& L, const NameSet& names,
                  UnitLive& live, int cv = -1) {
     for (int c : L.icols)
         if (names.count("ic" + std::to_string(c)) && c != cv && !ident(M, members[0], c)) live.icols.push_back(c);
@@ -1015,7 +1015,7 @@ std::string unit_tile(const Model& M, int mode, const Unit& U, int& ntmp, UnitLi
             e.raw(line);
         }
     }
-    const std::set<std::string> names = e.emit(os, "            ");
+    const NameSet names = e.emit(os, "            ");
 
     // ---- augmentation pulls of the scalar jobs (cons values, jprod tangents)
     // Base rows pull the augmentation terms that add to them, in declaration
@@ -1203,7 +1203,7 @@ std::string pull_fn(const Model& M, int mode, const OwnSrc& s, int& ntmp, UnitLi
             if (want[i])
                 e.out("r", (jm == M_GRAD ? std::string() : "r + ") + "o" + std::to_string(p) + "[" + std::to_string(i) + "]");
     }
-    const std::set<std::string> names = e.emit(os, "    ");
+    const NameSet names = e.emit(os, "    ");
     os << "    return r;\n}\n";
     UnitLive own;
     record_live(M, members, L, names, own, cv);
@@ -1348,7 +1348,7 @@ std::string own_lunit(const Model& M, int mode, const OwnUnit& U, int sum, int& 
             e.out(g, g + " + o" + std::to_string(p) + "[" + std::to_string(i) + "]");
         }
     }
-    const std::set<std::string> names = e.emit(os, "        ");
+    const NameSet names = e.emit(os, "        ");
     os << "        if (q < ne) {\n";
     for (size_t o = 0; o < U.outs.size(); ++o) {
         const std::vector<int>& refs = U.outs[o].refs;
@@ -1496,7 +1496,7 @@ std::string own_hunit(const Model& M, int mode, const OwnUnit& U, int sum, int& 
         emit_pulls(M, jm, c.after, v, tag(i, "c"), "            ", os);
         if (mode == M_LAG) emit_pulls(M, jm, c.grad, v, tag(i, "q"), "            ", os);
     }
-    const std::set<std::string> names = e.emit(os, "            ");
+    const NameSet names = e.emit(os, "            ");
     for (size_t i = 0; i < U.chains.size(); ++i) {
         const OwnChain& c = U.chains[i];
         int span = 0;

@@ -44,10 +44,14 @@ std::mutex g_mod_mu;
 std::map<std::string, std::weak_ptr<Module>> g_mods;
 
 std::string hex_hash(const std::string& s) {
-    uint64_t h = 1469598103934665603ull;  // FNV-1a
-    for (unsigned char c : s) {
-        h ^= c;
-        h *= 1099511628211ull;
+    // FNV-1a over 8-byte words (a generated source has some 300,000 bytes, hashed
+    // at every create), folded so that a word's high bits reach the low ones
+    uint64_t h = 1469598103934665603ull;
+    for (size_t i = 0; i < s.size(); i += 8) {
+        uint64_t w = 0;
+        std::memcpy(&w, s.data() + i, std::min<size_t>(8, s.size() - i));
+        h = (h ^ w) * 1099511628211ull;
+        h ^= h >> 32;
     }
     char buf[32];
     snprintf(buf, sizeof buf, "%016llx", (unsigned long long)h);
@@ -169,14 +173,16 @@ std::string cache_dir_of(const char* opt_dir) {
     return (e && *e) ? e : "";
 }
 
-std::shared_ptr<Module> compile_module(const std::string& src, const std::string& cache_dir, bool* cache_hit) {
+std::shared_ptr<Module> compile_module(const std::string& src, const std::string& cache_dir, bool* cache_hit, bool* shared) {
     if (cache_hit) *cache_hit = false;
+    if (shared) *shared = true;
     const std::string key = hex_hash(src) + ":" + std::to_string(src.size());
     std::lock_guard<std::mutex> lk(g_mod_mu);
     auto it = g_mods.find(key);
     if (it != g_mods.end())
         if (auto m = it->second.lock())
             if (m->source == src) return m;
+    if (shared) *shared = false;
     auto m = std::make_shared<Module>();
     m->source = src;
     m->code = cached_code(src, cache_dir, cache_hit);
@@ -265,8 +271,10 @@ std::vector<ExaTile> make_tiles(const Model& M, int mode, int inst, int64_t tile
                 // variables whose lists' entries are one round of lanes
                 const int64_t cap = std::min<int64_t>(tile_pts, EXA_LIST_TILE);
                 for (int64_t i = 0; i < U.n;) {
-                    int64_t e = i + 1;
-                    while (e < U.n && e - i < cap && U.lptr[e + 1] - U.lptr[i] <= cap) ++e;
+                    // the last variable whose entries still fit, at least one
+                    const auto b = U.lptr.begin();
+                    const int64_t fit = std::upper_bound(b + i + 1, b + std::min(U.n, i + cap) + 1, (int64_t)U.lptr[i] + cap) - b - 1;
+                    const int64_t e = std::max(i + 1, fit);
                     ExaTile t{};
                     t.pat = U.code;
                     t.inst = inst;
@@ -483,14 +491,7 @@ void build_device(Model& M) {
     auto t0 = std::chrono::steady_clock::now();
     const std::string src = generate_source(M, &M.live);
     auto t1 = std::chrono::steady_clock::now();
-    {
-        std::lock_guard<std::mutex> lk(g_mod_mu);
-        M.module_shared = false;
-        auto it = g_mods.find(hex_hash(src) + ":" + std::to_string(src.size()));
-        if (it != g_mods.end())
-            if (auto m = it->second.lock()) M.module_shared = m->source == src;
-    }
-    D.module = compile_module(src, M.cache_dir, &M.cache_hit);
+    D.module = compile_module(src, M.cache_dir, &M.cache_hit, &M.module_shared);
     auto t2 = std::chrono::steady_clock::now();
     M.codegen_ms = std::chrono::duration<double, std::milli>(t1 - t0).count();
     M.compile_ms = std::chrono::duration<double, std::milli>(t2 - t1).count();
@@ -1995,7 +1996,7 @@ void eval_body(Model& M, const exa_eval_args* a, hipStream_t s, bool lag = false
         // models; one-pass units hold many registers), patterns over the
         // same data in one lane
         auto untuned = [&](uint32_t k) {
-            const int epl = untimed_epl(M.epl, M.epl_most, [&](int e) {
+            const int epl = untimed_epl(M.epl, M.epl_most && !M.autotune, [&](int e) {
                 int64_t n = 0;
                 for (int mode : launch_modes(M, k, EXA_UNITS_PER_CALLBACK))
                     if (mode != M_OBJ) n += (int64_t)make_tiles(M, mode, 0, (int64_t)M.block * e, true).size();

@@ -176,7 +176,9 @@ std::vector<char> compile_code(const std::string& src);
 std::vector<char> cached_code(const std::string& src, const std::string& dir, bool* hit);
 // The cache directory: the option's, else $EXA_CACHE_DIR, else none.
 std::string cache_dir_of(const char* opt_dir);
-std::shared_ptr<Module> compile_module(const std::string& src, const std::string& cache_dir, bool* cache_hit);
+// shared: whether a live model had it already.
+std::shared_ptr<Module> compile_module(const std::string& src, const std::string& cache_dir, bool* cache_hit,
+                                       bool* shared = nullptr);
 // One line to stderr when the environment variable EXA_LOG is set (not "0").
 bool log_on();
 void log_msg(const std::string& msg);
