@@ -63,3 +63,66 @@ def test_gaps_that_pay_keep_their_table():
     d = DataSet(n, i=np.arange(n) * 3)
     m.add_con(sin(x[d.i]), d)
     assert sources(plan(m)[JT]) == [(0, 0, 1, True)]
+
+
+def units(text):
+    return re.findall(r"U(\d+)S(\d+)", text)
+
+
+def lists(text):
+    """Data sets whose contributions are pulled through incidence lists."""
+    return [int(g) for g in re.findall(r"l(\d+)\.\d+:", text)]
+
+
+def chain_shifts(text):
+    """Lane shifts of every chain."""
+    chains = re.findall(r"c\d+:((?:\d+/\d+,)+)b", text)
+    return [[int(r.split("/")[0]) for r in c.split(",")[:-1]] for c in chains]
+
+
+def test_list_length_limit():
+    from test_incidence_gpu import network
+    for kind, want in (("hub", True), ("long", False)):  # 64 and 65 entries
+        text = plan(network(kind, 100, 300).model)
+        assert bool(lists(text[JT])) == want and bool(lists(text[HV])) == want, text
+
+
+def test_lists_in_the_points_order_or_small():
+    from test_incidence_gpu import network
+    for kind, nb, nl, want in (("ring", 60000, 80000, True), ("plain", 60000, 80000, False), ("plain", 1000, 1400, True)):
+        assert bool(lists(plan(network(kind, nb, nl).model)[JT])) == want, (kind, nb)
+
+
+def shifted(n, s):
+    m = Model("shifted")
+    x = m.add_var(n + s)
+    d = DataSet(n, i=np.arange(n))
+    m.add_con(sin(x[d.i] * x[d.i + s]), d)
+    return m
+
+
+def test_chain_span_limit():
+    assert chain_shifts(plan(shifted(500, 8))[JT]) == [[0, 8]]
+    assert not chain_shifts(plan(shifted(500, 9))[JT])  # overlapping, too far for a shift: a unit over variables
+    assert [s for s in sources(plan(shifted(500, 9))[JT]) if s[2] == 0]
+
+
+@pytest.mark.parametrize("period", [0, 1, 2, 4, 32, 64])
+def test_shared_references(period):
+    """Partial sums for a literal index (0) and a period of 2 to 32 points;
+    a period of 1 (every point the same entry) repeats with 2; one of 64 is
+    left to lists or the map."""
+    n = 640
+    m = Model("shared")
+    x, z = m.add_var(n), m.add_var(64)
+    d = DataSet(n, i=np.arange(n), s=np.arange(n) % max(1, period))
+    m.add_con(x[d.i] * sin(z[3] if period == 0 else z[d.s]), d)
+    got = re.findall(r"s(\d+)/(\d+),", plan(m)[JT])
+    want = {0: [("1", "1")], 1: [("1", "2")], 64: []}.get(period, [("1", str(period))])
+    assert got == want, plan(m)[JT]
+
+
+def test_gaps_take_a_table():
+    from test_sums_gpu import forms
+    assert [s for s in sources(plan(forms("gaps", 513).model)[JT]) if s[2] == 1]
+    assert not [s for s in sources(plan(forms("plain", 513).model)[JT]) if s[2] == 1]
