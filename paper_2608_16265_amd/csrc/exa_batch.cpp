@@ -285,16 +285,16 @@ void instance_tiles(const exa_batch& b, int i, const std::vector<int>& modes, bo
 int64_t ahead_tiles(const exa_batch& b, int i, const std::vector<ExaTile>& mine, const std::vector<int>& modes, bool tagged,
                  std::vector<ExaTile>& out) {
     const Model& M = b.models[i]->impl;
-    const AheadRecs rec = ahead_recs(M, modes);
+    const AheadIn has = ahead_in(M, modes);
     Ahead in;
     for (size_t s = 0; s < mine.size();) {
         size_t e = s;
         while (e < mine.size() && mine[e].pat == mine[s].pat) ++e;
         const int mode = tagged ? mine[s].pat >> EXA_MODE_SHIFT : modes[0];
-        if ((mine[s].pat & ((1 << EXA_MODE_SHIFT) - 1)) != EXA_AHEAD_TILE) ahead_unit(M, mode, &mine[s], e - s, rec, in);
+        ahead_unit(M, mode, &mine[s], e - s, has, in);
         s = e;
     }
-    in.tiles(i, tagged, out);
+    in.tiles(i, out);
     return in.bytes();
 }
 
@@ -603,6 +603,7 @@ void launch_eval(exa_batch& b, uint32_t mask, const ExaMulti& rec, hipStream_t s
                 mc.tiles = Lc.tiles;
                 mc.ntiles = Lc.ntiles;
                 mc.per_xcd = Lc.ntiles / 8;
+                multi_inputs(mc);
                 hipFunction_t fn = Lc.units == EXA_UNITS_ONE_PASS   ? K.fn_onepass
                                    : Lc.units == EXA_UNITS_JAC_HESS ? K.fn_multijh
                                                                     : K.fn_multi;

@@ -1838,11 +1838,8 @@ __device__ __forceinline__ void exa_store_direct(double* __restrict__ dst, const
 // thread t holds lanes t, t + blockDim.x, ...; the 256 lane sums then go
 // through a fixed tree in LDS.  The order never depends on the launch.
 #define EXA_VLANES 256
-__device__ __forceinline__ double exa_vlane_sum(const double* acc, double* lds) {
+__device__ __forceinline__ double exa_lane_tree(double* lds) {
     const int nthr = (int)blockDim.x;
-#pragma unroll
-    for (int q = 0; q < EXA_VLANES / 64; ++q)
-        if (q * nthr < EXA_VLANES) lds[threadIdx.x + q * nthr] = acc[q];
     __syncthreads();
     for (int s = EXA_VLANES / 2; s > 0; s >>= 1) {
         for (int t = threadIdx.x; t < s; t += nthr) lds[t] += lds[t + s];
@@ -1851,6 +1848,13 @@ __device__ __forceinline__ double exa_vlane_sum(const double* acc, double* lds) 
     const double r = lds[0];
     __syncthreads();  // lds is free again for the next tile
     return r;
+}
+__device__ __forceinline__ double exa_vlane_sum(const double* acc, double* lds) {
+    const int nthr = (int)blockDim.x;
+#pragma unroll
+    for (int q = 0; q < EXA_VLANES / 64; ++q)
+        if (q * nthr < EXA_VLANES) lds[threadIdx.x + q * nthr] = acc[q];
+    return exa_lane_tree(lds);
 }
 // Index of the i-th augmentation term of a row whose terms are
 // ridx[jb, je), clamped into [0, je) so that every lane loads a valid term
@@ -1892,24 +1896,25 @@ __device__ __forceinline__ void exa_obj_finish(const ExaCall& C, long long n, lo
     }
     __syncthreads();
     if (!last) return;
-    const int nthr = (int)blockDim.x;
-    double acc[EXA_VLANES / 64] = {};
-#pragma unroll
-    for (int q = 0; q < EXA_VLANES / 64; ++q) {
-        if (q * nthr >= EXA_VLANES) break;
-        // eight loads in flight before their additions
-        for (long long i0 = threadIdx.x + q * nthr; i0 < n; i0 += 8 * EXA_VLANES) {
+    // lane l of 256 adds sums l, l + 256, ..., eight loads in flight before their
+    // additions
+    const int nthr = (int)blockDim.x, ni = (int)n;
+    for (int l = threadIdx.x; l < EXA_VLANES; l += nthr) {
+        double acc = 0.0;
+        for (int i0 = l; i0 < ni; i0 += 8 * EXA_VLANES) {
             unsigned long long v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                v[u] = __hip_atomic_load(&P[i0 + u * EXA_VLANES < n ? i0 + u * EXA_VLANES : n - 1], __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + u * EXA_VLANES;
+                v[u] = __hip_atomic_load(&P[i < ni ? i : ni - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (i0 + u * EXA_VLANES < n) acc[q] += __longlong_as_double((long long)v[u]);
+                if (i0 + u * EXA_VLANES < ni) acc += __longlong_as_double((long long)v[u]);
         }
+        lds[l] = acc;
     }
-    const double f = exa_vlane_sum(acc, lds);
+    const double f = exa_lane_tree(lds);
     if (threadIdx.x == 0) C.out1[0] = f;
 }
 // The tables anew: what a round reads from them is not kept in registers over
@@ -1919,17 +1924,22 @@ __device__ __forceinline__ const EXA_K ExaInstDev* exa_again(const EXA_K ExaInst
     return p;
 }
 // Reads a tile's input range into this XCD's L2, one dword per 128-byte line:
-// 256 lanes cover 32 KB with one load each.
-__device__ __forceinline__ void exa_ahead(const ExaCall& C, const EXA_K ExaInstDev& I, const ExaTile& T) {
-    const EXA_G char* p = T.slot == )" << EXA_AHEAD_X << " ? (const EXA_G char*)(C.x + I.off[" << EXA_OFF_X << "] + T.start) : T.slot == "
-       << EXA_AHEAD_Y << " ? (const EXA_G char*)(C.y + I.off[" << EXA_OFF_Y << "] + T.start) : T.slot == " << EXA_AHEAD_V
-       << " ? (const EXA_G char*)(C.v + I.off[" << EXA_OFF_X << R"(] + T.start) : (const EXA_G char*)T.slot + T.start;
-    const long long last = T.count - 4;
+// 256 lanes cover 32 KB with one load each.  A kernel holds one copy, whatever
+// the modes whose inputs it reads: a copy per mode took 0.3 s to compile.
+__device__ __forceinline__ void exa_ahead(const double* x, const double* y, const double* v, const double* w,
+                                          const EXA_K ExaInstDev& I, const ExaTile& T) {
+    const EXA_G char* p = (const EXA_G char*)T.slot + T.start;
+    if (T.slot <= )" << EXA_AHEAD_W << R"() {
+        const bool rows = T.slot == )" << EXA_AHEAD_Y << " || T.slot == " << EXA_AHEAD_W << R"(;
+        const double* a = rows ? (T.slot == )" << EXA_AHEAD_Y << R"( ? y : w) : (T.slot == )" << EXA_AHEAD_X << R"( ? x : v);
+        p = (const EXA_G char*)(a + I.off[rows ? )" << EXA_OFF_Y << " : " << EXA_OFF_X << R"(] + T.start);
+    }
+    const unsigned n = (unsigned)T.count, last = n - 4;
     int acc = 0;
-    for (long long o = 128ll * threadIdx.x; o < T.count; o += 8 * 128ll * blockDim.x) {
+    for (unsigned o = 128u * threadIdx.x; o < n; o += 8 * 128u * blockDim.x) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const long long q = o + u * 128ll * blockDim.x;
+            const unsigned q = o + u * 128u * blockDim.x;
             acc ^= *(const EXA_G int*)(p + (q < last ? q : last));
         }
     }
@@ -1951,7 +1961,7 @@ __device__ __forceinline__ void exa_ahead(const ExaCall& C, const EXA_K ExaInstD
         os << "        const EXA_K ExaInstDev& I = C.inst[T.inst];\n";
         os << "        switch (T.pat) {\n";
         for (auto& c : cases) os << "            " << c << "\n";
-        if (ahead) os << "            case " << EXA_AHEAD_TILE << ": exa_ahead(C, I, T); break;\n";
+        if (ahead) os << "            case " << EXA_AHEAD_TILE << ": exa_ahead(C.x, C.y, C.v, C.y, I, T); break;\n";
         os << "            default: break;\n";
         os << "        }\n";
         os << "    }\n";
@@ -2010,9 +2020,7 @@ __device__ __forceinline__ void exa_ahead(const ExaCall& C, const EXA_K ExaInstD
         os << "    const ExaTile T = C.tiles[w];\n";
         os << "    switch (T.pat) {\n";
         for (auto& c : cases) os << "        " << c << "\n";
-        for (int m = 0; m < M_COUNT; ++m)
-            os << "        case " << ((m << EXA_MODE_SHIFT) | EXA_AHEAD_TILE) << ": exa_ahead(C.c[" << m << "], C.c[" << m
-               << "].inst[T.inst], T); break;\n";
+        os << "        case " << EXA_AHEAD_TILE << ": exa_ahead(C.in[0], C.in[1], C.in[2], C.in[3], C.inst[T.inst], T); break;\n";
         os << "        default: break;\n";
         os << "    }\n";
         os << "}\n";

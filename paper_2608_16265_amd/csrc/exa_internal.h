@@ -57,12 +57,13 @@ void set_last_error(const std::string& msg);
 #define EXA_LIST_TILE 256
 #define EXA_PAD_TILE 4095  // a tile that matches no unit: does nothing
 // A tile that only reads T.count bytes of input ahead of the tiles that need
-// them: from entry T.start of x, y (the weights) or v of its mode's call
-// record (T.slot = EXA_AHEAD_*), or from the device address T.slot.
+// them: from entry T.start of x, y, v or the J^T w weights of its launch
+// (T.slot = EXA_AHEAD_*), or from byte T.start of the device address T.slot.
 #define EXA_AHEAD_TILE 4094
 #define EXA_AHEAD_X 0
 #define EXA_AHEAD_Y 1
 #define EXA_AHEAD_V 2
+#define EXA_AHEAD_W 3
 
 // ExaPatDev::hvd: bit r set when the pattern's group stores H v reference r
 // straight into the output (Group::hv_direct, for this instance's data).
@@ -74,7 +75,8 @@ void set_last_error(const std::string& msg);
 // and nrun[s] are the 64-lane chunks per wave and the runs of the data set's
 // unit for sum s (SumKind).  ExaInstDev::vlo[s][j]: the first variable of the
 // j-th unit over variables of sum s.  ExaInstDev::nobj: objective tiles, whose
-// partial sums the last of them adds (ExaCall::direct, EXA_ARRIVAL).  ExaInstDev::lptr[s][j], lent[s][j] (J^T w
+// partial sums the last of them adds (ExaCall::direct, EXA_ARRIVAL).
+// ExaMulti::in: the launch's inputs by EXA_AHEAD_*, for read-ahead tiles.  ExaInstDev::lptr[s][j], lent[s][j] (J^T w
 // and H v): incidence lists of its j-th list unit, entries lptr[i] .. lptr[i+1]
 // of the unit's i-th variable, each a data point * 4 + the slot (OwnUnit::slots).
 // EXA_G and EXA_K name the address spaces of data (global memory) and of the
@@ -147,6 +149,8 @@ void set_last_error(const std::string& msg);
         long long ntiles;                                                        \
         long long per_xcd;                                                       \
         struct ExaCall c[10];                                                    \
+        const double* in[4];                                                     \
+        const EXA_K struct ExaInstDev* inst;                                     \
     };
 
 #define EXA_G

@@ -716,22 +716,26 @@ ChunkPlan chunk_plan(const SegMap& S, bool own) {
 // while a round of tiles runs, a few tiles read the next round's inputs, one
 // load per 128-byte line, into the L2 of the XCD that will need them.
 
-AheadRecs ahead_recs(const Model& M, const std::vector<int>& modes) {
-    AheadRecs r;
-    auto first = [](int& at, int mode) {
-        if (at < 0) at = mode;
-    };
-    for (int mode : modes) {
-        const bool multi = multi_unit_mode(mode);
-        const int own = mode == M_LAG ? (int)M_JTPROD : tile_mode(mode);
-        first(r.x, multi ? (int)M_JAC : own);
+AheadIn ahead_in(const Model& M, const std::vector<int>& modes) {
+    AheadIn r;
+    for (int mode : modes)
         for (int m : job_modes(M, mode)) {
-            if (m == M_JPROD || m == M_HPROD || m == M_ADJ) first(r.v, multi ? (int)M_JPROD : own);
-            if (m == M_HESS || m == M_HPROD || m == M_ADJ) first(r.y, multi ? (int)M_HESS : own);
-            if (m == M_JTPROD) first(r.w, own);
+            r.v = r.v || m == M_JPROD || m == M_HPROD || m == M_ADJ;
+            r.y = r.y || m == M_HESS || m == M_HPROD || m == M_ADJ;
+            r.w = r.w || m == M_JTPROD;
         }
-    }
     return r;
+}
+
+void multi_inputs(ExaMulti& mc) {
+    for (const ExaCall& c : mc.c) {
+        if (!mc.inst) mc.inst = c.inst;
+        if (!mc.in[EXA_AHEAD_X]) mc.in[EXA_AHEAD_X] = c.x;
+        if (!mc.in[EXA_AHEAD_V]) mc.in[EXA_AHEAD_V] = c.v;
+    }
+    for (int m : {M_HESS, M_JH, M_HPROD})
+        if (!mc.in[EXA_AHEAD_Y]) mc.in[EXA_AHEAD_Y] = mc.c[m].y;
+    mc.in[EXA_AHEAD_W] = mc.c[M_JTPROD].y;
 }
 
 int64_t Ahead::bytes() const {
@@ -748,7 +752,7 @@ int64_t Ahead::bytes() const {
     return total;
 }
 
-void Ahead::tiles(int inst, bool tagged, std::vector<ExaTile>& out) {
+void Ahead::tiles(int inst, std::vector<ExaTile>& out) {
     for (auto& kv : spans) {
         auto& v = kv.second;
         std::sort(v.begin(), v.end());
@@ -757,11 +761,11 @@ void Ahead::tiles(int inst, bool tagged, std::vector<ExaTile>& out) {
             for (++i; i < v.size() && v[i].first <= hi + 256; ++i) hi = std::max(hi, v[i].second);
             for (int64_t s = lo; s < hi; s += kAheadBytes) {
                 ExaTile t{};
-                t.pat = EXA_AHEAD_TILE | (tagged ? kv.first.second << EXA_MODE_SHIFT : 0);
+                t.pat = EXA_AHEAD_TILE;
                 t.inst = inst;
-                t.slot = kv.first.first;
-                // x, y and v by entry, data columns by byte
-                t.start = t.slot <= EXA_AHEAD_V ? s / 8 : s;
+                t.slot = kv.first;
+                // x, y, v and w by entry, data columns by byte
+                t.start = t.slot <= EXA_AHEAD_W ? s / 8 : s;
                 t.count = std::min(kAheadBytes, hi - s);
                 out.push_back(t);
             }
@@ -776,16 +780,16 @@ namespace {
 // reached through others, gathered in no order that could be read ahead, only
 // for the data set as a whole (a batch's instances).
 void ahead_points(const Model& M, const Group& G, const std::vector<int>& members, const UnitLive& L, int mode, int64_t a,
-                  int64_t b, const AheadRecs& rec, Ahead& in) {
+                  int64_t b, const AheadIn& has, Ahead& in) {
     a = std::max<int64_t>(a, 0);
     b = std::min(b, G.ndata);
     if (a >= b) return;
     const int m0 = G.members[0];
     const Pattern& P0 = M.pats[m0];
     const ExaPatDev& d = M.dev->inst_host.pat[m0];
-    for (int c : L.icols) in.add(rec.x, (int64_t)d.ic[c], 4 * a, 4 * b);
-    for (int c : L.fcols) in.add(rec.x, (int64_t)d.fc[c], 8 * a, 8 * b);
-    auto refs = [&](const std::vector<int>& list, int at, int slot) {
+    for (int c : L.icols) in.add(true, (int64_t)d.ic[c], 4 * a, 4 * b);
+    for (int c : L.fcols) in.add(true, (int64_t)d.fc[c], 8 * a, 8 * b);
+    auto refs = [&](const std::vector<int>& list, bool at, int slot) {
         for (int ref : list) {
             const RefKey& k = G.vrefs[ref];
             if (k.col < 0) continue;
@@ -799,14 +803,14 @@ void ahead_points(const Model& M, const Group& G, const std::vector<int>& member
             }
         }
     };
-    refs(L.vrefs, rec.x, EXA_AHEAD_X);
-    refs(L.vseeds, rec.v, EXA_AHEAD_V);
+    refs(L.vrefs, true, EXA_AHEAD_X);
+    refs(L.vseeds, has.v, EXA_AHEAD_V);
     for (int m : job_modes(M, mode)) {
         if (m != M_HESS && m != M_HPROD && m != M_JTPROD) continue;
         for (int p : members) {
             const Pattern& P = M.pats[p];
             if (P.kind == EXA_CON && pattern_in_mode(P, m))
-                in.add(m == M_JTPROD ? rec.w : rec.y, EXA_AHEAD_Y, 8 * (P.o0 + a), 8 * (P.o0 + b));
+                in.add(m == M_JTPROD ? has.w : has.y, m == M_JTPROD ? EXA_AHEAD_W : EXA_AHEAD_Y, 8 * (P.o0 + a), 8 * (P.o0 + b));
         }
     }
     // the row lists of the terms that base rows pull, once per walk (64
@@ -818,8 +822,8 @@ void ahead_points(const Model& M, const Group& G, const std::vector<int>& member
         if (A.kind != EXA_AUG || A.ndata == 0 || std::find(members.begin(), members.end(), A.target) == members.end()) continue;
         if (std::any_of(walks.begin(), walks.end(), [&](int w) { return same_walk(M, w, q); })) continue;
         walks.push_back(q);
-        in.add(rec.x, (int64_t)M.dev->inst_host.pat[q].rptr, 4 * a, 4 * (b + 1));
-        in.add(rec.x, (int64_t)M.dev->inst_host.pat[q].ridx, 4 * (int64_t)A.rptr[a], 4 * (int64_t)A.rptr[b]);
+        in.add(true, (int64_t)M.dev->inst_host.pat[q].rptr, 4 * a, 4 * (b + 1));
+        in.add(true, (int64_t)M.dev->inst_host.pat[q].ridx, 4 * (int64_t)A.rptr[a], 4 * (int64_t)A.rptr[b]);
     }
 }
 
@@ -839,7 +843,7 @@ int64_t tile_outputs(const Model& M, int mode, const ExaTile* t, size_t n) {
 }
 
 // Inputs of one unit's tiles t[0 .. n), in order.
-void ahead_unit(const Model& M, int mode, const ExaTile* t, size_t n, const AheadRecs& rec, Ahead& in) {
+void ahead_unit(const Model& M, int mode, const ExaTile* t, size_t n, const AheadIn& has, Ahead& in) {
     const int code = t[0].pat & ((1 << EXA_MODE_SHIFT) - 1);
     if (code == EXA_ZERO_TILE) return;
     const int64_t a = t[0].start, b = t[n - 1].start + t[n - 1].count;
@@ -849,7 +853,7 @@ void ahead_unit(const Model& M, int mode, const ExaTile* t, size_t n, const Ahea
     if (code < EXA_OWN_CODE) {
         const bool fused = code >= EXA_MAX_PATTERNS;
         const Group& G = M.groups[fused ? code - EXA_MAX_PATTERNS : M.pats[code].group];
-        ahead_points(M, G, fused ? G.members : std::vector<int>{code}, L, mode, a, b, rec, in);
+        ahead_points(M, G, fused ? G.members : std::vector<int>{code}, L, mode, a, b, has, in);
         return;
     }
     const OwnPlan* plan = own_plan(M, mode, true);
@@ -860,16 +864,16 @@ void ahead_unit(const Model& M, int mode, const ExaTile* t, size_t n, const Ahea
             const Group& G = M.groups[U.lgroup];
             const ExaInstDev& I = M.dev->inst_host;
             const int sum = mode == M_HPROD ? SUM_HV : SUM_JT;
-            in.add(rec.x, (int64_t)I.lptr[sum][U.lunit], 4 * a, 4 * (b + 1));
-            in.add(rec.x, (int64_t)I.lent[sum][U.lunit], 4 * (int64_t)U.lptr[a], 4 * (int64_t)U.lptr[b]);
+            in.add(true, (int64_t)I.lptr[sum][U.lunit], 4 * a, 4 * (b + 1));
+            in.add(true, (int64_t)I.lent[sum][U.lunit], 4 * (int64_t)U.lptr[a], 4 * (int64_t)U.lptr[b]);
             // the points in the lists' order only as a whole
-            if (a == 0 && b == U.n) ahead_points(M, G, G.members, L, mode, 0, G.ndata, rec, in);
+            if (a == 0 && b == U.n) ahead_points(M, G, G.members, L, mode, 0, G.ndata, has, in);
             continue;
         }
         if (U.vunit < 0) {
             const Group& G = M.groups[U.group];
             const int64_t per = U.plain() ? 1 : U.points_per_run();
-            ahead_points(M, G, G.members, L, mode, a * per - U.S, b * per, rec, in);
+            ahead_points(M, G, G.members, L, mode, a * per - U.S, b * per, has, in);
             continue;
         }
         for (const OwnSrc& s : U.srcs) {
@@ -882,12 +886,12 @@ void ahead_unit(const Model& M, int mode, const ExaTile* t, size_t n, const Ahea
                           kb = std::lower_bound(c.begin(), c.end(), hi) - c.begin();
             if (s.how == OWN_INVERSE) {
                 const int64_t c0 = c.front(), c1 = (int64_t)c.back() + 1;
-                in.add(rec.x, (int64_t)M.dev->inst_host.pat[G.members[0]].inv[k.col],
+                in.add(true, (int64_t)M.dev->inst_host.pat[G.members[0]].inv[k.col],
                        4 * (std::max(lo, c0) - c0), 4 * (std::min(hi, c1) - c0));
             }
             UnitLive R;  // the reference itself stands for what its derivative reads
             if (s.wread < 0) R.vrefs.push_back(s.ref);
-            ahead_points(M, G, s.wread >= 0 ? std::vector<int>() : G.members, R, mode, ka, kb, rec, in);
+            ahead_points(M, G, s.wread >= 0 ? std::vector<int>() : G.members, R, mode, ka, kb, has, in);
         }
     }
 }
@@ -914,7 +918,7 @@ std::vector<ExaTile> interleave_units(const Model& M, const std::vector<std::vec
                                       const std::vector<int>& modes, bool tagged) {
     size_t most = 0;
     for (const auto& u : units) most = std::max(most, u.size());
-    const AheadRecs rec = ahead_recs(M, modes);
+    const AheadIn has = ahead_in(M, modes);
     size_t rounds = std::min<size_t>(16, std::max<size_t>(1, most / (8 * 32)));
     bool ahead = false;
     int64_t written = 0;
@@ -923,7 +927,7 @@ std::vector<ExaTile> interleave_units(const Model& M, const std::vector<std::vec
     if (reads_ahead(0, written) && (tagged || mode_reads_ahead(modes[0]))) {
         Ahead whole;
         for (size_t i = 0; i < units.size(); ++i)
-            if (!units[i].empty()) ahead_unit(M, modes[i], units[i].data(), units[i].size(), rec, whole);
+            if (!units[i].empty()) ahead_unit(M, modes[i], units[i].data(), units[i].size(), has, whole);
         ahead = reads_ahead(whole.bytes(), written);
         if (ahead) rounds = std::max(rounds, std::min<size_t>(most / (8 * 8), whole.bytes() / (8 * kRoundBytes)));
     }
@@ -935,9 +939,9 @@ std::vector<ExaTile> interleave_units(const Model& M, const std::vector<std::vec
             Ahead in;
             for (size_t i = 0; i < units.size(); ++i) {
                 const size_t lo = units[i].size() * (r + 1) / kRounds, hi = units[i].size() * (r + 2) / kRounds;
-                if (hi > lo) ahead_unit(M, modes[i], &units[i][lo], hi - lo, rec, in);
+                if (hi > lo) ahead_unit(M, modes[i], &units[i][lo], hi - lo, has, in);
             }
-            in.tiles(0, tagged, all);
+            in.tiles(0, all);
         }
         for (const auto& u : units)
             all.insert(all.end(), u.begin() + u.size() * r / kRounds, u.begin() + u.size() * (r + 1) / kRounds);
@@ -1183,6 +1187,7 @@ void raw_launch_multi(Model& M, uint32_t mask, ExaMulti mc, hipStream_t s) {
     mc.ntiles = S.ntiles;
     mc.per_xcd = (S.ntiles + 7) / 8;
     for (ExaCall& c : mc.c) c.unstaged = S.unstaged ? 1 : 0;
+    multi_inputs(mc);
     void* args[] = {&mc};
     const Module& K = *M.dev->module;
     hipFunction_t fn = S.units == EXA_UNITS_ONE_PASS   ? K.fn_onepass

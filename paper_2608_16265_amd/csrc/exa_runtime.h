@@ -125,26 +125,27 @@ int untimed_epl(int epl, bool most, const Tiles& tiles) {
 // kZeroTileEntries entries each (more when a tile of points is larger).
 constexpr int64_t kZeroTileEntries = 4096;
 void add_zero_tiles(const Model& M, int64_t tp, std::vector<ExaTile>& tiles);
-// Bytes one read-ahead tile covers (EXA_AHEAD_TILE), and the call records
-// (modes) from which a launch of `modes` reads x, v, y and the J^T w weights.
+// Bytes one read-ahead tile covers (EXA_AHEAD_TILE).
 constexpr int64_t kAheadBytes = 256 * 1024;
 // Inputs of one round of tiles on one XCD (interleave_units).
 constexpr int64_t kRoundBytes = 512 * 1024;
-struct AheadRecs {
-    int x = -1, v = -1, y = -1, w = -1;
+// Which inputs beside x a launch of `modes` has: v, y and the J^T w weights.
+struct AheadIn {
+    bool v = false, y = false, w = false;
 };
-AheadRecs ahead_recs(const Model& M, const std::vector<int>& modes);
+AheadIn ahead_in(const Model& M, const std::vector<int>& modes);
 // Input ranges to be read ahead of some tiles: per array (EXA_AHEAD_* or a
-// data column's device address, and the call record), [first, last) in bytes.
+// data column's device address), [first, last) in bytes.
 struct Ahead {
-    std::map<std::pair<int64_t, int>, std::vector<std::pair<int64_t, int64_t>>> spans;
-    void add(int mode, int64_t slot, int64_t lo, int64_t hi) {
-        if (hi > lo && mode >= 0) spans[{slot, mode}].emplace_back(lo, hi);
+    std::map<int64_t, std::vector<std::pair<int64_t, int64_t>>> spans;
+    void add(bool has, int64_t slot, int64_t lo, int64_t hi) {
+        if (hi > lo && has) spans[slot].emplace_back(lo, hi);
     }
     int64_t bytes() const;  // of their union
-    // their union as tiles (tagged: with the mode above EXA_MODE_SHIFT)
-    void tiles(int inst, bool tagged, std::vector<ExaTile>& out);
+    void tiles(int inst, std::vector<ExaTile>& out);  // their union as tiles
 };
+// Fills ExaMulti::in and inst from the call records.
+void multi_inputs(ExaMulti& mc);
 // Whether a launch reads ahead: its stores sweep the last-level cache (256 MB)
 // and outweigh its reads.  Launches that mostly read, or write less, find
 // their inputs in that cache at the next iterate, and the extra workgroups
@@ -154,7 +155,7 @@ struct Ahead {
 inline bool reads_ahead(int64_t in, int64_t out) { return out >= in && out >= (int64_t)96 << 20; }
 // Bytes a unit's tiles write as outputs.
 int64_t tile_outputs(const Model& M, int mode, const ExaTile* t, size_t n);
-void ahead_unit(const Model& M, int mode, const ExaTile* t, size_t n, const AheadRecs& rec, Ahead& in);
+void ahead_unit(const Model& M, int mode, const ExaTile* t, size_t n, const AheadIn& has, Ahead& in);
 bool has_fusable_group(const Model& M, int mode);
 // Modes of an exa_eval mask (with jh: Jacobian + Hessian as JH units), the
 // one-pass unit mode covering a mask (or -1), whether a mask has both the

@@ -126,3 +126,13 @@ def test_gaps_take_a_table():
     from test_sums_gpu import forms
     assert [s for s in sources(plan(forms("gaps", 513).model)[JT]) if s[2] == 1]
     assert not [s for s in sources(plan(forms("plain", 513).model)[JT]) if s[2] == 1]
+
+
+def test_one_read_ahead_loop_per_kernel():
+    """Kernels that may read ahead hold the loop once, not once per callback:
+    copies cost compile time on every model."""
+    src = ExaModel(edges(100, 1), host_only=True).generated_source()
+    body = src[src.index("exa_ahead(const double* x"):]
+    kernels = re.split(r'extern "C" __global__', body)[1:]
+    calls = [k.count("exa_ahead(") for k in kernels]
+    assert max(calls) == 1 and sum(calls) == 6, calls
