@@ -2018,9 +2018,10 @@ __device__ __forceinline__ void exa_ahead(const double* x, const double* y, cons
         os << "    const long long w = (blockIdx.x % 8) * C.per_xcd + blockIdx.x / 8;\n";
         os << "    if (w >= C.ntiles) return;\n";
         os << "    const ExaTile T = C.tiles[w];\n";
+        os << "    const EXA_K ExaInstDev& I = C.inst[T.inst];\n";
         os << "    switch (T.pat) {\n";
         for (auto& c : cases) os << "        " << c << "\n";
-        os << "        case " << EXA_AHEAD_TILE << ": exa_ahead(C.in[0], C.in[1], C.in[2], C.in[3], C.inst[T.inst], T); break;\n";
+        os << "        case " << EXA_AHEAD_TILE << ": exa_ahead(C.in[0], C.in[1], C.in[2], C.in[3], I, T); break;\n";
         os << "        default: break;\n";
         os << "    }\n";
         os << "}\n";
@@ -2035,7 +2036,7 @@ __device__ __forceinline__ void exa_ahead(const double* x, const double* y, cons
         const std::string K = "C.c[" + std::to_string(mode == M_LAG ? (int)M_JTPROD : mode) + "]";
         auto add = [&](int c, const char* pre) {
             cases.push_back("case " + std::to_string((mode << EXA_MODE_SHIFT) | c) + ": " + pre + mode_name(mode) + "_" +
-                            std::to_string(c) + "(" + K + ", " + K + ".inst[T.inst], T, lds); break;");
+                            std::to_string(c) + "(" + K + ", I, T, lds); break;");
         };
         for (int c : codes) add(c, "unit_");
         const OwnPlan* plan = own_plan(M, mode, true);
@@ -2043,12 +2044,11 @@ __device__ __forceinline__ void exa_ahead(const double* x, const double* y, cons
         for (const OwnUnit& u : plan->units) add(u.code, "own_");
         if (mode != M_GRAD)
             cases.push_back("case " + std::to_string((mode << EXA_MODE_SHIFT) | EXA_ZERO_TILE) + ": " +
-                            own_fill(mode, K, K + ".inst[T.inst]") + "; break;");
+                            own_fill(mode, K, "I") + "; break;");
     };
     const std::string G = "C.c[" + std::to_string(M_GRAD) + "]";
     const std::string zero_case = "case " + std::to_string((M_GRAD << EXA_MODE_SHIFT) | EXA_ZERO_TILE) +
-                                  ": exa_fill((" + G + ".direct ? " + G + ".out0 : " + G + ".out1) + " + G +
-                                  ".inst[T.inst].off[" + std::to_string(EXA_OFF_X) + "] + T.start, T.count, 0.0); break;";
+                                  ": exa_fill((" + G + ".direct ? " + G + ".out0 : " + G + ".out1) + I.off[" + std::to_string(EXA_OFF_X) + "] + T.start, T.count, 0.0); break;";
     if (M.lag_units) os << own_units(M, M_LAG, ntmp, live);
     // every unit's tiles share a kernel's register budget: ask for at least
     // four waves per SIMD, so that one wave of the launch fits on the chip at
@@ -2084,8 +2084,7 @@ __device__ __forceinline__ void exa_ahead(const double* x, const double* y, cons
                 os << unit_tile(M, mode, kv.second, ntmp, L);
                 if (live) (*live)[{mode, kv.first}] = L;
                 cases.push_back("case " + std::to_string((mode << EXA_MODE_SHIFT) | kv.first) + ": unit_" +
-                                mode_name(mode) + "_" + std::to_string(kv.first) + "(C, C.c[" + std::to_string(M_JAC) +
-                                "].inst[T.inst], T, lds); break;");
+                                mode_name(mode) + "_" + std::to_string(kv.first) + "(C, I, T, lds); break;");
             }
         }
         // the objective's and J^T w's tiles, and those of sums whose units

@@ -148,9 +148,9 @@ void set_last_error(const std::string& msg);
         const struct ExaTile* tiles;                                             \
         long long ntiles;                                                        \
         long long per_xcd;                                                       \
+        const EXA_K struct ExaInstDev* inst;                                     \
         struct ExaCall c[10];                                                    \
         const double* in[4];                                                     \
-        const EXA_K struct ExaInstDev* inst;                                     \
     };
 
 #define EXA_G
