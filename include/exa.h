@@ -38,6 +38,8 @@
  *     test hook for the EXA_ECOMPILE path).
  *   - Concurrent callbacks on ONE model from different streams race on the
  *     model's internal work buffers; serialize them (one stream per model).
+ *     Calls that overlap all the same may give wrong values; the calls after
+ *     them are right again.
  *     Calls on one model from several host threads must not overlap either
  *     (a model builds its schedules at first use); different models are
  *     independent.
@@ -266,10 +268,11 @@ exa_status exa_jprod(exa_model* m, const double* x, const double* v, double* Jv,
  * (Jacobian entry times w of its row, members in declaration order) to one
  * variable reference in the lane; the reduction then sums these per
  * variable in a fixed order (Sec. 7.2.3), or the evaluation kernel finishes
- * a variable itself, in the same order, where all its contributions come
- * through strictly increasing index columns.  Contributions to a variable
- * that every point of a data set shares are first added over runs of
- * consecutive points.  An augmentation term that is
+ * a variable itself, in the same order: where its contributions come through
+ * strictly increasing index columns, or through one data set's columns in no
+ * order with at most 64 entries to a variable.  Contributions to a variable
+ * that every point of a data set shares, or every 2nd to 32nd, are first
+ * added over runs of consecutive points.  An augmentation term that is
  * plus or minus one variable, and its data set's only contribution to that
  * reference, contributes plus or minus w of its row: the reduction reads
  * that weight from w itself, at the same place in the order. */
@@ -304,10 +307,11 @@ exa_status exa_hprod_noalloc(exa_model* m, const double* x, const double* y, dou
 /* Gradient of the Lagrangian of eq. nlp, sigma grad f(x) + J(x)^T y, into
  * out [nvar]; x [nvar] and y [ncon] are device arrays, sigma = obj_weight
  * (the first-order half of what hess_coord weights, Sec. 2.1.3).  One
- * evaluation launch of the gradient and J^T y terms and their reductions,
- * which finish out = sigma * grad + J^T y with the product rounded before
- * the sum (one elementwise launch more when the gradient itself needs a
- * reduction): bit-identical to exa_grad into out, exa_jtprod into t and
+ * evaluation launch of the gradient and J^T y terms, which finishes
+ * out = sigma * grad + J^T y, the product rounded before the sum, for the
+ * variables whose sums it finishes; a reduction launch for the others, when
+ * there are any (one elementwise launch more when the gradient itself needs
+ * a reduction).  Bit-identical to exa_grad into out, exa_jtprod into t and
  * then out = sigma * out followed by out = out + t.  Uses a library-owned
  * nvar buffer for J^T y, so overlapping calls on one model race.  Counts
  * as one grad and one jtprod evaluation.  Errors: EXA_EINVAL for a NULL

@@ -2,8 +2,9 @@
 
 The instances (ExaModel objects whose pattern trees are identical, sizes may
 differ) are evaluated together: one evaluation launch over the tiles of every
-instance and selected callback, one launch of every instance's reductions,
-replayed from a HIP graph; see exa_batch_* in include/exa.h.  Inputs and
+instance and selected callback (one per kind of instance where index columns of
+different shape make instances finish their sums differently), one launch of
+every instance's reductions, replayed from a HIP graph; see exa_batch_* in include/exa.h.  Inputs and
 outputs are the concatenations of the per-instance arrays (``offsets()``).
 """
 from __future__ import annotations

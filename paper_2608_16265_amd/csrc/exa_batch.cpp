@@ -2,20 +2,21 @@
 // models, generalised to instances of different sizes and to every
 // callback).
 //
-// All instances share the generated code; their data stays where each model
+// Instances of a class share the generated code; their data stays where each model
 // put it, and their sizes and offsets are table data (one ExaInstDev per
 // instance, whose offsets place the instance in the concatenated inputs,
 // outputs and work buffers).  A call is
-//   * ONE evaluation launch over a tile list of (instance, unit, data range)
-//     tiles of every selected callback, one workgroup per tile (the kernels
-//     and units of exa_eval: per-callback tiles, Jacobian + Hessian units or
-//     one pass per point), or one launch per callback (each kernel with the
-//     register budget of its own units), plus a launch for the parameter
-//     adjoint;
-//   * ONE launch of every instance's deterministic reductions (the same
-//     segment sums, chunks and parts as the instance's own reduction, and
-//     its objective partials), plus one small launch for the part sums of
-//     segments longer than 1024 entries;
+//   * ONE evaluation launch (one per class of instances that finish their sums
+//     by different units, exa_batch::Class; nearly always one class) over a
+//     tile list of (instance, unit, data range) tiles of every selected
+//     callback, one workgroup per tile (the kernels and units of exa_eval:
+//     per-callback tiles, Jacobian + Hessian units or one pass per point), or
+//     one launch per callback (each kernel with the register budget of its own
+//     units), plus a launch for the parameter adjoint;
+//   * ONE launch of every instance's deterministic reductions (what the units
+//     leave: the same segment sums, chunks and parts as the instance's own
+//     reduction, and its objective partials), plus one small launch for the
+//     part sums of segments added in parts;
 // recorded once into a HIP graph and replayed.  With xcd_aware, instances are
 // binned over the 8 XCDs by algorithmic bytes (largest first into the
 // lightest bin) and XCD j takes bin j's tiles and reduction blocks, so an

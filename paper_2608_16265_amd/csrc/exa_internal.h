@@ -371,9 +371,10 @@ struct SegMap {
 // ---- sums finished by the units themselves -----------------------------------
 // A variable whose contributions to a sum all come through strictly increasing
 // index columns gets at most one from each (data set, reference), at a data
-// point that follows from the variable.  Such a variable needs no work buffer
-// and no map: a unit adds its contributions in the map's order (data set,
-// point, reference) and stores the sum.  plan_sums finds these variables per
+// point that follows from the variable; one data set's columns in no order
+// give a variable a list of points (incidence lists).  Such a variable needs
+// no work buffer and no map: a unit adds its contributions in the map's order
+// (data set, point, reference) and stores the sum.  plan_sums finds these variables per
 // sum, in clusters (intervals of variables whose references overlap), and the
 // units that own them:
 //  * the unit of a host data set whose columns count up by one: lane of point
@@ -381,6 +382,8 @@ struct SegMap {
 //    offset is smaller by s from the lane s further up (a wave's last lanes
 //    recompute the next wave's first points: W = 64 - S owners per wave), and
 //    evaluates ("pulls") the contributions of other data sets itself;
+//  * where a data set's references come in no order, a unit over the cluster's
+//    variables that pulls its contributions through incidence lists;
 //  * otherwise a unit over the cluster's variables, one lane each, which pulls
 //    every contribution (through the column's inverse table where a column
 //    has gaps).
@@ -467,8 +470,9 @@ struct Model {
     // reduction maps (positions in the first-order buffer: grad part first)
     SegMap grad_map, jt_map, h_map, par_map;
     // sums finished by the units (per SumKind); device models run them, and
-    // their maps hold the other variables only (host-only models, and batches
-    // whose instances' plans differ, use the general maps and units)
+    // their maps hold the other variables only (host-only and lean models use
+    // the general maps and units).  A batch runs instances of one plan
+    // (own_sig) in one launch, each with its own plan's units
     OwnPlan own[SUM_COUNT];
     bool use_own = false;
     // a device-memory budget left no room for what finishing units need beside

@@ -146,12 +146,16 @@ struct Ahead {
 };
 // Fills ExaMulti::in and inst from the call records.
 void multi_inputs(ExaMulti& mc);
-// Whether a launch reads ahead: its stores sweep the last-level cache (256 MB)
-// and outweigh its reads.  Launches that mostly read, or write less, find
-// their inputs in that cache at the next iterate, and the extra workgroups
-// cost them up to 20% (64 networks: constraints 23 / 27 us without / with,
-// J v 26 / 32; every callback 174 / 170 with inputs in the cache, 213 / 196
-// with inputs from HBM; the trajectory's interior-point set 124 / 82 us).
+// Whether a launch reads ahead: its stores outweigh its reads, and with three
+// sets of buffers in turn they sweep the last-level cache (256 MB), so that the
+// next iterate's inputs come from HBM.  One set's inputs stay in that cache,
+// and the extra workgroups then cost a few per cent.  Every callback, us
+// without / with the tiles, three sets in turn and one: the 1,000,000-step
+// trajectory 158 / 126 and 103 / 107, its interior-point set 91 / 73 and
+// 69 / 70, the 1000 x 1000 grid 63 / 52 and 39 / 38, 64 networks 169 / 145 and
+// 121 / 130.  Launches that mostly read, or write less, find their inputs in the
+// cache either way, and the workgroups cost them up to 20% (64 networks:
+// constraints 23 / 27 us, J v 26 / 32).
 inline bool reads_ahead(int64_t in, int64_t out) { return out >= in && out >= (int64_t)96 << 20; }
 // Bytes a unit's tiles write as outputs.
 int64_t tile_outputs(const Model& M, int mode, const ExaTile* t, size_t n);
