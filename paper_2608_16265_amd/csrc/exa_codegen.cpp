@@ -1923,6 +1923,16 @@ __device__ __forceinline__ const EXA_K ExaInstDev* exa_again(const EXA_K ExaInst
     asm volatile("" : "+s"(p));
     return p;
 }
+// The launch record anew, in each case of a several-callback kernel.  Read
+// plainly, fields that several cases share are loaded in the branches that
+// choose among them, one wait after another before a tile's own loads begin
+// (every callback, 200 and 20,000 steps of a trajectory: 8.0 and 9.7 us, so 7.5
+// and 8.9; 118 buses 4.6 and 4.45; 177 registers of a one-pass kernel, 167).
+__device__ __forceinline__ const ExaMulti& exa_here(const ExaMulti& C) {
+    int z = 0;
+    asm volatile("" : "+s"(z));
+    return (&C)[z];
+}
 // Reads a tile's input range into this XCD's L2, one dword per 128-byte line:
 // 256 lanes cover 32 KB with one load each.  A kernel holds one copy, whatever
 // the modes whose inputs it reads: a copy per mode took 0.3 s to compile.
@@ -2002,9 +2012,9 @@ __device__ __forceinline__ void exa_ahead(const double* x, const double* y, cons
         kernel(kernel_name(mode), mode_lds_doubles(M, mode), cases, mode_reads_ahead(mode));
     }
     // Several callbacks in one launch: a tile's mode sits above
-    // EXA_MODE_SHIFT in its code, and its case passes that mode's call (a
-    // constant index, so the calls stay in kernel arguments).  One tile per
-    // workgroup, remapped per XCD as in the single-callback kernels.
+    // EXA_MODE_SHIFT in its code, and its case passes that mode's call out of
+    // the kernel arguments (exa_here).  One tile per workgroup, remapped per
+    // XCD as in the single-callback kernels.
     // exa_k_multi runs per-callback tiles; exa_k_onepass runs multi units
     // (every selected job of a point from one set of loads) with the
     // objective's and the gradient's zero tiles.  Two kernels, so that each
@@ -2026,6 +2036,10 @@ __device__ __forceinline__ void exa_ahead(const double* x, const double* y, cons
         os << "    }\n";
         os << "}\n";
     };
+    // a case of a several-callback kernel, its launch record read anew (H)
+    auto here = [](int mode, int code) {
+        return "case " + std::to_string((mode << EXA_MODE_SHIFT) | code) + ": { const ExaMulti& H = exa_here(C); ";
+    };
     // the units of a mode in a several-callback kernel; M_LAG's tiles use the
     // call record of J^T w
     auto mode_cases = [&](int mode, std::vector<std::string>& cases) {
@@ -2033,22 +2047,20 @@ __device__ __forceinline__ void exa_ahead(const double* x, const double* y, cons
         if (mode != M_LAG && emits_general(M, mode))
             for (int fused = 0; fused < 2; ++fused)
                 for (auto& u : units_for(M, mode, fused != 0)) codes.insert(u.code);
-        const std::string K = "C.c[" + std::to_string(mode == M_LAG ? (int)M_JTPROD : mode) + "]";
+        const std::string K = "H.c[" + std::to_string(mode == M_LAG ? (int)M_JTPROD : mode) + "]";
         auto add = [&](int c, const char* pre) {
-            cases.push_back("case " + std::to_string((mode << EXA_MODE_SHIFT) | c) + ": " + pre + mode_name(mode) + "_" +
-                            std::to_string(c) + "(" + K + ", I, T, lds); break;");
+            cases.push_back(here(mode, c) + pre + mode_name(mode) + "_" + std::to_string(c) + "(" + K + ", I, T, lds); break; }");
         };
         for (int c : codes) add(c, "unit_");
         const OwnPlan* plan = own_plan(M, mode, true);
         if (!plan) return;
         for (const OwnUnit& u : plan->units) add(u.code, "own_");
         if (mode != M_GRAD)
-            cases.push_back("case " + std::to_string((mode << EXA_MODE_SHIFT) | EXA_ZERO_TILE) + ": " +
-                            own_fill(mode, K, "I") + "; break;");
+            cases.push_back(here(mode, EXA_ZERO_TILE) + own_fill(mode, K, "I") + "; break; }");
     };
-    const std::string G = "C.c[" + std::to_string(M_GRAD) + "]";
-    const std::string zero_case = "case " + std::to_string((M_GRAD << EXA_MODE_SHIFT) | EXA_ZERO_TILE) +
-                                  ": exa_fill((" + G + ".direct ? " + G + ".out0 : " + G + ".out1) + I.off[" + std::to_string(EXA_OFF_X) + "] + T.start, T.count, 0.0); break;";
+    const std::string G = "H.c[" + std::to_string(M_GRAD) + "]";
+    const std::string zero_case = here(M_GRAD, EXA_ZERO_TILE) + "exa_fill((" + G + ".direct ? " + G + ".out0 : " + G +
+                                  ".out1) + I.off[" + std::to_string(EXA_OFF_X) + "] + T.start, T.count, 0.0); break; }";
     if (M.lag_units) os << own_units(M, M_LAG, ntmp, live);
     // every unit's tiles share a kernel's register budget: ask for at least
     // four waves per SIMD, so that one wave of the launch fits on the chip at
@@ -2083,8 +2095,8 @@ __device__ __forceinline__ void exa_ahead(const double* x, const double* y, cons
                 UnitLive L;
                 os << unit_tile(M, mode, kv.second, ntmp, L);
                 if (live) (*live)[{mode, kv.first}] = L;
-                cases.push_back("case " + std::to_string((mode << EXA_MODE_SHIFT) | kv.first) + ": unit_" +
-                                mode_name(mode) + "_" + std::to_string(kv.first) + "(C, I, T, lds); break;");
+                cases.push_back(here(mode, kv.first) + "unit_" + mode_name(mode) + "_" + std::to_string(kv.first) +
+                                "(H, I, T, lds); break; }");
             }
         }
         // the objective's and J^T w's tiles, and those of sums whose units
