@@ -1923,15 +1923,16 @@ __device__ __forceinline__ const EXA_K ExaInstDev* exa_again(const EXA_K ExaInst
     asm volatile("" : "+s"(p));
     return p;
 }
-// The launch record anew, in each case of a several-callback kernel.  Read
-// plainly, fields that several cases share are loaded in the branches that
-// choose among them, one wait after another before a tile's own loads begin
-// (every callback, 200 and 20,000 steps of a trajectory: 8.0 and 9.7 us, so 7.5
-// and 8.9; 118 buses 4.6 and 4.45; 177 registers of a one-pass kernel, 167).
-__device__ __forceinline__ const ExaMulti& exa_here(const ExaMulti& C) {
-    int z = 0;
-    asm volatile("" : "+s"(z));
-    return (&C)[z];
+// The launch record (a several-callback kernel's only argument) anew, in each
+// case; no instance is below 0.  Read plainly, fields that several cases share
+// are loaded in the branches that choose among them, one wait after another
+// before a tile's own loads begin (every callback, 200 and 20,000 steps of a
+// trajectory: 8.0 and 9.7 us, so 7.5 and 8.9; 118 buses 4.6 and 4.45; 177
+// registers of a one-pass kernel, 167).  From where the arguments lie: through
+// the parameter's address a kernel of many cases copied it to private memory.
+__device__ __forceinline__ const ExaMulti& exa_here(const ExaTile& T) {
+    const EXA_K ExaMulti* p = (const EXA_K ExaMulti*)__builtin_amdgcn_kernarg_segment_ptr();
+    return *(const ExaMulti*)(p + (T.inst >> 31));
 }
 // Reads a tile's input range into this XCD's L2, one dword per 128-byte line:
 // 256 lanes cover 32 KB with one load each.  A kernel holds one copy, whatever
@@ -2038,7 +2039,7 @@ __device__ __forceinline__ void exa_ahead(const double* x, const double* y, cons
     };
     // a case of a several-callback kernel, its launch record read anew (H)
     auto here = [](int mode, int code) {
-        return "case " + std::to_string((mode << EXA_MODE_SHIFT) | code) + ": { const ExaMulti& H = exa_here(C); ";
+        return "case " + std::to_string((mode << EXA_MODE_SHIFT) | code) + ": { const ExaMulti& H = exa_here(T); ";
     };
     // the units of a mode in a several-callback kernel; M_LAG's tiles use the
     // call record of J^T w
